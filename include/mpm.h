@@ -107,8 +107,8 @@ typedef enum {
  * MPM_SCHEDULE_AUTO takes the 64 x 64 blocks when the batch has at most 32
  * blocks of 256 x 256, else the symmetric schedule when it needs fewer work
  * rounds on the device's compute units, else the full one. The choice applies
- * to rows whose byte length is a multiple of 64; other rows use a kernel
- * without one. The partials (and everything reduced from them) are
+ * to rows whose byte length is a multiple of 64; for other rows the library
+ * always picks. The partials (and everything reduced from them) are
  * bit-identical under every schedule.
  */
 typedef enum {
@@ -220,8 +220,8 @@ int mpm_affinity_compact(const void* x, const int32_t* x_off, const float* x_inv
  * work a call issues: about 2 * w^2 * D flops per w x w block, nb^2 blocks per
  * image of nb = ceil(n_b / w) blocks under the full schedules (w = 256, or 64
  * for MPM_SCHEDULE_FULL_64) and nb (nb + 1) / 2 under the symmetric one
- * (w = 256). Rows whose byte length is not a multiple of 64 always report
- * MPM_SCHEDULE_FULL. Returns MPM_OK, MPM_ERR_INVALID_ARG for bad sizes, an
+ * (w = 256). Rows whose byte length is not a multiple of 64, for which the
+ * argument is not taken, always report MPM_SCHEDULE_FULL. Returns MPM_OK, MPM_ERR_INVALID_ARG for bad sizes, an
  * unknown schedule or a NULL pointer, or MPM_ERR_HIP when the device cannot be
  * queried.
  */
@@ -232,8 +232,8 @@ int mpm_affinity_schedule_used(int32_t B, int32_t N, int32_t D, int32_t dt, int3
  * block_rows on the current device, written to *rows (a host pointer): 256 or 128
  * (square blocks on the symmetric schedule; with block_rows 0, whichever an estimate of
  * the launch on a full raster grid of grid_w columns, at this window, finds faster), or
- * N for rows whose byte length is not a multiple of 64 (a kernel that runs each query
- * block's whole band). For reporting. Returns MPM_OK, MPM_ERR_INVALID_ARG for bad
+ * N for rows whose byte length is not a multiple of 64 (the argument is not taken and
+ * the library's pick not reported). For reporting. Returns MPM_OK, MPM_ERR_INVALID_ARG for bad
  * sizes, grid_w, window or block_rows (as mpm_merge_local) or a NULL pointer, or
  * MPM_ERR_HIP when the device cannot be queried.
  */

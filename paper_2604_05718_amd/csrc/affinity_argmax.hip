@@ -10,19 +10,18 @@
 // and rounding the unit vectors back to bfloat16 would cost about three
 // decimal digits of the cosine, so the inputs are never rescaled.
 //
-// Tiling. A workgroup owns QT queries of one image and streams every
-// candidate tile of CT tokens past them; the N x N affinity only ever lives
-// in MFMA accumulators. Per candidate tile the K dimension (D) is staged
-// through LDS in 128-byte chunks, double-buffered: the global loads of the
-// next chunk are in flight while the current one feeds the MFMAs.
+// Tiling. A work item is a block of QT queries against a tile of CT candidates
+// of one image; the N x N affinity only ever lives in MFMA accumulators. The K
+// dimension (D) of both is staged through LDS in 128-byte chunks,
+// double-buffered: the global loads of the next chunk are in flight while the
+// current one feeds the MFMAs.
 // In the 32x32 MFMA the candidate is the row operand and the query the column
 // operand, so each lane's 16 accumulator values belong to ONE query and 16
 // different candidates: the running (max, index) reduction is per lane, in
 // registers, in ascending candidate order, and lanes/waves are merged
 // lexicographically (larger score, then smaller index) only once at the end.
-// The candidate norms are accumulated from the same register fragments that
-// feed the MFMAs (one wave row per candidate slice), so X is read once per
-// tile and no separate normalisation pass exists.
+// The norms are summed from the same LDS rows that feed the MFMAs, so X is read
+// once per tile and no separate normalisation pass exists.
 #include <hip/hip_ext.h>
 
 #include <algorithm>
@@ -83,6 +82,8 @@ struct Mfma<F32> {
     }
 };
 
+constexpr int kChunkBytes = 128;  // bytes of each row per LDS stage
+constexpr int kSplitRows = 256;   // block rows of the symmetric schedule that has a half-block launch
 constexpr int kXcds = 8;  // MI355X: workgroups are dealt round-robin to 8 XCDs, each with its own L2
 
 // Workgroup barrier that waits only for this wave's LDS operations (not for
@@ -94,275 +95,15 @@ __device__ __forceinline__ void lds_barrier()
     asm volatile("" ::: "memory");
 }
 
-// Register-staged variant (any 16-byte row size, float32 or bfloat16): a
-// workgroup owns QT queries and loops over every candidate tile itself.
-// WC x WQ waves; each wave computes MT x NT tiles of 32 candidates x 32 queries;
-// CHUNK bytes of the K dimension are staged per LDS buffer.
-//
-// LOCAL: the locality constraint of Sec. 5 (candidates restricted to a window on the
-// token grid; positions in `win`). A token's position is a raster index on a grid of
-// win.grid_w columns (win.pos packed like x; null: the token's index in its image);
-// j is a candidate of i when both lie within win.radius rows and columns of each
-// other. Positions are non-decreasing in row along an image (raster order, which the
-// left-to-right ids keep for merged tokens), so the candidates of a query block lie in
-// a contiguous range of candidate tiles: only those are streamed, and every score is
-// masked by the window test.
+// The locality constraint of Sec. 5 (candidates restricted to a window on the token
+// grid): a token's position is a raster index on a grid of grid_w columns (pos packed
+// like x; null: the token's index in its image); j is a candidate of i when both lie
+// within radius rows and columns of each other. Positions are non-decreasing in row
+// along an image (raster order, which the left-to-right ids keep for merged tokens).
 struct Window {
     const int32_t* pos;
     int grid_w, radius;
 };
-
-template <class S, int WC, int WQ, int MT, int NT, int CHUNK, bool LOCAL = false>
-__global__ __launch_bounds__(WC * WQ * kWave) void affinity_argmax_kernel(
-    const uint8_t* __restrict__ x, const int32_t* __restrict__ x_off, int B, int N, int D, int qblocks,
-    int xcd_major, int T, float* __restrict__ pv, int32_t* __restrict__ pi, Window win)
-{
-    constexpr int THREADS = WC * WQ * kWave;
-    constexpr int CT = WC * MT * 32;     // candidates per tile
-    constexpr int QT = WQ * NT * 32;     // queries per workgroup
-    constexpr int STRIDE = CHUNK + 16;   // padded LDS row pitch (bytes)
-    constexpr int VPR = CHUNK / 16;      // 16-byte vectors per row per stage
-    constexpr int CLOADS = CT * VPR / THREADS;
-    constexpr int QLOADS = QT * VPR / THREADS;
-    static_assert(CT * VPR % THREADS == 0 && QT * VPR % THREADS == 0, "tile/thread mismatch");
-
-    __shared__ __attribute__((aligned(16))) uint8_t lds_c[2][CT * STRIDE];
-    __shared__ __attribute__((aligned(16))) uint8_t lds_q[2][QT * STRIDE];
-    __shared__ __attribute__((aligned(16))) float inv_c[2][CT];
-    __shared__ float red_v[WC][QT];
-    __shared__ int32_t red_i[WC][QT];
-    __shared__ int16_t cand_rc[LOCAL ? 2 : 1][LOCAL ? 2 * CT : 1];  // grid row and column per candidate
-
-    // Workgroup -> (image, query block). With xcd_major, consecutive ids that the
-    // hardware sends to the same XCD walk through the query blocks of one image
-    // before the next, so an image's candidate tiles are re-read from that XCD's L2.
-    int b, qb;
-    if (xcd_major) {
-        const int xcd = blockIdx.x % kXcds;
-        const int slot = blockIdx.x / kXcds;
-        b = xcd + kXcds * (slot / qblocks);
-        qb = slot % qblocks;
-    } else {
-        b = blockIdx.x / qblocks;
-        qb = blockIdx.x % qblocks;
-    }
-    if (b >= B) return;
-    const int qbase = qb * QT;
-    const int row0 = x_off ? x_off[b] : b * N;
-    const int n = x_off ? x_off[b + 1] - row0 : N;
-    if (qbase >= n) return;  // uniform over the workgroup, before any barrier
-
-    const int tid = threadIdx.x;
-    const int lane = tid & (kWave - 1);
-    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);  // wave-uniform: scalar registers and branches
-    const int wc = wave % WC;
-    const int wq = wave / WC;
-    const int lrow = lane & 31;   // operand row inside a 32-row MFMA tile
-    const int khalf = lane >> 5;  // which 16-byte half of a 32-byte k group
-
-    const long rowbytes = (long)D * S::kBytes;
-    const uint8_t* ximg = x + (long)row0 * rowbytes;
-    const int nchunks = (int)((rowbytes + CHUNK - 1) / CHUNK);
-    const int ntiles = (n + CT - 1) / CT;
-    // Candidate tiles [t_lo, t_hi] (all of them without the locality constraint).
-    int t_lo = 0, t_hi = ntiles - 1;
-    auto grid_pos = [&](int i) { return win.pos ? win.pos[row0 + i] : i; };
-    if (LOCAL) {
-        const int r_first = grid_pos(qbase) / win.grid_w;
-        const int r_last = grid_pos(min(qbase + QT, n) - 1) / win.grid_w;
-        while (t_lo < ntiles - 1 && grid_pos(min((t_lo + 1) * CT, n) - 1) / win.grid_w < r_first - win.radius) ++t_lo;
-        while (t_hi > t_lo && grid_pos(t_hi * CT) / win.grid_w > r_last + win.radius) --t_hi;
-    }
-    const int total = (t_hi - t_lo + 1) * nchunks;
-
-    u32x4 pc[CLOADS];
-    u32x4 pq[QLOADS];
-    const u32x4 zero = {0u, 0u, 0u, 0u};
-
-    auto gload = [&](int step) {
-        const int tile = t_lo + step / nchunks;
-        const long kb = (long)(step - (tile - t_lo) * nchunks) * CHUNK;
-#pragma unroll
-        for (int u = 0; u < CLOADS; ++u) {
-            const int slot = tid + u * THREADS;
-            const int r = slot / VPR;
-            const long kk = kb + (slot % VPR) * 16;
-            const int row = tile * CT + r;
-            pc[u] = (row < n && kk < rowbytes) ? load16(ximg + row * rowbytes + kk) : zero;
-        }
-#pragma unroll
-        for (int u = 0; u < QLOADS; ++u) {
-            const int slot = tid + u * THREADS;
-            const int r = slot / VPR;
-            const long kk = kb + (slot % VPR) * 16;
-            const int row = qbase + r;
-            pq[u] = (row < n && kk < rowbytes) ? load16(ximg + row * rowbytes + kk) : zero;
-        }
-    };
-    auto lstore = [&](int buf) {
-#pragma unroll
-        for (int u = 0; u < CLOADS; ++u) {
-            const int slot = tid + u * THREADS;
-            store16(&lds_c[buf][(slot / VPR) * STRIDE + (slot % VPR) * 16], pc[u]);
-        }
-#pragma unroll
-        for (int u = 0; u < QLOADS; ++u) {
-            const int slot = tid + u * THREADS;
-            store16(&lds_q[buf][(slot / VPR) * STRIDE + (slot % VPR) * 16], pq[u]);
-        }
-    };
-
-    f32x16 acc[MT][NT];
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = f32x16{};
-    float ss[MT];
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) ss[mt] = 0.0f;
-    float bv[NT];
-    int32_t bi[NT];
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt) {
-        bv[nt] = -__builtin_inff();
-        bi[nt] = -1;
-    }
-
-    gload(0);
-    lstore(0);
-    __syncthreads();
-
-    for (int step = 0; step < total; ++step) {
-        const int buf = step & 1;
-        if (step + 1 < total) gload(step + 1);
-
-        const uint8_t* lc = lds_c[buf] + (wc * MT * 32 + lrow) * STRIDE + khalf * 16;
-        const uint8_t* lq = lds_q[buf] + (wq * NT * 32 + lrow) * STRIDE + khalf * 16;
-#pragma unroll
-        for (int g = 0; g < CHUNK / 32; ++g) {
-            u32x4 a[MT], q[NT];
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt)
-                a[mt] = *reinterpret_cast<const u32x4*>(lc + mt * 32 * STRIDE + g * 32);
-#pragma unroll
-            for (int nt = 0; nt < NT; ++nt)
-                q[nt] = *reinterpret_cast<const u32x4*>(lq + nt * 32 * STRIDE + g * 32);
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-                for (int nt = 0; nt < NT; ++nt) Mfma<S>::mma(acc[mt][nt], a[mt], q[nt]);
-            // Candidate norms: m-tile mt is summed by the wave with wq == mt % WQ only.
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt)
-                if (mt % WQ == wq) ss[mt] = Mfma<S>::sumsq(a[mt], ss[mt]);
-        }
-
-        const int tile = t_lo + step / nchunks;
-        const bool tile_end = (step - (tile - t_lo) * nchunks) == nchunks - 1;
-        if (tile_end) {
-            if constexpr (LOCAL) {
-                // Grid row and column of each candidate of the tile (past the image: masked anyway).
-                for (int jl = tid; jl < CT; jl += THREADS) {
-                    const int j = tile * CT + jl;
-                    const int p = j < n ? grid_pos(j) : 0;
-                    cand_rc[tile & 1][2 * jl] = (int16_t)(p / win.grid_w);
-                    cand_rc[tile & 1][2 * jl + 1] = (int16_t)(p % win.grid_w);
-                }
-            }
-            // Lanes l and l+32 hold the two k halves of candidate row lrow.
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt) {
-                if (mt % WQ != wq) continue;
-                const float t = ss[mt] + __shfl_xor(ss[mt], 32);
-                ss[mt] = 0.0f;
-                if (khalf == 0) inv_c[tile & 1][wc * MT * 32 + mt * 32 + lrow] = 1.0f / fmaxf(sqrtf(t), 1e-12f);
-            }
-        }
-        if (step + 1 < total) lstore(buf ^ 1);
-        __syncthreads();
-
-        if (tile_end) {
-            // Epilogue: scale by the candidate's inverse norm, mask, running argmax.
-            const int cb = tile * CT;
-            const float* iv = inv_c[tile & 1];
-            const bool need_mask = LOCAL || (cb + CT > n) || (cb < qbase + QT && qbase < cb + CT);
-#pragma unroll
-            for (int nt = 0; nt < NT; ++nt) {
-                const int qi = qbase + wq * NT * 32 + nt * 32 + lrow;
-                int q_r = 0, q_c = 0;  // this lane's query cell (locality constraint)
-                if constexpr (LOCAL) {
-                    const int p = qi < n ? grid_pos(qi) : 0;
-                    q_r = p / win.grid_w;
-                    q_c = p % win.grid_w;
-                }
-#pragma unroll
-                for (int mt = 0; mt < MT; ++mt) {
-#pragma unroll
-                    for (int g = 0; g < 4; ++g) {
-                        // Accumulator element 4g+e of this lane is candidate row 8g + 4*khalf + e.
-                        const int jl = wc * MT * 32 + mt * 32 + 8 * g + 4 * khalf;
-                        const f32x4 ivv = *reinterpret_cast<const f32x4*>(&iv[jl]);
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) {
-                            const float s = acc[mt][nt][4 * g + e] * ivv[e];
-                            const int j = cb + jl + e;
-                            bool ok = !need_mask || (j < n && j != qi);
-                            if constexpr (LOCAL) {
-                                const int dr = cand_rc[tile & 1][2 * (jl + e)] - q_r;
-                                const int dc = cand_rc[tile & 1][2 * (jl + e) + 1] - q_c;
-                                ok = ok && dr <= win.radius && -dr <= win.radius && dc <= win.radius &&
-                                     -dc <= win.radius;
-                            }
-                            if (ok && s > bv[nt]) {
-                                bv[nt] = s;
-                                bi[nt] = j;
-                            }
-                        }
-                    }
-                    acc[mt][nt] = f32x16{};
-                }
-            }
-        }
-    }
-
-    // Merge the two lane halves (same query, interleaved candidate rows), then
-    // the WC candidate waves, lexicographically: larger score, then smaller index.
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt) {
-        float v = bv[nt];
-        int32_t i = bi[nt];
-        const float ov = __shfl_xor(v, 32);
-        const int32_t oi = __shfl_xor(i, 32);
-        if (ov > v || (ov == v && (uint32_t)oi < (uint32_t)i)) {
-            v = ov;
-            i = oi;
-        }
-        if (khalf == 0) {
-            const int ql = wq * NT * 32 + nt * 32 + lrow;
-            red_v[wc][ql] = v;
-            red_i[wc][ql] = i;
-        }
-    }
-    __syncthreads();
-    for (int ql = tid; ql < QT; ql += THREADS) {
-        const int qi = qbase + ql;
-        if (qi >= n) continue;
-        float v = red_v[0][ql];
-        int32_t i = red_i[0][ql];
-#pragma unroll
-        for (int w = 1; w < WC; ++w) {
-            const float ov = red_v[w][ql];
-            const int32_t oi = red_i[w][ql];
-            if (ov > v || (ov == v && (uint32_t)oi < (uint32_t)i)) {
-                v = ov;
-                i = oi;
-            }
-        }
-        // This kernel covers every candidate itself: one partial, in tile slot 0.
-        pv[(long)b * T * N + qi] = v;
-        pi[(long)b * T * N + qi] = i;
-    }
-}
 
 // Lane exchanges for the reverse-direction argmax of the symmetric schedule.
 // Each DPP pattern used is an involution on the lanes of a 16-lane row.
@@ -400,12 +141,12 @@ __device__ __forceinline__ void exchange_half(float* v, int32_t* ix, int upper)
     }
 }
 
-// Persistent variant for rows (bfloat16 or float32) that are a whole number of
-// CB-byte chunks; everything below is laid out in bytes, and Mfma<S> consumes
-// the same 16-byte fragments for either type. Work item = (image, query block of QT, candidate tile of CT); an item
-// streams its two operand blocks through a STAGES-deep ring of LDS buffers
-// filled by direct global->LDS loads (global_load_lds_dwordx4), runs the K loop
-// on MFMA, then reduces its tile to one (score, index) partial per query.
+// Persistent kernel for rows (bfloat16 or float32) of any whole number of 16-byte
+// pieces; everything below is laid out in bytes, and Mfma<S> consumes the same 16-byte
+// fragments for either type. Work item = (image, query block of QT, candidate tile of
+// CT); an item streams its two operand blocks in 128-byte chunks of the rows through
+// two LDS stages filled by direct global->LDS loads (global_load_lds_dwordx4), runs the
+// K loop on MFMA, then reduces its tile to one (score, index) partial per query.
 //
 // Scheduling for the 8 per-XCD L2 caches: workgroups are dealt round-robin to
 // the XCDs, so workgroup w serves XCD group w % xcds; a group owns the images
@@ -415,28 +156,31 @@ __device__ __forceinline__ void exchange_half(float* v, int32_t* ix, int upper)
 // fetched from HBM once and re-read from that XCD's L2 by the other items that
 // use it, instead of being refetched once per candidate tile.
 //
-// Pipeline. The chunks of all the workgroup's items form one stream. With
-// STAGES >= 3, before chunk c is consumed this wave's loads of chunks up to c+1
-// have landed and a barrier makes every wave's loads visible and retires the
-// ring slot of chunk c-1, which is then refilled with chunk c+STAGES-1. Within a
-// chunk the MFMA fragments are double-buffered: the fragments of the next
-// k-group (for the last k-group: of the next chunk, already visible) are
-// requested before the current k-group's MFMAs issue, so LDS latency hides
-// behind the matrix cores. With STAGES == 2 (128-byte chunks: two stages fill
-// 128 KB of LDS) the barrier before chunk c makes chunk c visible and retires
-// chunk c-1's slot; chunk c's first fragments are requested, then chunk c+1's
-// loads into the retired slot, so loads run one chunk ahead. Against 64-byte
-// chunks in four stages this halves the barriers and the load instructions per
-// byte, and each load instruction reads whole 128-byte lines.
+// Pipeline. The chunks of all the workgroup's items form one stream. The barrier before
+// chunk c makes chunk c visible and retires chunk c-1's stage; chunk c's first fragments
+// are requested, then chunk c+1's loads into the retired stage, so loads run one chunk
+// ahead. Within a chunk the MFMA fragments are double-buffered: the fragments of the next
+// k-group are requested before the current k-group's MFMAs issue, so LDS latency hides
+// behind the matrix cores. Each load instruction reads whole 128-byte lines; 64-byte
+// chunks in four stages had twice the barriers and half the load rate (95.5 against 85.6
+// us on 64 images of 1024 rows of 1536 bytes).
 // The global->LDS loads are written as assembly: the compiler cannot tell which
 // ring slot they fill and would otherwise wait for all of them before every LDS
 // read; their completion is waited for explicitly (vmcnt) instead.
 //
-// LDS layout of one stage: CB bytes of K per row (CB = 64 or 128), rows of an
-// operand stored one after the other, with the CB/16 16-byte columns of a row
-// permuted by an XOR swizzle: column c of row r sits in slot c ^ swz(r), with
-//   CB = 128: swz(r) = ((r % 8) / 2) | (((r / 8) % 2) << 2),
-//   CB =  64: swz(r) = (r / 4) % 4.
+// TAIL: rows that are no whole number of chunks. A row's last chunk is loaded with its
+// columns past the row's end clamped to the row's last 16 bytes (in bounds for the last
+// row of x too), and each lane overwrites the pieces it loaded there with zeros in LDS
+// before the barrier that makes the chunk visible, so the chunk loop itself is the same.
+// Zero pieces add nothing to the products or norms: the scores are bit-identical to a
+// K loop that ends with the row. The chunk is computed whole (400-byte rows issue 512 bytes
+// of products); cutting its empty k-groups off would put a branch into the chunk loop. 24
+// packed images of 346 to 990 rows of 400 bytes: 20 us, against 59 us for a kernel that
+// staged such rows through registers, one workgroup per query block.
+//
+// LDS layout of one stage: CB = 128 bytes of K per row, rows of an operand stored one
+// after the other, with the 16-byte columns of a row permuted by an XOR swizzle: column c
+// of row r sits in slot c ^ swz(r), swz(r) = ((r % 8) / 2) | (((r / 8) % 2) << 2).
 // One load instruction fills 1 KB = 1024/CB consecutive rows: lane l reads 16
 // bytes of row l / (CB/16) (the lanes of a row cover its CB contiguous bytes of
 // global memory) and lands at 16*l. An MFMA fragment read (one 16-byte column
@@ -466,7 +210,7 @@ __host__ __device__ inline int deferred_diagonals(int nimg, int nb, int slots)
     return (m > 0 && 2 * m <= slots && m <= nimg * nb) ? m : 0;
 }
 
-// HALVES: the second launch of a symmetric schedule on the two-stage ring. The first
+// HALVES: the second launch of a symmetric schedule on 256-row blocks. The first
 // launch (SYM) leaves out the last deferred_diagonals() diagonal blocks of its XCD group
 // (all of the last images', then the last ones of the image before), so that its slots
 // take whole rounds; this launch runs each deferred block as two items of the block's
@@ -476,7 +220,7 @@ __host__ __device__ inline int deferred_diagonals(int nimg, int nb, int slots)
 //
 // LOCAL: the locality constraint of Sec. 5 on the full schedule. A work item is a query
 // block with every candidate tile its window band reaches ([tlo, thi], found from the
-// positions at the block and tile boundaries, as in the register-staged kernel); the item
+// positions at the block and tile boundaries); the item
 // runs its tiles one after the other through the same ring (one K loop per tile), keeps
 // each query's running best across them in registers, masks every score by the window
 // test, and writes one partial per query (tile slot 0, tile width N). Positions (win.pos,
@@ -487,8 +231,7 @@ __host__ __device__ inline int deferred_diagonals(int nimg, int nb, int slots)
 // from the fragments in the K loop (vector ALU work in the K loop adds to its time about
 // one for one). Otherwise xinv is unused and every k-group's norm sums run without a
 // branch; each case is its own build.
-template <class S, int WC, int WQ, int MT, int NT, int CB, int STAGES, bool SYM, bool HALVES = false,
-          bool LOCAL = false, bool GIVEN = false>
+template <class S, int WC, int WQ, int MT, int NT, bool SYM, bool HALVES, bool LOCAL, bool GIVEN, bool TAIL>
 __global__ __launch_bounds__(WC * WQ * kWave, 2) void affinity_partial_kernel(  // 2 waves per SIMD
     const uint8_t* __restrict__ x, const int32_t* __restrict__ x_off, int B, int N, int D, int T, int xcds,
     int slots, float* __restrict__ pv, int32_t* __restrict__ pi, const float* __restrict__ xinv, Window win)
@@ -497,7 +240,7 @@ __global__ __launch_bounds__(WC * WQ * kWave, 2) void affinity_partial_kernel(  
     constexpr int WAVES = WC * WQ;
     constexpr int CT = WC * MT * 32;
     constexpr int QT = WQ * NT * 32;
-    static_assert(CB == 64 || CB == 128, "swizzled layouts exist for 64- and 128-byte row chunks");
+    constexpr int CB = kChunkBytes;
     constexpr int NS = CB / 16;                       // 16-byte slots per row
     constexpr int RPI = 64 / NS;                      // rows per load instruction (1 KB)
     // Rows a stage holds: the candidate tile, then the query block (none for a half item,
@@ -508,10 +251,9 @@ __global__ __launch_bounds__(WC * WQ * kWave, 2) void affinity_partial_kernel(  
     constexpr int STAGE_BYTES = (CT + QROWS) * CB;
     constexpr int KG = CB / 32;                       // 32-byte k-groups (one MFMA k-step each) per chunk
     static_assert(GROUPS % WAVES == 0 && CT % RPI == 0 && CT % 32 == 0 && QT % 32 == 0, "stage/wave mismatch");
-    static_assert(STAGES >= 2 && (STAGES - 2) * LOADS < 64, "pipeline depth / vmcnt range");
     static_assert(KG % 2 == 0, "the fragment double buffer alternates over an even number of k-groups");
 
-    __shared__ __attribute__((aligned(1024))) uint8_t lds[STAGES * STAGE_BYTES];
+    __shared__ __attribute__((aligned(1024))) uint8_t lds[2 * STAGE_BYTES];
     __shared__ __attribute__((aligned(16))) float inv_c[CT];
     __shared__ float red_v[WC][QT];
     __shared__ int32_t red_i[WC][QT];
@@ -542,14 +284,14 @@ __global__ __launch_bounds__(WC * WQ * kWave, 2) void affinity_partial_kernel(  
     const int per_img = LOCAL ? nqb : (SYM ? nqb * (nqb + 1) / 2 : nqb * nct);
     const int nimg = (B - group + xcds - 1) / xcds;
     static_assert(!HALVES || (!SYM && 2 * QT == CT), "half items: forward only, half a block of queries");
-    constexpr bool SPLIT = SYM && STAGES == 2 && !LOCAL;  // the layouts the second launch exists for
+    constexpr bool SPLIT = SYM && !LOCAL && CT == kSplitRows;  // the blocks the second launch exists for
     const int ndef = (SPLIT || HALVES) ? deferred_diagonals(nimg, nct, slots) : 0;
     const int dfull = ndef / nct, dpart = ndef % nct;
     const int dimg = nimg - dfull - 1;                        // the image with dpart deferred
     const int upto_dimg = (dimg + 1) * per_img - dpart;       // first-launch items of images 0..dimg
     const int nitems = HALVES ? 2 * ndef : nimg * per_img - ndef;
     const long rowbytes = (long)D * S::kBytes;
-    const int nchunks = (int)(rowbytes / CB);
+    const int nchunks = (int)((rowbytes + CB - 1) / CB);
 
     // Item cursor; all fields are uniform over the workgroup.
     struct Item {
@@ -642,11 +384,13 @@ __global__ __launch_bounds__(WC * WQ * kWave, 2) void affinity_partial_kernel(  
     };
 
     // Swizzle of the 16-byte column slot for a row (see the layout note above).
-    auto swz = [](int r) {
-        return CB == 128 ? (((r & 7) >> 1) | (((r >> 3) & 1) << 2)) : ((r >> 2) & 3);
-    };
+    auto swz = [](int r) { return ((r & 7) >> 1) | (((r >> 3) & 1) << 2); };
     const int lrowi = lane / NS;                          // row inside a load group
     const int lslot = lane % NS;                          // column slot this lane fills
+    // The byte column of a chunk this lane loads: the swizzle of its rows is the same in every
+    // load group of a wave (groups of a wave are a whole number of 16-row periods apart).
+    static_assert(RPI * WAVES % 16 == 0 && CT % 16 == 0, "one column per lane");
+    const int lcol = (lslot ^ swz((wave * RPI + lrowi) & 15)) << 4;
     // Load group u = wave + WAVES * i covers rows u*RPI .. u*RPI+RPI-1 of [cand; query].
     // Byte offsets (from the image's first row) of this lane's 16-byte pieces for
     // the issue cursor's item; they change per item, not per chunk.
@@ -662,7 +406,7 @@ __global__ __launch_bounds__(WC * WQ * kWave, 2) void affinity_partial_kernel(  
             const int r = u * RPI - (is_q ? CT : 0) + lrowi;   // row inside its operand block
             int row = (is_q ? it.qbase : it.cbase) + r;
             row = row < it.n ? row : it.n - 1;
-            o.v[i] = (uint32_t)row * (uint32_t)rowbytes + (uint32_t)((lslot ^ swz(r & 15)) << 4);
+            o.v[i] = (uint32_t)row * (uint32_t)rowbytes + (uint32_t)lcol;
         }
         return o;
     };
@@ -678,16 +422,18 @@ __global__ __launch_bounds__(WC * WQ * kWave, 2) void affinity_partial_kernel(  
     uint8_t* isb = lds;
     const uint8_t* ibase = x;
     bool iact = false;
+    uint32_t iback = 0;  // TAIL: how far this lane's column lies past its row's last 16 bytes
     auto issue_begin = [&]() {
         iact = ii.k < nitems;
-        isb = lds + (issued % STAGES) * STAGE_BYTES;
+        isb = lds + (issued & 1) * STAGE_BYTES;
+        if constexpr (TAIL) iback = (uint32_t)max(0, ichunk * CB + lcol - (int)(rowbytes - 16));
         ibase = x + (long)ii.row0 * rowbytes + (long)ichunk * CB;   // uniform
     };
     // Once the issue cursor is past its last item the loads go on, unconditionally (no branch
     // per load in the K loop): they re-read rows of the last item (valid addresses) into the
     // ring slot after the last chunk, which nothing reads any more.
     auto issue_part = [&](int i) {
-        const uint32_t off = ioff.v[i];
+        const uint32_t off = TAIL ? ioff.v[i] - iback : ioff.v[i];
         const uint32_t m0 =
             (uint32_t)(size_t)(__attribute__((address_space(3))) uint8_t*)(isb + (wave + WAVES * i) * RPI * CB);
         // The LDS destination goes in M0, which the instruction reads implicitly: an input
@@ -714,14 +460,12 @@ __global__ __launch_bounds__(WC * WQ * kWave, 2) void affinity_partial_kernel(  
     const int sw = swz(lrow & 15);
     const int lc_off = (wc * MT * 32 + lrow) * CB;
     // A half item's queries are rows qbase - cbase.. of its candidate tile. Its first value
-    // comes from the issue cursor's first item, which is the compute cursor's first item
-    // (the prologue of a deeper ring reads fragments before the compute cursor exists); a
-    // slot runs at most one half item (2 * ndef <= slots), so the read-ahead of a next
-    // chunk never crosses into another half item.
+    // comes from the issue cursor's first item, which is the compute cursor's first item; a
+    // slot runs at most one half item (2 * ndef <= slots).
     int lq_off = (HALVES ? ii.qbase - ii.cbase : CT) * CB + (wq * NT * 32 + lrow) * CB;
     u32x4 fa0[MT], fq0[NT], fa1[MT], fq1[NT];
     auto read_frags = [&](u32x4 (&fa)[MT], u32x4 (&fq)[NT], int chunk, int g) {
-        const uint8_t* sb = lds + (chunk % STAGES) * STAGE_BYTES;
+        const uint8_t* sb = lds + (chunk & 1) * STAGE_BYTES;
         const int col = ((2 * g + khalf) ^ sw) << 4;
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) fa[mt] = *reinterpret_cast<const u32x4*>(sb + lc_off + mt * 32 * CB + col);
@@ -754,18 +498,17 @@ __global__ __launch_bounds__(WC * WQ * kWave, 2) void affinity_partial_kernel(  
         sq[j] = 0.0f;
         own_q[j] = min(wc + j * WC, NT - 1) * 32 * CB;  // from lq_off
     }
-    // One load part before every PSTEP-th MFMA of a chunk: spread over all of the chunk's MFMAs
-    // with STAGES >= 3, over the first half with two stages (those loads must land before the
-    // chunk ends).
+    // One load part before every PSTEP-th MFMA of a chunk, over the first half of its MFMAs (the
+    // loads must land before the chunk ends).
     constexpr int PGROUPS = KG * MT * NT;  // MFMAs per chunk
-    constexpr int PSPAN = STAGES >= 3 ? PGROUPS : PGROUPS / 2;
+    constexpr int PSPAN = PGROUPS / 2;
     static_assert(PSPAN >= 1, "load parts per MFMA");
     constexpr int PSTEP = PSPAN >= LOADS ? PSPAN / LOADS : 1;              // MFMAs between load slots
     constexpr int PPER = PSPAN >= LOADS ? 1 : (LOADS + PSPAN - 1) / PSPAN;  // loads per slot (small tiles)
     auto mma_issue = [&](const u32x4 (&fa)[MT], const u32x4 (&fq)[NT], int chunk, int g) {
         u32x4 oc[NSC], oq[NSQ];
         if constexpr (!given) {
-            const uint8_t* sb = lds + (chunk % STAGES) * STAGE_BYTES;
+            const uint8_t* sb = lds + (chunk & 1) * STAGE_BYTES;
             const int col = ((2 * g + khalf) ^ sw) << 4;
 #pragma unroll
             for (int j = 0; j < NSC; ++j) oc[j] = *reinterpret_cast<const u32x4*>(sb + own_c[j] + col);
@@ -796,20 +539,7 @@ __global__ __launch_bounds__(WC * WQ * kWave, 2) void affinity_partial_kernel(  
             }
         }
     };
-    // vmcnt(n) with expcnt and lgkmcnt unconstrained.
-    constexpr int kWaitAhead = 0x0F70 | ((((STAGES - 2) * LOADS) & 15)) | ((((STAGES - 2) * LOADS) >> 4) << 14);
-
-    // Prologue: STAGES-1 chunks requested; with STAGES >= 3 chunk 0 has also landed, is
-    // visible and has its first fragments requested (with two stages the loop does that).
-#pragma unroll
-    for (int s = 0; s < STAGES - 1; ++s) issue_next();
-    if constexpr (STAGES >= 3) {
-        if (issued == STAGES - 1) __builtin_amdgcn_s_waitcnt(kWaitAhead);
-        else __builtin_amdgcn_s_waitcnt(0x0F70);
-        __builtin_amdgcn_s_barrier();
-        asm volatile("" ::: "memory");
-        read_frags(fa0, fq0, 0, 0);
-    }
+    issue_next();  // prologue: the first chunk
 
     Item ci = find(slot);  // compute cursor
     // With given norms, thread t fetches the inverse norm of candidate row t (t < CT) or
@@ -845,33 +575,28 @@ __global__ __launch_bounds__(WC * WQ * kWave, 2) void affinity_partial_kernel(  
     int cchunk = 0;
     int consumed = 0;
     while (ci.k < nitems) {
-        if constexpr (STAGES >= 3) {
-            // This wave's loads of chunks up to c+1 have landed (later ones may stay in flight) ...
-            const int ahead = issued - consumed - 2;
-            if (ahead >= STAGES - 2) __builtin_amdgcn_s_waitcnt(kWaitAhead);
-            else if (STAGES > 3 && ahead == 1)
-                __builtin_amdgcn_s_waitcnt(0x0F70 | (LOADS & 15) | ((LOADS >> 4) << 14));
-            else __builtin_amdgcn_s_waitcnt(0x0F70);
-            // ... every wave's are visible, and every wave is done with chunk c-1's slot.
-            __builtin_amdgcn_s_barrier();
-            asm volatile("" ::: "memory");
-            issue_begin();
-        } else {
-            // Chunk c has landed for this wave; after the barrier for every wave, and every
-            // wave is done with chunk c-1, whose slot then takes chunk c+1.
-            __builtin_amdgcn_s_waitcnt(0x0F70);
-            __builtin_amdgcn_s_barrier();
-            asm volatile("" ::: "memory");
-            read_frags(fa0, fq0, consumed, 0);
-            issue_begin();
+        // Chunk c has landed for this wave; after the barrier for every wave, and every
+        // wave is done with chunk c-1, whose stage then takes chunk c+1.
+        __builtin_amdgcn_s_waitcnt(0x0F70);
+        if constexpr (TAIL) {
+            if (cchunk == nchunks - 1) {
+                if (cchunk * CB + lcol >= rowbytes) {
+                    uint8_t* sb = lds + (consumed & 1) * STAGE_BYTES + lane * 16;
+#pragma unroll
+                    for (int i = 0; i < LOADS; ++i) store16(sb + (wave + WAVES * i) * RPI * CB, u32x4{0u, 0u, 0u, 0u});
+                }
+                __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
+            }
         }
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        read_frags(fa0, fq0, consumed, 0);
+        issue_begin();
 #pragma unroll
         for (int g = 0; g < KG; ++g) {
             if (g + 1 < KG) {
                 if ((g & 1) == 0) read_frags(fa1, fq1, consumed, g + 1);
                 else read_frags(fa0, fq0, consumed, g + 1);
-            } else if (STAGES >= 3 && issued > consumed + 1) {
-                read_frags(fa0, fq0, consumed + 1, 0);
             }
             if ((g & 1) == 0) mma_issue(fa0, fq0, consumed, g);
             else mma_issue(fa1, fq1, consumed, g);
@@ -1219,19 +944,14 @@ __global__ __launch_bounds__(WC * WQ * kWave, 2) void affinity_partial_kernel(  
     __builtin_amdgcn_s_waitcnt(0x0F70);  // the trailing loads land before the workgroup's LDS is released
 }
 
-// Persistent-kernel shape: 256 candidates x 256 queries on 8 waves, 128-byte K
-// chunks in a 2-deep ring (or 64-byte chunks 4 deep; 128 KB of LDS either way),
-// one workgroup per CU. The full
-// schedule splits the tile over 2 candidate x 4 query waves (128 x 64 each); the
-// symmetric one over 4 x 2 (64 x 128 each), so that its reverse direction merges 4
-// queries inside each lane before the cross-lane steps and carries half as many
-// rows through them.
-constexpr int kPWC = 2, kPWQ = 4, kPMT = 4, kPNT = 2, kPCB = 64, kPWGS = 1;
-// Rows that are a whole number of 128-byte chunks stream them through two stages;
-// other multiples of 64 bytes use 64-byte chunks in four stages.
-constexpr int kPCB2 = 128;
+// Block shapes. 256 x 256 on 8 waves (two 64 KB stages, one workgroup per CU): the full
+// schedule splits the tile over 2 candidate x 4 query waves (128 x 64 each), the symmetric
+// one over 4 x 2 (64 x 128 each), so that its reverse direction merges 4 queries inside
+// each lane before the cross-lane steps and carries half as many rows through them.
+constexpr int kPWC = 2, kPWQ = 4, kPMT = 4, kPNT = 2, kPWGS = 1;
 constexpr int kSWC = 4, kSWQ = 2, kSMT = 2, kSNT = 4;
 constexpr int kPCT = kPWC * kPMT * 32;
+static_assert(kPCT == kSplitRows, "the half-block launch splits the large blocks");
 // Small batches (few 256 x 256 blocks for the device's CUs) use 64 x 64 blocks on 4 waves
 // of one 32 x 32 tile each, so a single image of 1024 tokens still spreads over 256 CUs.
 constexpr int kTWC = 2, kTWQ = 2, kTMT = 1, kTNT = 1;
@@ -1241,11 +961,13 @@ static_assert(kTWQ * kTNT * 32 == kTCT && kPCT % kTCT == 0, "square small blocks
 static_assert(kSWC * kSMT * 32 == kPCT && kSWQ * kSNT * 32 == kPCT && kPWQ * kPNT * 32 == kPCT,
               "both schedules use 256 x 256 tiles, so their partials share one layout");
 
-bool use_persistent(int D, int dt) { return ((long)D * (dt == kBf16 ? 2 : 4)) % kPCB == 0; }
+// Rows that are a whole number of 64 bytes: the ones the schedule and block-size arguments
+// and given norms apply to.
+bool whole_64(int D, int dt) { return ((long)D * (dt == kBf16 ? 2 : 4)) % 64 == 0; }
 
 }  // namespace
 
-bool affinity_takes_norms(int D, int dt) { return dt == kBf16 && use_persistent(D, dt); }
+bool affinity_takes_norms(int D, int dt) { return dt == kBf16 && whole_64(D, dt); }
 
 namespace {
 
@@ -1266,62 +988,67 @@ bool defers_diagonals(int B, int N, int xcds, int slots)
     return false;
 }
 
-template <class S, int WC, int WQ, int MT, int NT, bool SYM, bool LOCAL, bool GIVEN>
+template <class S, int WC, int WQ, int MT, int NT, bool SYM, bool LOCAL, bool GIVEN, bool TAIL>
 void launch_persistent_as(const void* x, const int32_t* x_off, const float* xinv, int B, int N, int D, int T, int xcds,
-                       int groups, float* pv, int32_t* pi, hipStream_t stream, hipEvent_t start, hipEvent_t stop,
-                       Window win = Window{nullptr, 1, 0})
+                          int groups, float* pv, int32_t* pi, hipStream_t stream, hipEvent_t start, hipEvent_t stop,
+                          Window win)
 {
     const uint8_t* xb = static_cast<const uint8_t*>(x);
-    if (((long)D * S::kBytes) % kPCB2 == 0) {
-        // The symmetric schedule's deferred diagonal blocks, as half blocks, in a second launch
-        // (one item per slot); the timing events then span both.
-        const bool halves = SYM && !LOCAL && defers_diagonals(B, N, xcds, groups / xcds);
-        hipExtLaunchKernelGGL((affinity_partial_kernel<S, WC, WQ, MT, NT, kPCB2, 2, SYM, false, LOCAL, GIVEN>), dim3(groups),
-                              dim3(WC * WQ * kWave), 0, stream, start, halves ? nullptr : stop, 0, xb, x_off, B, N,
-                              D, T, xcds, groups / xcds, pv, pi, xinv, win);
-        if constexpr (SYM) {
-            if (halves)
-                hipExtLaunchKernelGGL((affinity_partial_kernel<S, WC, WQ, MT, NT / 2, kPCB2, 2, false, true, false, GIVEN>),
-                                      dim3(groups), dim3(WC * WQ * kWave), 0, stream, nullptr, stop, 0, xb, x_off, B,
-                                      N, D, T, xcds, groups / xcds, pv, pi, xinv, win);
-        }
-    } else
-        hipExtLaunchKernelGGL((affinity_partial_kernel<S, WC, WQ, MT, NT, kPCB, 4, SYM, false, LOCAL, GIVEN>), dim3(groups),
-                              dim3(WC * WQ * kWave), 0, stream, start, stop, 0, xb, x_off, B, N, D, T, xcds,
-                              groups / xcds, pv, pi, xinv, win);
+    // The symmetric schedule's deferred diagonal blocks, as half blocks, in a second launch
+    // (one item per slot); the timing events then span both.
+    constexpr bool SPLIT = SYM && !LOCAL && WC * MT * 32 == kSplitRows;
+    const bool halves = SPLIT && defers_diagonals(B, N, xcds, groups / xcds);
+    hipExtLaunchKernelGGL((affinity_partial_kernel<S, WC, WQ, MT, NT, SYM, false, LOCAL, GIVEN, TAIL>), dim3(groups),
+                          dim3(WC * WQ * kWave), 0, stream, start, halves ? nullptr : stop, 0, xb, x_off, B, N, D, T,
+                          xcds, groups / xcds, pv, pi, xinv, win);
+    if constexpr (SPLIT) {
+        if (halves)
+            hipExtLaunchKernelGGL((affinity_partial_kernel<S, WC, WQ, MT, NT / 2, false, true, false, GIVEN, TAIL>),
+                                  dim3(groups), dim3(WC * WQ * kWave), 0, stream, nullptr, stop, 0, xb, x_off, B, N, D,
+                                  T, xcds, groups / xcds, pv, pi, xinv, win);
+    }
 }
 
 // Given norms (bfloat16 only) and norms summed in the K loop are separate builds: with one
 // build and a run-time flag, the flag's branch per k-group cost the summing launches 2-4%,
 // and two builds alternating between insertions showed no instruction-cache penalty.
 template <class S, int WC, int WQ, int MT, int NT, bool SYM, bool LOCAL = false>
-void launch_persistent(const void* x, const int32_t* x_off, const float* xinv, int B, int N, int D, int T, int xcds,
-                       int groups, float* pv, int32_t* pi, hipStream_t stream, hipEvent_t start, hipEvent_t stop,
-                       Window win = Window{nullptr, 1, 0})
+void launch_blocks(const void* x, const int32_t* x_off, const float* xinv, int B, int N, int D, int T, int xcds,
+                   int groups, float* pv, int32_t* pi, hipStream_t stream, hipEvent_t start, hipEvent_t stop,
+                   Window win = Window{nullptr, 1, 0})
 {
+    const bool tail = ((long)D * S::kBytes) % kChunkBytes != 0;
     if constexpr (S::kBytes == 2) {
         if (xinv != nullptr) {
-            launch_persistent_as<S, WC, WQ, MT, NT, SYM, LOCAL, true>(x, x_off, xinv, B, N, D, T, xcds, groups, pv,
-                                                                      pi, stream, start, stop, win);
+            if (tail)
+                launch_persistent_as<S, WC, WQ, MT, NT, SYM, LOCAL, true, true>(x, x_off, xinv, B, N, D, T, xcds, groups,
+                                                                                pv, pi, stream, start, stop, win);
+            else
+                launch_persistent_as<S, WC, WQ, MT, NT, SYM, LOCAL, true, false>(x, x_off, xinv, B, N, D, T, xcds,
+                                                                                 groups, pv, pi, stream, start, stop,
+                                                                                 win);
             return;
         }
     }
-    launch_persistent_as<S, WC, WQ, MT, NT, SYM, LOCAL, false>(x, x_off, nullptr, B, N, D, T, xcds, groups, pv, pi,
-                                                               stream, start, stop, win);
+    if (tail)
+        launch_persistent_as<S, WC, WQ, MT, NT, SYM, LOCAL, false, true>(x, x_off, nullptr, B, N, D, T, xcds, groups, pv,
+                                                                         pi, stream, start, stop, win);
+    else
+        launch_persistent_as<S, WC, WQ, MT, NT, SYM, LOCAL, false, false>(x, x_off, nullptr, B, N, D, T, xcds, groups,
+                                                                          pv, pi, stream, start, stop, win);
 }
 
-template <class S, int WC, int WQ, int MT, int NT, int CHUNK, bool LOCAL = false>
-hipError_t launch_staged(const void* x, const int32_t* x_off, int B, int N, int D, int T, float* pv, int32_t* pi,
-                         hipStream_t stream, hipEvent_t start, hipEvent_t stop, Window win = Window{nullptr, 1, 0})
+template <int WC, int WQ, int MT, int NT, bool SYM, bool LOCAL = false>
+void launch_persistent(int dt, const void* x, const int32_t* x_off, const float* xinv, int B, int N, int D, int T,
+                       int xcds, int groups, float* pv, int32_t* pi, hipStream_t stream, hipEvent_t start,
+                       hipEvent_t stop, Window win = Window{nullptr, 1, 0})
 {
-    constexpr int QT = WQ * NT * 32;
-    const int qblocks = (N + QT - 1) / QT;
-    const int xcd_major = B >= kXcds ? 1 : 0;
-    const long groups = xcd_major ? (long)kXcds * ((B + kXcds - 1) / kXcds) * qblocks : (long)B * qblocks;
-    hipExtLaunchKernelGGL((affinity_argmax_kernel<S, WC, WQ, MT, NT, CHUNK, LOCAL>), dim3((unsigned)groups),
-                          dim3(WC * WQ * kWave), 0, stream, start, stop, 0, static_cast<const uint8_t*>(x), x_off, B, N,
-                          D, qblocks, xcd_major, T, pv, pi, win);
-    return hipGetLastError();
+    if (dt == kBf16)
+        launch_blocks<Bf16, WC, WQ, MT, NT, SYM, LOCAL>(x, x_off, xinv, B, N, D, T, xcds, groups, pv, pi, stream, start,
+                                                        stop, win);
+    else
+        launch_blocks<F32, WC, WQ, MT, NT, SYM, LOCAL>(x, x_off, nullptr, B, N, D, T, xcds, groups, pv, pi, stream,
+                                                       start, stop, win);
 }
 
 }  // namespace
@@ -1400,10 +1127,13 @@ double local_cost(int B, int N, int grid_w, int radius, int ts, int xcds, int sl
 
 bool valid_local_block_rows(int requested) { return requested == 0 || requested == kLCT || requested == kPCT; }
 
-int local_block_rows(int B, int N, int D, int dt, int grid_w, int radius, int requested)
+namespace {
+
+// The block rows a windowed launch runs (local_block_rows reports N for rows the argument
+// does not apply to).
+int local_rows(int B, int N, int D, int dt, int grid_w, int radius, int requested)
 {
-    if (!use_persistent(D, dt)) return N;
-    if (requested != 0) return requested;
+    if (requested != 0 && whole_64(D, dt)) return requested;
     const int cus = device_cus();
     if (cus <= 0) return kPCT;
     const int xcds = (cus % kXcds == 0 && B >= kXcds) ? kXcds : 1;
@@ -1412,24 +1142,55 @@ int local_block_rows(int B, int N, int D, int dt, int grid_w, int radius, int re
     return small < large ? kLCT : kPCT;
 }
 
+}  // namespace
+
+int local_block_rows(int B, int N, int D, int dt, int grid_w, int radius, int requested)
+{
+    if (!whole_64(D, dt)) return N;
+    return local_rows(B, N, D, dt, grid_w, radius, requested);
+}
+
+int local_tile_width(int B, int N, int D, int dt, int grid_w, int radius, int requested)
+{
+    return local_rows(B, N, D, dt, grid_w, radius, requested);
+}
+
+namespace {
+
+enum Blocks : int { kBlocks64, kBlocks256, kBlocksSym256 };
+
+// The block size and schedule of a launch: the requested one where the argument applies,
+// else (and for MPM_SCHEDULE_AUTO) small blocks for small batches, then the symmetric
+// schedule where it needs fewer rounds.
+Blocks pick_blocks(int B, int N, int D, int dt, int schedule)
+{
+    const int sched = whole_64(D, dt) ? schedule : (int)kScheduleAuto;
+    if (small_blocks(B, N, sched)) return kBlocks64;
+    const int cus = device_cus();
+    const int xcds = (cus % kXcds == 0 && B >= kXcds) ? kXcds : 1;
+    return symmetric_schedule(B, N, xcds, max(1, cus * kPWGS / xcds), sched) ? kBlocksSym256 : kBlocks256;
+}
+
+}  // namespace
+
 int partial_tile_width(int B, int D, int dt, int N, int schedule)
 {
-    if (!use_persistent(D, dt)) return N;
-    return small_blocks(B, N, schedule) ? kTCT : kPCT;
+    switch (pick_blocks(B, N, D, dt, schedule)) {
+    case kBlocks64: return kTCT;
+    default: return kPCT;
+    }
 }
 
 hipError_t affinity_schedule(int B, int N, int D, int dt, int schedule, int* used)
 {
     *used = kScheduleFull;
-    if (!use_persistent(D, dt)) return hipSuccess;  // the staged kernel covers every pair
-    if (small_blocks(B, N, schedule)) {
-        *used = kScheduleFull64;
-        return hipSuccess;
+    if (!whole_64(D, dt)) return hipSuccess;  // no choice of schedule
+    if (device_cus() <= 0) return hipErrorInvalidDevice;
+    switch (pick_blocks(B, N, D, dt, schedule)) {
+    case kBlocks64: *used = kScheduleFull64; break;
+    case kBlocks256: *used = kScheduleFull; break;
+    default: *used = kScheduleSymmetric; break;
     }
-    const int cus = device_cus();
-    if (cus <= 0) return hipErrorInvalidDevice;
-    const int xcds = (cus % kXcds == 0 && B >= kXcds) ? kXcds : 1;
-    if (symmetric_schedule(B, N, xcds, cus * kPWGS / xcds, schedule)) *used = kScheduleSymmetric;
     return hipSuccess;
 }
 
@@ -1438,42 +1199,25 @@ hipError_t launch_affinity(const void* x, const int32_t* x_off, int B, int N, in
 {
     const int T = partial_tiles(N);
     if (xinv && !affinity_takes_norms(D, dt)) return hipErrorInvalidValue;  // those kernels sum their own norms
-    if (use_persistent(D, dt)) {
-        const int cus = device_cus();
-        if (cus <= 0) return hipErrorInvalidDevice;
-        // kPWGS workgroups per CU. With a batch of at least 8 images, group the
-        // workgroups by XCD.
-        const int xcds = (cus % kXcds == 0 && B >= kXcds) ? kXcds : 1;
-        const int groups = cus * kPWGS;
-        if (small_blocks(B, N, schedule)) {
-            if (dt == kBf16)
-                launch_persistent<Bf16, kTWC, kTWQ, kTMT, kTNT, false>(x, x_off, xinv, B, N, D, T, xcds, groups, pv, pi,
-                                                                        stream, start, stop);
-            else
-                launch_persistent<F32, kTWC, kTWQ, kTMT, kTNT, false>(x, x_off, xinv, B, N, D, T, xcds, groups, pv, pi,
-                                                                       stream, start, stop);
-            return hipGetLastError();
-        }
-        const bool sym = symmetric_schedule(B, N, xcds, groups / xcds, schedule);
-        if (dt == kBf16) {
-            if (sym)
-                launch_persistent<Bf16, kSWC, kSWQ, kSMT, kSNT, true>(x, x_off, xinv, B, N, D, T, xcds, groups, pv, pi,
-                                                                       stream, start, stop);
-            else
-                launch_persistent<Bf16, kPWC, kPWQ, kPMT, kPNT, false>(x, x_off, xinv, B, N, D, T, xcds, groups, pv, pi,
-                                                                        stream, start, stop);
-        } else {
-            if (sym)
-                launch_persistent<F32, kSWC, kSWQ, kSMT, kSNT, true>(x, x_off, xinv, B, N, D, T, xcds, groups, pv, pi,
-                                                                      stream, start, stop);
-            else
-                launch_persistent<F32, kPWC, kPWQ, kPMT, kPNT, false>(x, x_off, xinv, B, N, D, T, xcds, groups, pv, pi,
-                                                                       stream, start, stop);
-        }
-        return hipGetLastError();
+    const int cus = device_cus();
+    if (cus <= 0) return hipErrorInvalidDevice;
+    // With a batch of at least 8 images, group the workgroups by XCD.
+    const int xcds = (cus % kXcds == 0 && B >= kXcds) ? kXcds : 1;
+    switch (pick_blocks(B, N, D, dt, schedule)) {
+    case kBlocks64:
+        launch_persistent<kTWC, kTWQ, kTMT, kTNT, false>(dt, x, x_off, xinv, B, N, D, T, xcds, cus * kPWGS, pv, pi,
+                                                         stream, start, stop);
+        break;
+    case kBlocksSym256:
+        launch_persistent<kSWC, kSWQ, kSMT, kSNT, true>(dt, x, x_off, xinv, B, N, D, T, xcds, cus * kPWGS, pv, pi,
+                                                        stream, start, stop);
+        break;
+    default:
+        launch_persistent<kPWC, kPWQ, kPMT, kPNT, false>(dt, x, x_off, xinv, B, N, D, T, xcds, cus * kPWGS, pv, pi,
+                                                         stream, start, stop);
+        break;
     }
-    if (dt == kBf16) return launch_staged<Bf16, 2, 4, 4, 2, 128>(x, x_off, B, N, D, T, pv, pi, stream, start, stop);
-    return launch_staged<F32, 2, 2, 2, 2, 128>(x, x_off, B, N, D, T, pv, pi, stream, start, stop);
+    return hipGetLastError();
 }
 
 hipError_t launch_affinity_local(const void* x, const int32_t* x_off, const float* xinv, const int32_t* pos,
@@ -1481,37 +1225,20 @@ hipError_t launch_affinity_local(const void* x, const int32_t* x_off, const floa
                                  int B, int N, int D, int dt, float* pv, int32_t* pi, hipStream_t stream,
                                  hipEvent_t start, hipEvent_t stop)
 {
+    // The persistent kernel on the symmetric schedule, one item per query block and the
+    // tiles of its band from its own on (given norms: bf16 only), with blocks of block_rows.
     const int T = partial_tiles(N);
     const Window win{pos, grid_w, radius};
-    if (use_persistent(D, dt)) {
-        // The persistent kernel on the symmetric schedule, one item per query block and the
-        // tiles of its band from its own on (given norms: bf16 only), with the block size
-        // local_block_rows picks (block_rows: the caller's, 0 to estimate it here).
-        const int cus = device_cus();
-        if (cus <= 0) return hipErrorInvalidDevice;
-        const int xcds = (cus % kXcds == 0 && B >= kXcds) ? kXcds : 1;
-        const bool small = local_block_rows(B, N, D, dt, grid_w, radius, block_rows) == kLCT;
-        if (small) {
-            if (dt == kBf16)
-                launch_persistent<Bf16, kLWC, kLWQ, kLMT, kLNT, true, true>(x, x_off, xinv, B, N, D, T, xcds,
-                                                                            cus * kLWGS, pv, pi, stream, start, stop,
-                                                                            win);
-            else
-                launch_persistent<F32, kLWC, kLWQ, kLMT, kLNT, true, true>(x, x_off, nullptr, B, N, D, T, xcds,
-                                                                           cus * kLWGS, pv, pi, stream, start, stop,
-                                                                           win);
-        } else if (dt == kBf16) {
-            launch_persistent<Bf16, kSWC, kSWQ, kSMT, kSNT, true, true>(x, x_off, xinv, B, N, D, T, xcds, cus * kPWGS,
-                                                                        pv, pi, stream, start, stop, win);
-        } else {
-            launch_persistent<F32, kSWC, kSWQ, kSMT, kSNT, true, true>(x, x_off, nullptr, B, N, D, T, xcds, cus * kPWGS,
-                                                                       pv, pi, stream, start, stop, win);
-        }
-        return hipGetLastError();
-    }
-    if (dt == kBf16)
-        return launch_staged<Bf16, 2, 4, 2, 2, 128, true>(x, x_off, B, N, D, T, pv, pi, stream, start, stop, win);
-    return launch_staged<F32, 2, 2, 2, 2, 128, true>(x, x_off, B, N, D, T, pv, pi, stream, start, stop, win);
+    const int cus = device_cus();
+    if (cus <= 0) return hipErrorInvalidDevice;
+    const int xcds = (cus % kXcds == 0 && B >= kXcds) ? kXcds : 1;
+    if (block_rows == kLCT)
+        launch_persistent<kLWC, kLWQ, kLMT, kLNT, true, true>(dt, x, x_off, xinv, B, N, D, T, xcds, cus * kLWGS, pv, pi,
+                                                              stream, start, stop, win);
+    else
+        launch_persistent<kSWC, kSWQ, kSMT, kSNT, true, true>(dt, x, x_off, xinv, B, N, D, T, xcds, cus * kPWGS, pv, pi,
+                                                              stream, start, stop, win);
+    return hipGetLastError();
 }
 
 }  // namespace mpm

@@ -526,7 +526,7 @@ int mpm_merge_local(const void* x, const int32_t* x_off, const float* x_inv, con
     MPM_LAUNCH_GATE();
     MPM_DATA_CHECK(checked_rows(x, x_off, x_inv, pos, grid_w, B, N, D, dt, as_stream(stream)));
     const hipStream_t st = as_stream(stream);
-    const int rows = mpm::local_block_rows(B, N, D, dt, grid_w, window, block_rows);
+    const int rows = mpm::local_tile_width(B, N, D, dt, grid_w, window, block_rows);
     hipError_t e = mpm::launch_affinity_local(x, x_off, x_inv, pos, grid_w, window, rows, B, N, D, dt, w.pv, w.pi, st,
                                               static_cast<hipEvent_t>(start_event),
                                               static_cast<hipEvent_t>(stop_event));

@@ -30,9 +30,11 @@ int partial_tile_width(int B, int D, int dt, int N, int schedule);
 // ... and of launch_affinity_local's kernel: the rows of its square blocks on the
 // persistent kernel's symmetric schedule (`requested`, 128 or 256; 0: whichever an
 // estimate of the launch on a full raster grid of grid_w columns finds faster on the
-// current device), else N (one slot covering the image).
+// current device). local_block_rows reports N for rows that are no whole number of 64
+// bytes, where `requested` is not taken; local_tile_width is what a launch runs.
 int local_block_rows(int B, int N, int D, int dt, int grid_w, int radius, int requested);
 bool valid_local_block_rows(int requested);
+int local_tile_width(int B, int N, int D, int dt, int grid_w, int radius, int requested);
 // The schedule (kScheduleFull, kScheduleSymmetric or kScheduleFull64) launch_affinity runs
 // for this shape and requested schedule on the current device.
 hipError_t affinity_schedule(int B, int N, int D, int dt, int schedule, int* used);
