@@ -104,9 +104,10 @@ typedef enum {
  * halves of their queries each. MPM_SCHEDULE_FULL_64 computes every pair of
  * 64 x 64 blocks, so that a small batch (a single image of 1024 tokens has 16
  * blocks of 256 x 256 but 256 of 64 x 64) still occupies every compute unit.
- * MPM_SCHEDULE_AUTO takes the 64 x 64 blocks when the batch has at most 32
- * blocks of 256 x 256, else the symmetric schedule when it needs fewer work
- * rounds on the device's compute units, else the full one. The choice applies
+ * MPM_SCHEDULE_AUTO takes the 64 x 64 blocks for small batches (at most 32
+ * blocks of 256 x 256 among them), else whichever of the symmetric schedule (on
+ * 256 x 256 or, where those would leave compute units idle, 128 x 128 blocks)
+ * and the full one an estimate of the launch finds faster. The choice applies
  * to rows whose byte length is a multiple of 64; for other rows the library
  * always picks. The partials (and everything reduced from them) are
  * bit-identical under every schedule.
@@ -146,8 +147,8 @@ int mpm_last_hip_error(void);
  *   pv    float[B*T*N], pi int32[B*T*N]  per-candidate-tile argmax partials,
  *                               T = ceil(N / 64) slots per token: tile t of image b
  *                               for token i at (b*T + t)*N + i; a launch fills the
- *                               first ceil(n_b / w) slots, w = the block width of
- *                               its schedule (64 or 256 tokens).
+ *                               first ceil(n_b / w) slots, w = the block width it
+ *                               runs (mpm_affinity_block_rows).
  * The sync region must be zero before a workspace's first use by
  * mpm_affinity_compact or mpm_merge (mpm_workspace_init); every call leaves it
  * zero again (an interrupted call may not). Returns 0 for B < 1 or N < 1.
@@ -218,14 +219,25 @@ int mpm_affinity_compact(const void* x, const int32_t* x_off, const float* x_inv
  * most N tokens of D channels of dtype dt under `schedule` on the current
  * device, written to *used (a host pointer). For reporting the matrix-core
  * work a call issues: about 2 * w^2 * D flops per w x w block, nb^2 blocks per
- * image of nb = ceil(n_b / w) blocks under the full schedules (w = 256, or 64
- * for MPM_SCHEDULE_FULL_64) and nb (nb + 1) / 2 under the symmetric one
- * (w = 256). Rows whose byte length is not a multiple of 64, for which the
+ * image of nb = ceil(n_b / w) blocks under the full schedules and nb (nb + 1) / 2
+ * under the symmetric one, w = mpm_affinity_block_rows. A call with offsets may
+ * pick another schedule than the one reported, that of a call without. Rows whose byte length is not a multiple of 64, for which the
  * argument is not taken, always report MPM_SCHEDULE_FULL. Returns MPM_OK, MPM_ERR_INVALID_ARG for bad sizes, an
  * unknown schedule or a NULL pointer, or MPM_ERR_HIP when the device cannot be
  * queried.
  */
 int mpm_affinity_schedule_used(int32_t B, int32_t N, int32_t D, int32_t dt, int32_t schedule, int32_t* used);
+
+/*
+ * The rows of the square blocks mpm_affinity runs for B images of at most N tokens of D
+ * channels of dtype dt under `schedule` on the current device, without offsets
+ * (packed = 0) or with them, written to *rows (a host pointer): 64, 128 or 256. This is
+ * the token width w of one partial in the workspace. For reporting. Returns MPM_OK,
+ * MPM_ERR_INVALID_ARG for bad sizes, an unknown schedule or a NULL pointer, or
+ * MPM_ERR_HIP when the device cannot be queried.
+ */
+int mpm_affinity_block_rows(int32_t B, int32_t N, int32_t D, int32_t dt, int32_t schedule, int32_t packed,
+                            int32_t* rows);
 
 /*
  * The block size mpm_merge_local's affinity runs for this shape, window and requested

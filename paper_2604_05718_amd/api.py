@@ -147,6 +147,16 @@ def affinity_schedule_used(B: int, N: int, D: int, dtype: torch.dtype, schedule:
     return {v: k for k, v in SCHEDULES.items()}[out.value]
 
 
+def affinity_block_rows(B: int, N: int, D: int, dtype: torch.dtype, schedule: str = "auto", packed: bool = False) -> int:
+    """Rows of the square blocks the affinity runs for this shape (with offsets: ``packed``)
+    and requested schedule on the current device: 64, 128 or 256."""
+    out = ctypes.c_int32()
+    _lib.check("mpm_affinity_block_rows",
+               _lib.load().mpm_affinity_block_rows(B, N, D, _DTYPES[dtype], _sched(schedule), int(packed),
+                                                   ctypes.byref(out)))
+    return out.value
+
+
 def local_block_rows(B: int, N: int, D: int, dtype: torch.dtype, grid_w: int, window: int,
                      block_rows: int = 0) -> int:
     """Rows of the square blocks merge_local's affinity runs for this shape, window and

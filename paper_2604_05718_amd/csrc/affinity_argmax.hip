@@ -25,10 +25,12 @@
 #include <hip/hip_ext.h>
 
 #include <algorithm>
+#include <cmath>
 #include <vector>
 
 #include "mpm_device.h"
 #include "mpm_launch.h"
+#include "mpm_work.h"
 
 namespace mpm {
 namespace {
@@ -148,13 +150,13 @@ __device__ __forceinline__ void exchange_half(float* v, int32_t* ix, int upper)
 // two LDS stages filled by direct global->LDS loads (global_load_lds_dwordx4), runs the
 // K loop on MFMA, then reduces its tile to one (score, index) partial per query.
 //
-// Scheduling for the 8 per-XCD L2 caches: workgroups are dealt round-robin to
-// the XCDs, so workgroup w serves XCD group w % xcds; a group owns the images
-// b = group + xcds * i and its `slots` workgroups take the group's items in
-// order (item k goes to slot k % slots). All items of an image therefore run at
-// the same time on one XCD, in lockstep over K, and each 256-row block is
-// fetched from HBM once and re-read from that XCD's L2 by the other items that
-// use it, instead of being refetched once per candidate tile.
+// Scheduling for the 8 per-XCD L2 caches: workgroups are dealt round-robin to the XCDs,
+// so workgroup w serves XCD group w % xcds, and each group takes a contiguous share of the
+// batch's items (mpm_work.h). The items of an image run at the same time on one XCD, in
+// lockstep over K, and each block of rows is fetched from HBM once and re-read from that
+// XCD's L2 by the other items that use it, instead of being refetched once per candidate
+// tile. Packed images are counted by their own lengths: the workgroup tabulates the block
+// counts of up to kMaxCountedImages images first (one wave, 64 offsets at a time).
 //
 // Pipeline. The chunks of all the workgroup's items form one stream. The barrier before
 // chunk c makes chunk c visible and retires chunk c-1's stage; chunk c's first fragments
@@ -200,19 +202,10 @@ __device__ __forceinline__ void exchange_half(float* v, int32_t* ix, int upper)
 // directly, so the partials are bit-identical to the full schedule's. Items are
 // taken image by image, the blocks of an image row by row, so all the items of
 // an image still run together on one XCD and share its L2.
-// Diagonal blocks taken out of a group's symmetric-schedule order (see HALVES below): with
-// `whole` items on `slots` workgroups the last round holds m = whole mod slots items; when
-// 0 < 2m <= slots and the group has at least m diagonal blocks, m of them are deferred.
-__host__ __device__ inline int deferred_diagonals(int nimg, int nb, int slots)
-{
-    const int whole = nimg * (nb * (nb + 1) / 2);
-    const int m = whole % slots;
-    return (m > 0 && 2 * m <= slots && m <= nimg * nb) ? m : 0;
-}
-
+//
 // HALVES: the second launch of a symmetric schedule on 256-row blocks. The first
-// launch (SYM) leaves out the last deferred_diagonals() diagonal blocks of its XCD group
-// (all of the last images', then the last ones of the image before), so that its slots
+// launch (SYM) leaves out the last diagonal blocks of its XCD group's share, as many as its
+// last round would hold on at most half of the slots (work_share()), so that its slots
 // take whole rounds; this launch runs each deferred block as two items of the block's
 // 256 candidates and one half of its queries (QT = CT/2). A diagonal block needs no
 // reverse direction, so the two halves write disjoint query partials, and each score
@@ -231,10 +224,11 @@ __host__ __device__ inline int deferred_diagonals(int nimg, int nb, int slots)
 // from the fragments in the K loop (vector ALU work in the K loop adds to its time about
 // one for one). Otherwise xinv is unused and every k-group's norm sums run without a
 // branch; each case is its own build.
-template <class S, int WC, int WQ, int MT, int NT, bool SYM, bool HALVES, bool LOCAL, bool GIVEN, bool TAIL>
+template <class S, int WC, int WQ, int MT, int NT, bool SYM, bool HALVES, bool LOCAL, bool GIVEN, bool TAIL,
+          bool COUNTED>
 __global__ __launch_bounds__(WC * WQ * kWave, 2) void affinity_partial_kernel(  // 2 waves per SIMD
-    const uint8_t* __restrict__ x, const int32_t* __restrict__ x_off, int B, int N, int D, int T, int xcds,
-    int slots, float* __restrict__ pv, int32_t* __restrict__ pi, const float* __restrict__ xinv, Window win)
+    const uint8_t* __restrict__ x, const int32_t* __restrict__ x_off, int B, int N, int D, int T, int log_xcds,
+    int slots, WorkShape shape, float* __restrict__ pv, int32_t* __restrict__ pi, const float* __restrict__ xinv, Window win)
 {
     constexpr int THREADS = WC * WQ * kWave;
     constexpr int WAVES = WC * WQ;
@@ -277,79 +271,60 @@ __global__ __launch_bounds__(WC * WQ * kWave, 2) void affinity_partial_kernel(  
     const int lrow = lane & 31;
     const int khalf = lane >> 5;
 
-    const int group = blockIdx.x % xcds;
-    const int slot = blockIdx.x / xcds;
-    const int nqb = (N + QT - 1) / QT;
-    const int nct = (N + CT - 1) / CT;  // candidate tiles per image (T, the slot stride, may be larger)
-    const int per_img = LOCAL ? nqb : (SYM ? nqb * (nqb + 1) / 2 : nqb * nct);
-    const int nimg = (B - group + xcds - 1) / xcds;
     static_assert(!HALVES || (!SYM && 2 * QT == CT), "half items: forward only, half a block of queries");
+    static_assert(HALVES || QT == CT, "square blocks");
     constexpr bool SPLIT = SYM && !LOCAL && CT == kSplitRows;  // the blocks the second launch exists for
-    const int ndef = (SPLIT || HALVES) ? deferred_diagonals(nimg, nct, slots) : 0;
-    const int dfull = ndef / nct, dpart = ndef % nct;
-    const int dimg = nimg - dfull - 1;                        // the image with dpart deferred
-    const int upto_dimg = (dimg + 1) * per_img - dpart;       // first-launch items of images 0..dimg
-    const int nitems = HALVES ? 2 * ndef : nimg * per_img - ndef;
+    constexpr WorkOrder ORDER = LOCAL ? kOrderBand : (SYM || HALVES) ? kOrderSymmetric : kOrderFull;
+    __shared__ int32_t items_tab[COUNTED ? kMaxCountedImages + 1 : 1], diags_tab[COUNTED ? kMaxCountedImages + 1 : 1];
+    const WorkCounts<COUNTED> counts{shape, items_tab, diags_tab};
+    if constexpr (COUNTED) {
+        if (wave == 0) {
+            int items = 0, diags = 0;  // of the images so far
+            for (int b0 = 0; b0 < B; b0 += kWave) {
+                const int b = b0 + lane;
+                const int im = work_place(b, shape.run);
+                const int nb = b < B ? (x_off[im + 1] - x_off[im] + CT - 1) / CT : 0;
+                int si = work_items(ORDER, nb), sd = nb;
+#pragma unroll
+                for (int o = 1; o < kWave; o <<= 1) {
+                    const int yi = __shfl_up(si, o), yd = __shfl_up(sd, o);
+                    si += lane >= o ? yi : 0;
+                    sd += lane >= o ? yd : 0;
+                }
+                if (b < B) {
+                    items_tab[b + 1] = items + si;
+                    diags_tab[b + 1] = diags + sd;
+                }
+                items += __shfl(si, kWave - 1);
+                diags += __shfl(sd, kWave - 1);
+            }
+            if (lane == 0) items_tab[0] = diags_tab[0] = 0;
+        }
+        __syncthreads();
+    }
+    const int group = blockIdx.x & ((1 << log_xcds) - 1);
+    const int slot = blockIdx.x >> log_xcds;
+    const WorkShare share = work_share(counts, B, group, log_xcds, slots, SPLIT || HALVES);
+    const int nitems = HALVES ? 2 * share.ndef : share.cnt - share.ndef;
+    if (slot >= nitems) return;  // uniform over the workgroup
     const long rowbytes = (long)D * S::kBytes;
     const int nchunks = (int)((rowbytes + CB - 1) / CB);
 
     // Item cursor; all fields are uniform over the workgroup.
     struct Item {
-        int k, b, qbase, cbase, n, row0;
+        int k, b, place, qbase, cbase, n, row0;
         int tlo, thi;  // LOCAL: the item's band of candidate tiles (cbase walks up to thi)
     };
-    auto find = [&](int k) {
+    auto find = [&](int k, int from) {
         Item it;
         for (; k < nitems; k += slots) {
-            int ib, qbase, t;
-            if (HALVES) {  // deferred diagonal e, query half k % 2
-                const int e = k >> 1;
-                int qb;
-                if (e < dpart) {
-                    ib = dimg;
-                    qb = nct - dpart + e;
-                } else {
-                    ib = dimg + 1 + (e - dpart) / nct;
-                    qb = (e - dpart) - (ib - dimg - 1) * nct;
-                }
-                t = qb;
-                qbase = qb * CT + (k & 1) * QT;
-            } else if (LOCAL) {  // query block qb of image ib; its band's first tile is found below
-                ib = k / nqb;
-                t = k - ib * nqb;
-                qbase = t * QT;
-            } else if (SYM) {  // blocks qb <= t of the upper triangle, row by row, minus deferred diagonals
-                int w;
-                if (k < upto_dimg) {
-                    ib = k / per_img;
-                    w = k - ib * per_img;
-                } else {
-                    const int rest = max(1, per_img - nqb);
-                    ib = dimg + 1 + (k - upto_dimg) / rest;
-                    w = (k - upto_dimg) - (ib - dimg - 1) * rest;
-                }
-                const int d = ib > dimg ? nqb : (ib == dimg ? dpart : 0);  // image ib's deferred diagonals
-                int qb = 0;
-                for (;;) {
-                    const int len = nqb - qb - (qb >= nqb - d ? 1 : 0);
-                    if (w < len) break;
-                    w -= len;
-                    ++qb;
-                }
-                t = qb + w + (qb >= nqb - d ? 1 : 0);
-                qbase = qb * QT;
-            } else {
-                ib = k / per_img;
-                const int w = k - ib * per_img;
-                const int qb = w / nct;
-                t = w - qb * nct;
-                qbase = qb * QT;
-            }
-            const int b = group + xcds * ib;
+            const WorkBlock w = HALVES ? work_deferred(counts, B, share, k >> 1) : work_block<ORDER, SPLIT>(counts, share, k, from);
+            const int b = work_place(w.b, shape.run), t = w.t;
+            const int qbase = HALVES ? w.q * CT + (k & 1) * QT : w.q * QT;  // half item: query half k % 2
             const int row0 = x_off ? x_off[b] : b * N;
             const int n = x_off ? x_off[b + 1] - row0 : N;
             if (qbase < n && t * CT < n) {
-                it.k = k; it.b = b; it.qbase = qbase; it.cbase = t * CT; it.n = n; it.row0 = row0;
+                it.k = k; it.b = b; it.place = w.b; it.qbase = qbase; it.cbase = t * CT; it.n = n; it.row0 = row0;
                 it.tlo = t;
                 it.thi = t;
                 if constexpr (LOCAL) {
@@ -368,7 +343,7 @@ __global__ __launch_bounds__(WC * WQ * kWave, 2) void affinity_partial_kernel(  
                 return it;
             }
         }
-        it.k = nitems; it.b = 0; it.qbase = 0; it.cbase = 0; it.n = 1; it.row0 = 0; it.tlo = 0; it.thi = 0;
+        it.k = nitems; it.b = 0; it.place = 0; it.qbase = 0; it.cbase = 0; it.n = 1; it.row0 = 0; it.tlo = 0; it.thi = 0;
         return it;
     };
     // The work after `it`: its next band tile (LOCAL), else the slot's next item.
@@ -380,7 +355,7 @@ __global__ __launch_bounds__(WC * WQ * kWave, 2) void affinity_partial_kernel(  
                 return nx;
             }
         }
-        return find(it.k + slots);
+        return find(it.k + slots, it.place);
     };
 
     // Swizzle of the 16-byte column slot for a row (see the layout note above).
@@ -411,7 +386,8 @@ __global__ __launch_bounds__(WC * WQ * kWave, 2) void affinity_partial_kernel(  
         return o;
     };
 
-    Item ii = find(slot);  // issue cursor
+    Item ii = find(slot, work_image(counts, B, share.lo));  // issue cursor
+    Item inext = ii;  // the item of the chunk issued last
     if (ii.k >= nitems) return;  // no work for this slot (uniform over the workgroup)
     Offsets ioff = offsets_of(ii);
     int ichunk = 0;
@@ -441,13 +417,17 @@ __global__ __launch_bounds__(WC * WQ * kWave, 2) void affinity_partial_kernel(  
         asm volatile("global_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(ibase), "{m0}"(m0) : "memory");
     };
     auto issue_end = [&]() {
+        inext = ii;
         if (!iact) return;
         ++issued;
-        if (++ichunk == nchunks) {
-            ichunk = 0;
-            ii = next_of(ii);
-            if (ii.k < nitems) ioff = offsets_of(ii);
-        }
+        ++ichunk;
+    };
+    // The issue cursor's next item, once its chunks are all requested.
+    auto advance = [&]() {
+        if (ichunk < nchunks) return;
+        ichunk = 0;
+        ii = next_of(ii);
+        if (ii.k < nitems) ioff = offsets_of(ii);
     };
     auto issue_next = [&]() {
         issue_begin();
@@ -539,9 +519,8 @@ __global__ __launch_bounds__(WC * WQ * kWave, 2) void affinity_partial_kernel(  
             }
         }
     };
+    Item ci = ii;  // compute cursor
     issue_next();  // prologue: the first chunk
-
-    Item ci = find(slot);  // compute cursor
     // With given norms, thread t fetches the inverse norm of candidate row t (t < CT) or
     // query row t - CT (symmetric schedule) of the compute cursor's item when the cursor
     // reaches it; the value is written to LDS at the item's end. Rows past the image are
@@ -591,6 +570,7 @@ __global__ __launch_bounds__(WC * WQ * kWave, 2) void affinity_partial_kernel(  
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
         read_frags(fa0, fq0, consumed, 0);
+        advance();
         issue_begin();
 #pragma unroll
         for (int g = 0; g < KG; ++g) {
@@ -936,7 +916,7 @@ __global__ __launch_bounds__(WC * WQ * kWave, 2) void affinity_partial_kernel(  
             }
         }
         cchunk = 0;
-        ci = next_of(ci);
+        ci = inext;  // loads run one chunk ahead: the chunk issued last is the next item's first
         fetch_inv(ci);
         fetch_pos(ci);
         if constexpr (HALVES) lq_off = (ci.qbase - ci.cbase + wq * NT * 32 + lrow) * CB;
@@ -952,11 +932,10 @@ constexpr int kPWC = 2, kPWQ = 4, kPMT = 4, kPNT = 2, kPWGS = 1;
 constexpr int kSWC = 4, kSWQ = 2, kSMT = 2, kSNT = 4;
 constexpr int kPCT = kPWC * kPMT * 32;
 static_assert(kPCT == kSplitRows, "the half-block launch splits the large blocks");
-// Small batches (few 256 x 256 blocks for the device's CUs) use 64 x 64 blocks on 4 waves
-// of one 32 x 32 tile each, so a single image of 1024 tokens still spreads over 256 CUs.
-constexpr int kTWC = 2, kTWQ = 2, kTMT = 1, kTNT = 1;
+// Small batches use 64 x 64 blocks on 4 waves of one 32 x 32 tile each, up to four
+// workgroups per CU, so a single image of 1024 tokens still spreads over 256 CUs.
+constexpr int kTWC = 2, kTWQ = 2, kTMT = 1, kTNT = 1, kTWGS = 4;
 constexpr int kTCT = kTWC * kTMT * 32;
-constexpr long kSmallItems = 32;  // batches with at most this many 256 x 256 blocks take them
 static_assert(kTWQ * kTNT * 32 == kTCT && kPCT % kTCT == 0, "square small blocks that nest in the large ones");
 static_assert(kSWC * kSMT * 32 == kPCT && kSWQ * kSNT * 32 == kPCT && kPWQ * kPNT * 32 == kPCT,
               "both schedules use 256 x 256 tiles, so their partials share one layout");
@@ -979,76 +958,94 @@ int device_cus()
     return cus;
 }
 
-// Whether a symmetric launch on the two-stage ring defers diagonal blocks in any XCD group.
-bool defers_diagonals(int B, int N, int xcds, int slots)
+// Whether a symmetric launch may defer diagonal blocks in any XCD group (images whose
+// lengths only the device knows: any may).
+bool defers_diagonals(bool counted, int B, int N, int log_xcds, int slots)
 {
+    if (counted) return true;
     const int nb = (N + kPCT - 1) / kPCT;
-    for (int g = 0; g < xcds; ++g)
-        if (deferred_diagonals((B - g + xcds - 1) / xcds, nb, slots) > 0) return true;
+    const WorkShape shape(kOrderSymmetric, B, nb);
+    const WorkCounts<false> counts{shape, nullptr, nullptr};
+    for (int g = 0; g < 1 << log_xcds; ++g)
+        if (work_share(counts, B, g, log_xcds, slots, true).ndef > 0) return true;
     return false;
 }
 
-template <class S, int WC, int WQ, int MT, int NT, bool SYM, bool LOCAL, bool GIVEN, bool TAIL>
-void launch_persistent_as(const void* x, const int32_t* x_off, const float* xinv, int B, int N, int D, int T, int xcds,
-                          int groups, float* pv, int32_t* pi, hipStream_t stream, hipEvent_t start, hipEvent_t stop,
-                          Window win)
+struct AffinityArgs {
+    const void* x;
+    const int32_t* x_off;
+    const float* xinv;
+    int B, N, D, T, xcds;
+    float* pv;
+    int32_t* pi;
+    hipStream_t stream;
+    hipEvent_t start, stop;
+    Window win;
+};
+
+template <class S, int WC, int WQ, int MT, int NT, bool SYM, bool LOCAL, bool GIVEN, bool TAIL, bool COUNTED>
+void launch_counted(const AffinityArgs& a, int slots, const WorkShape& shape)
 {
-    const uint8_t* xb = static_cast<const uint8_t*>(x);
+    const uint8_t* xb = static_cast<const uint8_t*>(a.x);
+    const int log_xcds = a.xcds == 1 ? 0 : 3;
+    static_assert(kXcds == 8, "the groups of mpm_work.h");
+    const dim3 grid(slots * a.xcds), block(WC * WQ * kWave);
     // The symmetric schedule's deferred diagonal blocks, as half blocks, in a second launch
     // (one item per slot); the timing events then span both.
     constexpr bool SPLIT = SYM && !LOCAL && WC * MT * 32 == kSplitRows;
-    const bool halves = SPLIT && defers_diagonals(B, N, xcds, groups / xcds);
-    hipExtLaunchKernelGGL((affinity_partial_kernel<S, WC, WQ, MT, NT, SYM, false, LOCAL, GIVEN, TAIL>), dim3(groups),
-                          dim3(WC * WQ * kWave), 0, stream, start, halves ? nullptr : stop, 0, xb, x_off, B, N, D, T,
-                          xcds, groups / xcds, pv, pi, xinv, win);
+    const bool halves = SPLIT && defers_diagonals(COUNTED, a.B, a.N, log_xcds, slots);
+    hipExtLaunchKernelGGL((affinity_partial_kernel<S, WC, WQ, MT, NT, SYM, false, LOCAL, GIVEN, TAIL, COUNTED>), grid,
+                          block, 0, a.stream, a.start, halves ? nullptr : a.stop, 0, xb, a.x_off, a.B, a.N, a.D, a.T,
+                          log_xcds, slots, shape, a.pv, a.pi, a.xinv, a.win);
     if constexpr (SPLIT) {
         if (halves)
-            hipExtLaunchKernelGGL((affinity_partial_kernel<S, WC, WQ, MT, NT / 2, false, true, false, GIVEN, TAIL>),
-                                  dim3(groups), dim3(WC * WQ * kWave), 0, stream, nullptr, stop, 0, xb, x_off, B, N, D,
-                                  T, xcds, groups / xcds, pv, pi, xinv, win);
+            hipExtLaunchKernelGGL((affinity_partial_kernel<S, WC, WQ, MT, NT / 2, false, true, false, GIVEN, TAIL, COUNTED>),
+                                  grid, block, 0, a.stream, nullptr, a.stop, 0, xb, a.x_off, a.B, a.N, a.D, a.T,
+                                  log_xcds, slots, shape, a.pv, a.pi, a.xinv, a.win);
     }
+}
+
+template <class S, int WC, int WQ, int MT, int NT, bool SYM, bool LOCAL, bool GIVEN, bool TAIL>
+void launch_persistent_as(const AffinityArgs& a, int groups)
+{
+    // No more slots than a group can have items (images of N tokens), and no count of the
+    // images' own blocks when every item has its slot (the count costs each workgroup 0.8 us).
+    constexpr int CT = WC * MT * 32;
+    constexpr WorkOrder ORDER = LOCAL ? kOrderBand : SYM ? kOrderSymmetric : kOrderFull;
+    const int nb = (a.N + CT - 1) / CT;
+    const long total = (long)a.B * work_items(ORDER, nb);
+    const int most = groups / a.xcds;
+    const int slots = (int)std::min<long>(most, (total + a.xcds - 1) / a.xcds);
+    const WorkShape shape(ORDER, a.B, nb);
+    if (a.x_off != nullptr && a.B <= kMaxCountedImages && total > (long)most * a.xcds)
+        launch_counted<S, WC, WQ, MT, NT, SYM, LOCAL, GIVEN, TAIL, true>(a, slots, shape);
+    else
+        launch_counted<S, WC, WQ, MT, NT, SYM, LOCAL, GIVEN, TAIL, false>(a, slots, shape);
 }
 
 // Given norms (bfloat16 only) and norms summed in the K loop are separate builds: with one
 // build and a run-time flag, the flag's branch per k-group cost the summing launches 2-4%,
 // and two builds alternating between insertions showed no instruction-cache penalty.
-template <class S, int WC, int WQ, int MT, int NT, bool SYM, bool LOCAL = false>
-void launch_blocks(const void* x, const int32_t* x_off, const float* xinv, int B, int N, int D, int T, int xcds,
-                   int groups, float* pv, int32_t* pi, hipStream_t stream, hipEvent_t start, hipEvent_t stop,
-                   Window win = Window{nullptr, 1, 0})
+template <class S, int WC, int WQ, int MT, int NT, bool SYM, bool LOCAL>
+void launch_blocks(const AffinityArgs& a, int groups)
 {
-    const bool tail = ((long)D * S::kBytes) % kChunkBytes != 0;
+    const bool tail = ((long)a.D * S::kBytes) % kChunkBytes != 0;
     if constexpr (S::kBytes == 2) {
-        if (xinv != nullptr) {
-            if (tail)
-                launch_persistent_as<S, WC, WQ, MT, NT, SYM, LOCAL, true, true>(x, x_off, xinv, B, N, D, T, xcds, groups,
-                                                                                pv, pi, stream, start, stop, win);
-            else
-                launch_persistent_as<S, WC, WQ, MT, NT, SYM, LOCAL, true, false>(x, x_off, xinv, B, N, D, T, xcds,
-                                                                                 groups, pv, pi, stream, start, stop,
-                                                                                 win);
+        if (a.xinv != nullptr) {
+            if (tail) launch_persistent_as<S, WC, WQ, MT, NT, SYM, LOCAL, true, true>(a, groups);
+            else launch_persistent_as<S, WC, WQ, MT, NT, SYM, LOCAL, true, false>(a, groups);
             return;
         }
     }
-    if (tail)
-        launch_persistent_as<S, WC, WQ, MT, NT, SYM, LOCAL, false, true>(x, x_off, nullptr, B, N, D, T, xcds, groups, pv,
-                                                                         pi, stream, start, stop, win);
-    else
-        launch_persistent_as<S, WC, WQ, MT, NT, SYM, LOCAL, false, false>(x, x_off, nullptr, B, N, D, T, xcds, groups,
-                                                                          pv, pi, stream, start, stop, win);
+    if (tail) launch_persistent_as<S, WC, WQ, MT, NT, SYM, LOCAL, false, true>(a, groups);
+    else launch_persistent_as<S, WC, WQ, MT, NT, SYM, LOCAL, false, false>(a, groups);
 }
 
 template <int WC, int WQ, int MT, int NT, bool SYM, bool LOCAL = false>
-void launch_persistent(int dt, const void* x, const int32_t* x_off, const float* xinv, int B, int N, int D, int T,
-                       int xcds, int groups, float* pv, int32_t* pi, hipStream_t stream, hipEvent_t start,
-                       hipEvent_t stop, Window win = Window{nullptr, 1, 0})
+void launch_persistent(int dt, const AffinityArgs& a, int groups)
 {
-    if (dt == kBf16)
-        launch_blocks<Bf16, WC, WQ, MT, NT, SYM, LOCAL>(x, x_off, xinv, B, N, D, T, xcds, groups, pv, pi, stream, start,
-                                                        stop, win);
-    else
-        launch_blocks<F32, WC, WQ, MT, NT, SYM, LOCAL>(x, x_off, nullptr, B, N, D, T, xcds, groups, pv, pi, stream,
-                                                       start, stop, win);
+    if (dt == kBf16) launch_blocks<Bf16, WC, WQ, MT, NT, SYM, LOCAL>(a, groups);
+    else launch_blocks<F32, WC, WQ, MT, NT, SYM, LOCAL>(a, groups);
 }
 
 }  // namespace
@@ -1063,28 +1060,6 @@ bool valid_schedule(int schedule)
 }
 
 namespace {
-
-// Whether a persistent launch of this shape and requested schedule uses the 64 x 64
-// blocks (no device query).
-bool small_blocks(int B, int N, int schedule)
-{
-    if (schedule != kScheduleAuto) return schedule == kScheduleFull64;
-    const long nqb = (N + kPCT - 1) / kPCT;
-    return (long)B * nqb * nqb <= kSmallItems;
-}
-
-bool symmetric_schedule(int B, int N, int xcds, int slots, int schedule)
-{
-    if (schedule != kScheduleAuto) return schedule == kScheduleSymmetric;
-    // Rounds of work items per workgroup slot under either schedule. An off-diagonal
-    // item of the symmetric one costs about a fifth more (its reverse direction), so
-    // it pays only when it saves more than that in rounds.
-    const long nqb = (N + kPCT - 1) / kPCT;
-    const long nimg = (B + xcds - 1) / xcds;
-    const long full = (nimg * nqb * nqb + slots - 1) / slots;
-    const long sym = (nimg * nqb * (nqb + 1) / 2 + slots - 1) / slots;
-    return 5 * sym < 4 * full;
-}
 
 // The locality-constrained schedule's two block sizes: 256 x 256 blocks on 8 waves, one
 // workgroup per CU (the dense symmetric shape), or 128 x 128 blocks on 4 waves of 64 x 64,
@@ -1112,9 +1087,8 @@ double local_cost(int B, int N, int grid_w, int radius, int ts, int xcds, int sl
         tiles[t] = (int)(thi - t + 1);
         total += tiles[t];
     }
-    const long imgs = (B + xcds - 1) / xcds;  // images of the largest group
-    const long items = imgs * nblk;
-    if (items > 64L * slots) return (double)imgs * total / slots * wgs_per_cu * block_cost;  // many rounds: balanced
+    const long items = ((long)B * nblk + xcds - 1) / xcds;  // of the largest group
+    if (items > 64L * slots) return (double)items * total / nblk / slots * wgs_per_cu * block_cost;  // many rounds: balanced
     std::vector<long> load(slots, 0);
     for (long k = 0; k < items; ++k) load[k % slots] += tiles[k % nblk];
     std::sort(load.begin(), load.end());
@@ -1136,7 +1110,7 @@ int local_rows(int B, int N, int D, int dt, int grid_w, int radius, int requeste
     if (requested != 0 && whole_64(D, dt)) return requested;
     const int cus = device_cus();
     if (cus <= 0) return kPCT;
-    const int xcds = (cus % kXcds == 0 && B >= kXcds) ? kXcds : 1;
+    const int xcds = cus % kXcds == 0 ? kXcds : 1;
     const double large = local_cost(B, N, grid_w, radius, kPCT, xcds, cus * kPWGS / xcds, kPWGS, 1.0);
     const double small = local_cost(B, N, grid_w, radius, kLCT, xcds, cus * kLWGS / xcds, kLWGS, kLSmallBlockCost);
     return small < large ? kLCT : kPCT;
@@ -1157,28 +1131,101 @@ int local_tile_width(int B, int N, int D, int dt, int grid_w, int radius, int re
 
 namespace {
 
-enum Blocks : int { kBlocks64, kBlocks256, kBlocksSym256 };
+// Block shape and schedule of a launch: 64 x 64 full, 128 x 128 symmetric (the shape of the
+// small window blocks: 4 waves, two workgroups per CU), 256 x 256 full and symmetric.
+enum Blocks : int { kBlocks64, kBlocks128, kBlocks256, kBlocksSym256 };
 
-// The block size and schedule of a launch: the requested one where the argument applies,
-// else (and for MPM_SCHEDULE_AUTO) small blocks for small batches, then the symmetric
-// schedule where it needs fewer rounds.
-Blocks pick_blocks(int B, int N, int D, int dt, int schedule)
+// Estimated duration (us) of a dense launch's items on c 128-byte chunks of K: a fixed part,
+// and a round of the workgroup slots. Fitted to launches of 1 to 64 images of 100 to 4096
+// bfloat16 rows of 128 to 2048 bytes (495 shapes, replayed from a graph): the pick it gives is
+// 0.2% slower than the fastest of the four shapes over the dense ones, 0.5% over packed
+// batches, and 15% (dense) and 19% (packed) faster than 64 x 64 blocks for at most 32 large
+// blocks and 256 x 256 ones elsewhere. Examples, 64 / 128 / 256 full / 256 symmetric, dense rows
+// of 1536 bytes: 8 images of 400 rows 10.0 / 13.5 / 21.2 / 24.2 us; 12 of 1024 rows 35.8 /
+// 18.0 / 22.6 / 24.7; 24 of 1024 rows 67.7 / 32.3 / 41.9 / 27.1; 16 of 1024 rows of 384 bytes
+// - / 15.7 / 11.3 / 14.6.
+double round_us(double fixed, double round, double rounds) { return fixed + round * rounds; }
+
+double estimate_us(Blocks k, double blocks64, double blocks128, double full256, double sym256, double c, double cus,
+                   bool counted)
 {
-    const int sched = whole_64(D, dt) ? schedule : (int)kScheduleAuto;
-    if (small_blocks(B, N, sched)) return kBlocks64;
-    const int cus = device_cus();
-    const int xcds = (cus % kXcds == 0 && B >= kXcds) ? kXcds : 1;
-    return symmetric_schedule(B, N, xcds, max(1, cus * kPWGS / xcds), sched) ? kBlocksSym256 : kBlocks256;
+    // Rounds of whole slots; a packed batch's lengths are only guessed, so a part of a round is
+    // taken to cost its mean there.
+    switch (k) {
+    case kBlocks64: {
+        const double per_cu = blocks64 / cus;  // up to four workgroups share a CU
+        return 3.5 + 0.29 * c + std::max(0.0, per_cu - 1.0) * (0.68 + 0.20 * c);
+    }
+    case kBlocks128: {
+        const double round = 5.3 + 0.79 * c, r = blocks128 / (2 * cus);
+        // The last round's workgroups run alone on their CU up to half of the slots.
+        auto part = [](double f) { return f <= 0 ? 0.0 : f <= 0.5 ? 0.6 : 0.6 + 0.4 * (2 * f - 1); };
+        if (counted) return round_us(4.4, round, 1.1 * r <= 1 ? part(1.1 * r) : r + 0.31);
+        return round_us(4.4, round, std::floor(r) + part(r - std::floor(r)));
+    }
+    case kBlocks256: return round_us(2.5, 4.3 + 1.43 * c, std::ceil(full256 / cus));
+    default: {
+        const double round = 9.0 + 1.31 * c, r = sym256 / cus;
+        if (counted) return round_us(2.0, round, 1.1 * r <= 1 ? 1 : r + 0.62) + (1.1 * r <= 1 ? 0 : 3.0);
+        const double f = r - std::floor(r);  // a short last round runs as half blocks
+        return round_us(2.0, round, std::floor(r) + (f <= 0 ? 0 : r > 1 && f <= 0.5 ? 0.82 : 1.0));
+    }
+    }
 }
+
+Blocks pick_blocks(int B, int N, int D, int dt, int schedule, bool packed)
+{
+    if (whole_64(D, dt)) {
+        if (schedule == kScheduleFull) return kBlocks256;
+        if (schedule == kScheduleSymmetric) return kBlocksSym256;
+        if (schedule == kScheduleFull64) return kBlocks64;
+    }
+    const int cus = std::max(1, device_cus());
+    auto blocks = [&](int w, WorkOrder order, int percent) {
+        return (double)B * work_items(order, (int)(((long)N * percent / 100 + w - 1) / w));
+    };
+    const double capacity64 = blocks(kTCT, kOrderFull, 100);
+    const double full256 = blocks(kPCT, kOrderFull, 100);
+    if (dt != kBf16) {
+        // float32: a block's matrix work outweighs the rest of it, so only the rounds count (an
+        // off-diagonal symmetric item costs a fifth more for its reverse direction).
+        const double nqb = std::sqrt(full256 / B), xcds = cus % kXcds == 0 ? kXcds : 1;
+        if (full256 <= 32) return kBlocks64;
+        const double nimg = std::ceil(B / xcds), slots = cus / xcds;
+        return 5 * std::ceil(nimg * nqb * (nqb + 1) / 2 / slots) < 4 * std::ceil(nimg * nqb * nqb / slots) ? kBlocksSym256
+                                                                                                            : kBlocks256;
+    }
+    const double c = std::ceil(2.0 * D / kChunkBytes);
+    double b64 = capacity64, b128 = blocks(kLCT, kOrderSymmetric, 100), s256 = blocks(kPCT, kOrderSymmetric, 100);
+    if (packed) {  // images as an earlier insertion leaves them: 80 to 90% of N tokens
+        b64 = b128 = s256 = 0;
+        for (int percent : {80, 85, 90}) {
+            b64 += blocks(kTCT, kOrderFull, percent) / 3;
+            b128 += blocks(kLCT, kOrderSymmetric, percent) / 3;
+            s256 += blocks(kPCT, kOrderSymmetric, percent) / 3;
+        }
+    }
+    Blocks best = kBlocks128;
+    double us = estimate_us(kBlocks128, b64, b128, full256, s256, c, cus, packed);
+    for (Blocks k : {kBlocks64, kBlocks256, kBlocksSym256}) {
+        if (k == kBlocks64 && capacity64 > 2.5 * cus) continue;  // beyond, 128 x 128 blocks are as fast
+        if (k == kBlocks256 && packed && full256 > cus) continue;  // a round of whole images or the symmetric blocks
+        const double e = estimate_us(k, b64, b128, full256, s256, c, cus, packed);
+        if (e < us) {
+            us = e;
+            best = k;
+        }
+    }
+    return best;
+}
+
+int block_rows(Blocks k) { return k == kBlocks64 ? kTCT : k == kBlocks128 ? kLCT : kPCT; }
 
 }  // namespace
 
-int partial_tile_width(int B, int D, int dt, int N, int schedule)
+int partial_tile_width(int B, int D, int dt, int N, int schedule, bool packed)
 {
-    switch (pick_blocks(B, N, D, dt, schedule)) {
-    case kBlocks64: return kTCT;
-    default: return kPCT;
-    }
+    return block_rows(pick_blocks(B, N, D, dt, schedule, packed));
 }
 
 hipError_t affinity_schedule(int B, int N, int D, int dt, int schedule, int* used)
@@ -1186,7 +1233,7 @@ hipError_t affinity_schedule(int B, int N, int D, int dt, int schedule, int* use
     *used = kScheduleFull;
     if (!whole_64(D, dt)) return hipSuccess;  // no choice of schedule
     if (device_cus() <= 0) return hipErrorInvalidDevice;
-    switch (pick_blocks(B, N, D, dt, schedule)) {
+    switch (pick_blocks(B, N, D, dt, schedule, false)) {
     case kBlocks64: *used = kScheduleFull64; break;
     case kBlocks256: *used = kScheduleFull; break;
     default: *used = kScheduleSymmetric; break;
@@ -1201,21 +1248,14 @@ hipError_t launch_affinity(const void* x, const int32_t* x_off, int B, int N, in
     if (xinv && !affinity_takes_norms(D, dt)) return hipErrorInvalidValue;  // those kernels sum their own norms
     const int cus = device_cus();
     if (cus <= 0) return hipErrorInvalidDevice;
-    // With a batch of at least 8 images, group the workgroups by XCD.
-    const int xcds = (cus % kXcds == 0 && B >= kXcds) ? kXcds : 1;
-    switch (pick_blocks(B, N, D, dt, schedule)) {
-    case kBlocks64:
-        launch_persistent<kTWC, kTWQ, kTMT, kTNT, false>(dt, x, x_off, xinv, B, N, D, T, xcds, cus * kPWGS, pv, pi,
-                                                         stream, start, stop);
-        break;
-    case kBlocksSym256:
-        launch_persistent<kSWC, kSWQ, kSMT, kSNT, true>(dt, x, x_off, xinv, B, N, D, T, xcds, cus * kPWGS, pv, pi,
-                                                        stream, start, stop);
-        break;
-    default:
-        launch_persistent<kPWC, kPWQ, kPMT, kPNT, false>(dt, x, x_off, xinv, B, N, D, T, xcds, cus * kPWGS, pv, pi,
-                                                         stream, start, stop);
-        break;
+    const int xcds = cus % kXcds == 0 ? kXcds : 1;
+    const AffinityArgs a{x, x_off, dt == kBf16 ? xinv : nullptr, B, N, D, T, xcds, pv, pi, stream, start, stop,
+                         Window{nullptr, 1, 0}};
+    switch (pick_blocks(B, N, D, dt, schedule, x_off != nullptr)) {
+    case kBlocks64: launch_persistent<kTWC, kTWQ, kTMT, kTNT, false>(dt, a, cus * kTWGS); break;
+    case kBlocks128: launch_persistent<kLWC, kLWQ, kLMT, kLNT, true>(dt, a, cus * kLWGS); break;
+    case kBlocksSym256: launch_persistent<kSWC, kSWQ, kSMT, kSNT, true>(dt, a, cus * kPWGS); break;
+    default: launch_persistent<kPWC, kPWQ, kPMT, kPNT, false>(dt, a, cus * kPWGS); break;
     }
     return hipGetLastError();
 }
@@ -1228,16 +1268,13 @@ hipError_t launch_affinity_local(const void* x, const int32_t* x_off, const floa
     // The persistent kernel on the symmetric schedule, one item per query block and the
     // tiles of its band from its own on (given norms: bf16 only), with blocks of block_rows.
     const int T = partial_tiles(N);
-    const Window win{pos, grid_w, radius};
     const int cus = device_cus();
     if (cus <= 0) return hipErrorInvalidDevice;
-    const int xcds = (cus % kXcds == 0 && B >= kXcds) ? kXcds : 1;
-    if (block_rows == kLCT)
-        launch_persistent<kLWC, kLWQ, kLMT, kLNT, true, true>(dt, x, x_off, xinv, B, N, D, T, xcds, cus * kLWGS, pv, pi,
-                                                              stream, start, stop, win);
-    else
-        launch_persistent<kSWC, kSWQ, kSMT, kSNT, true, true>(dt, x, x_off, xinv, B, N, D, T, xcds, cus * kPWGS, pv, pi,
-                                                              stream, start, stop, win);
+    const int xcds = cus % kXcds == 0 ? kXcds : 1;
+    const AffinityArgs a{x, x_off, dt == kBf16 ? xinv : nullptr, B, N, D, T, xcds, pv, pi, stream, start, stop,
+                         Window{pos, grid_w, radius}};
+    if (block_rows == kLCT) launch_persistent<kLWC, kLWQ, kLMT, kLNT, true, true>(dt, a, cus * kLWGS);
+    else launch_persistent<kSWC, kSWQ, kSMT, kSNT, true, true>(dt, a, cus * kPWGS);
     return hipGetLastError();
 }
 

@@ -248,24 +248,22 @@ int check_affinity(const void* x, const int32_t* x_off, const float* x_inv, int3
     return MPM_OK;
 }
 
-// nb from the affinity partials, then mutual pairs, compact ids and offsets. With few
-// candidate tiles the compaction kernel (one workgroup per image) reduces the
-// partials itself; with more, that serial reduction dominates, so a fully
-// parallel reduction writes nb first and the compaction reads it. A batch of a
-// few images (as small as the 64 x 64 block schedule is for) leaves most of
-// the device idle either way, and one launch fewer wins up to 16 tiles.
-constexpr int kFusedReduceMaxTiles = 4;
-constexpr int kFusedReduceMaxTilesFewImages = 16;
-constexpr int kFewImages = 8;
+// nb from the affinity partials, then mutual pairs, compact ids and offsets. The
+// compaction kernel (one workgroup of 1024 threads per image) reduces the partials itself
+// while each thread has few to wait for: a thread takes ceil(N / 1024) tokens and loads 8
+// tiles of one at a time, and up to 4 such batches in a row cost no more than a parallel
+// reduction's own launch. 32 images, reduced first / in the compaction: 400 tokens of 4 tiles
+// 7.5 / 5.7 us, 1024 of 8 tiles 8.1 / 6.7, 1521 of 12 tiles 9.3 / 9.2, 2304 of 18 tiles
+// 9.3 / 13.1.
+constexpr int kFusedReduceBatches = 4;
 
-// Compaction from partials of ct candidate rows each (reduced first by their own launch
-// when an image has more tiles than the compaction reduces well itself).
+// Compaction from partials of ct candidate rows each.
 hipError_t compact_partials_ct(const Workspace& w, const int32_t* x_off, int32_t B, int32_t N, int32_t D, int32_t dt,
                                int ct, int32_t* map, int32_t* y_off, hipStream_t st)
 {
     const int T = mpm::partial_tiles(N);
-    const int fused_max = B <= kFewImages ? kFusedReduceMaxTilesFewImages : kFusedReduceMaxTiles;
-    if ((N + ct - 1) / ct <= fused_max)
+    const int tiles = (N + ct - 1) / ct;
+    if ((N + 1023) / 1024 * ((tiles + 7) / 8) <= kFusedReduceBatches)
         return mpm::launch_pair_compact_partials(w.pv, w.pi, T, ct, w.nb, x_off, B, N, map, w.src, y_off, w.sync, st);
     hipError_t e = mpm::launch_reduce_partials(w.pv, w.pi, ct, nullptr, x_off, B, N, D, dt, w.nb, nullptr, st);
     if (e == hipSuccess) e = mpm::launch_pair_compact(w.nb, x_off, B, N, map, w.src, y_off, w.sync, st);
@@ -275,7 +273,8 @@ hipError_t compact_partials_ct(const Workspace& w, const int32_t* x_off, int32_t
 hipError_t compact_from_partials(const Workspace& w, const int32_t* x_off, int32_t B, int32_t N, int32_t D,
                                  int32_t dt, int32_t schedule, int32_t* map, int32_t* y_off, hipStream_t st)
 {
-    return compact_partials_ct(w, x_off, B, N, D, dt, mpm::partial_tile_width(B, D, dt, N, schedule), map, y_off, st);
+    return compact_partials_ct(w, x_off, B, N, D, dt, mpm::partial_tile_width(B, D, dt, N, schedule, x_off != nullptr), map,
+                               y_off, st);
 }
 
 // One insertion's affinity (events bound to its launches) and compaction into the carved workspace.
@@ -414,6 +413,18 @@ int mpm_affinity_schedule_used(int32_t B, int32_t N, int32_t D, int32_t dt, int3
     return st;
 }
 
+int mpm_affinity_block_rows(int32_t B, int32_t N, int32_t D, int32_t dt, int32_t schedule, int32_t packed,
+                            int32_t* rows)
+{
+    const int s = check_rows(B, N, D, dt);
+    if (s != MPM_OK) return s;
+    if (!rows || !mpm::valid_schedule(schedule)) return MPM_ERR_INVALID_ARG;
+    int dev = 0;
+    const int st = hip_status(hipGetDevice(&dev));
+    if (st == MPM_OK) *rows = mpm::partial_tile_width(B, D, dt, N, schedule, packed != 0);
+    return st;
+}
+
 int mpm_local_block_rows(int32_t B, int32_t N, int32_t D, int32_t dt, int32_t grid_w, int32_t window,
                          int32_t block_rows, int32_t* rows)
 {
@@ -440,8 +451,9 @@ int mpm_argmax(const void* x, const int32_t* x_off, int32_t B, int32_t N, int32_
     const hipStream_t st = as_stream(stream);
     hipError_t e = mpm::launch_affinity(x, x_off, B, N, D, dt, schedule, w.pv, w.pi, st, nullptr, nullptr, nullptr);
     if (e == hipSuccess)
-        e = mpm::launch_reduce_partials(w.pv, w.pi, mpm::partial_tile_width(B, D, dt, N, schedule), x, x_off, B, N, D,
-                                        dt, nb, best, st);
+        e = mpm::launch_reduce_partials(w.pv, w.pi,
+                                        mpm::partial_tile_width(B, D, dt, N, schedule, x_off != nullptr), x, x_off, B,
+                                        N, D, dt, nb, best, st);
     return hip_status(e);
 }
 

@@ -25,8 +25,9 @@ hipError_t launch_affinity(const void* x, const int32_t* x_off, int B, int N, in
 bool affinity_takes_norms(int D, int dt);
 // Partial slots per token in the workspace (the tile stride of pv/pi): ceil(N / 64).
 int partial_tiles(int N);
-// Candidate rows covered by one partial of the kernel launch_affinity picks for this call.
-int partial_tile_width(int B, int D, int dt, int N, int schedule);
+// Candidate rows covered by one partial of the blocks launch_affinity picks for this call
+// (packed: with offsets).
+int partial_tile_width(int B, int D, int dt, int N, int schedule, bool packed);
 // ... and of launch_affinity_local's kernel: the rows of its square blocks on the
 // persistent kernel's symmetric schedule (`requested`, 128 or 256; 0: whichever an
 // estimate of the launch on a full raster grid of grid_w columns finds faster on the

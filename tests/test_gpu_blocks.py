@@ -58,3 +58,54 @@ def test_rows_of_any_width(dtype, D):
     m = mpm.merge(x, off, N=N)
     torch.cuda.synchronize()
     check_merge(imgs, dtype, m)
+
+
+# Batches whose automatic pick is each block shape, with images that end at, before and
+# past a block, several images per XCD share or several shares per image, empty images.
+WORK_CASES = {
+    "one_image_128": (64, [1500]),
+    "three_images_128": (64, [1024, 129, 897]),
+    "uneven_shares": (64, [300, 0, 513, 256, 1, 128, 640, 257, 384, 0, 511, 127]),
+    "many_small": (64, [65, 64, 1, 0, 63, 2] * 20),
+    "counted_limit": (32, [130, 1] * 256),          # 512 images, the most counted one by one
+    "past_counted_limit": (32, [130, 1] * 256 + [40]),
+    "long_and_short": (64, [2300] + [30] * 9 + [1700]),
+}
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("name", list(WORK_CASES))
+def test_work_distribution(dtype, name):
+    """Ragged packed batches on the automatic pick, dense or packed, equal those on the
+    forced full schedule: same neighbours, maps and merged rows; sampled images against
+    the oracle."""
+    D, ns = WORK_CASES[name]
+    rng = np.random.default_rng(len(ns) + D)
+    print(f"work distribution {name} {dtype}: rows {mpm.affinity_block_rows(len(ns), max(ns), D, TORCH_DT[dtype], packed=True)}",
+          flush=True)
+    imgs = [store(clustered(rng, n, D, k=max(1, n // 6)), dtype) for n in ns]
+    x, off, N = packed(imgs)
+    m = mpm.merge(x, off, N=N)
+    f = mpm.merge(x, off, N=N, schedule="full")
+    torch.cuda.synchronize()
+    total = int(m.y_off[-1])
+    assert torch.equal(m.y_off, f.y_off) and torch.equal(m.map, f.map)
+    assert torch.equal(m.y[:total], f.y[:total])
+    nb, fb = m.nb.cpu().numpy(), f.nb.cpu().numpy()
+    for b, n in enumerate(ns):
+        assert np.array_equal(nb[b, :n], fb[b, :n]), b
+        if n and b in (0, 1, 2, len(ns) - 1):
+            check_nearest(to64(imgs[b]), nb[b, :n])
+
+
+@pytest.mark.parametrize("B,N,D", [(1, 1500, 64), (5, 1024, 768), (24, 1024, 384), (9, 900, 192), (48, 200, 64)])
+def test_picked_blocks_equal_full(B, N, D):
+    """Dense batches: nearest neighbours and cosines of the automatic pick are bit for bit
+    those of the full schedule on 256 x 256 blocks."""
+    rng = np.random.default_rng(B * N)
+    x = torch.stack([store(clustered(rng, N, D, k=20), "bf16") for _ in range(B)]).to(DEV)
+    print(f"picked blocks B={B} N={N} D={D}: {mpm.affinity_block_rows(B, N, D, torch.bfloat16)} rows", flush=True)
+    nb, best = mpm.argmax(x, with_best=True)
+    fn, fb = mpm.argmax(x, with_best=True, schedule="full")
+    torch.cuda.synchronize()
+    assert torch.equal(nb, fn) and torch.equal(best.view(torch.int32), fb.view(torch.int32))

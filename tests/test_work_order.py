@@ -1,0 +1,126 @@
+"""The affinity's work distribution (csrc/mpm_work.h) on the CPU: over equal and ragged
+batches, every block of every image belongs to exactly one workgroup of one launch."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+DRIVER = r"""
+#include "mpm_work.h"
+#include <cstdio>
+#include <cstdlib>
+#include <map>
+#include <random>
+#include <tuple>
+#include <vector>
+using namespace mpm;
+
+static long shapes = 0;
+
+template <WorkOrder ORDER, bool SPLIT, bool TAB>
+static void check(const std::vector<int>& nb, int log_groups, int slots)
+{
+    const int B = (int)nb.size();
+    std::vector<int32_t> items(B + 1, 0), diags(B + 1, 0);
+    for (int b = 0; b < B; ++b) {
+        items[b + 1] = items[b] + work_items(ORDER, nb[b]);
+        diags[b + 1] = diags[b] + nb[b];
+    }
+    const WorkShape shape(ORDER, B, nb[0] ? nb[0] : 1);
+    const WorkCounts<TAB> c{shape, items.data(), diags.data()};
+    std::map<std::tuple<int, int, int>, int> seen;
+    int least = 1 << 30, most = 0;
+    for (int g = 0; g < 1 << log_groups; ++g) {
+        const WorkShare s = work_share(c, B, g, log_groups, slots, SPLIT);
+        least = s.cnt < least ? s.cnt : least;
+        most = s.cnt > most ? s.cnt : most;
+        if (2 * s.ndef > slots || (s.ndef && (s.cnt - s.ndef) % slots)) { std::printf("rounds\n"); std::exit(1); }
+        for (int slot = 0; slot < slots; ++slot) {
+            int from = s.cnt > slot && s.lo < items[B] ? work_image(c, B, s.lo) : 0;
+            for (int r = slot; r < s.cnt - s.ndef; r += slots) {
+                const WorkBlock k = work_block<ORDER, SPLIT>(c, s, r, from);
+                if (k.b < from) { std::printf("backwards\n"); std::exit(1); }
+                from = k.b;
+                ++seen[{k.b, k.q, k.t}];
+            }
+        }
+        for (int e = 0; e < s.ndef; ++e) {
+            const WorkBlock k = work_deferred(c, B, s, e);
+            ++seen[{k.b, k.q, k.t}];
+        }
+    }
+    if (most - least > 1) { std::printf("unbalanced\n"); std::exit(1); }
+    long want = 0;
+    for (int b = 0; b < B; ++b)
+        for (int q = 0; q < nb[b]; ++q)
+            for (int t = 0; t < nb[b]; ++t) {
+                if (ORDER == kOrderSymmetric && t < q) continue;
+                if (ORDER == kOrderBand && t != q) continue;
+                ++want;
+                if (seen[{b, q, t}] != 1) {
+                    std::printf("B=%d block (%d, %d, %d) taken %d times\n", B, b, q, t, seen[{b, q, t}]);
+                    std::exit(1);
+                }
+            }
+    if ((long)seen.size() != want) { std::printf("%zu items, %ld blocks\n", seen.size(), want); std::exit(1); }
+    ++shapes;
+}
+
+template <WorkOrder ORDER, bool SPLIT>
+static void all(std::vector<int> n, int nb, int log_groups, int slots, std::mt19937& rng)
+{
+    check<ORDER, SPLIT, false>(n, log_groups, slots);
+    check<ORDER, SPLIT, true>(n, log_groups, slots);
+    for (int& v : n) v = (int)(rng() % (nb + 1));  // empty images among them
+    check<ORDER, SPLIT, true>(n, log_groups, slots);
+}
+
+int main()
+{
+    std::mt19937 rng(7);
+    for (int B : {1, 2, 3, 7, 8, 9, 16, 24, 33, 64, 65})
+        for (int nb : {1, 2, 3, 4, 5, 9, 16})
+            for (int groups : {0, 3})
+                for (int slots : {256 >> groups, 512 >> groups, 5}) {
+                    const std::vector<int> n(B, nb);
+                    all<kOrderFull, false>(n, nb, groups, slots, rng);
+                    all<kOrderSymmetric, false>(n, nb, groups, slots, rng);
+                    all<kOrderSymmetric, true>(n, nb, groups, slots, rng);
+                    all<kOrderBand, false>(n, nb, groups, slots, rng);
+                }
+    for (int B = 1; B < 200; ++B) {  // the places are a permutation of the images
+        const WorkShape shape(kOrderFull, B, 1);
+        std::vector<int> hit(B, 0);
+        for (int i = 0; i < B; ++i) {
+            const int b = work_place(i, shape.run);
+            if (b < 0 || b >= B || hit[b]++) { std::printf("place %d of %d: %d\n", i, B, b); return 1; }
+        }
+    }
+    for (uint32_t d : {1u, 2u, 3u, 7u, 10u, 36u, 136u, 4096u, 65535u, 65536u, 1000003u, 0x7fffffffu}) {
+        const FixedDiv f(d);
+        for (uint32_t k = 0; k < 100000; ++k) {
+            const uint32_t v = (k < 1000 ? k : k < 2000 ? 0x7fffffffu - (k - 1000) : rng()) & 0x7fffffffu;
+            if ((uint32_t)f((int)v) != v / d) { std::printf("%u / %u\n", v, d); return 1; }
+        }
+    }
+    std::printf("%ld\n", shapes);
+    return 0;
+}
+"""
+
+
+def test_every_block_exactly_once(tmp_path):
+    if shutil.which("g++") is None:
+        pytest.skip("no host compiler")
+    src = tmp_path / "work.cpp"
+    src.write_text(DRIVER)
+    exe = tmp_path / "work"
+    csrc = os.path.join(ROOT, "paper_2604_05718_amd", "csrc")
+    subprocess.run(["g++", "-O1", "-std=c++17", "-Wall", "-Werror", "-fsanitize=undefined,address", "-I", csrc,
+                    str(src), "-o", str(exe)], check=True)
+    r = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout + r.stderr
+    assert int(r.stdout) > 1000
