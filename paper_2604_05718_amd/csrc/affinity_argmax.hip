@@ -104,7 +104,8 @@ __device__ __forceinline__ void lds_barrier()
 // along an image (raster order, which the left-to-right ids keep for merged tokens).
 struct Window {
     const int32_t* pos;
-    int grid_w, radius;
+    FixedDiv grid_w;  // row of a position: grid_w(pos)
+    int radius;
 };
 
 // Lane exchanges for the reverse-direction argmax of the symmetric schedule.
@@ -118,6 +119,12 @@ template <int CTRL>
 __device__ __forceinline__ int32_t dpp_i(int32_t x)
 {
     return __builtin_amdgcn_update_dpp(0, x, CTRL, 0xF, 0xF, false);
+}
+// x + the value of the lane 32 away.
+__device__ __forceinline__ float half_sum(float x)
+{
+    const auto s = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return __uint_as_float(s[0]) + __uint_as_float(s[1]);
 }
 // (v, i) = the lexicographic maximum of (av, ai) and (bv, bi): larger score, then
 // smaller index (as unsigned, so -1 loses every tie). Branch-free.
@@ -248,18 +255,19 @@ __global__ __launch_bounds__(WC * WQ * kWave, 2) void affinity_partial_kernel(  
     static_assert(KG % 2 == 0, "the fragment double buffer alternates over an even number of k-groups");
 
     __shared__ __attribute__((aligned(1024))) uint8_t lds[2 * STAGE_BYTES];
-    __shared__ __attribute__((aligned(16))) float inv_c[CT];
+    __shared__ __attribute__((aligned(16))) float inv_all[CT + (SYM ? QT : 0)];  // of the candidates, then the queries
+    float* const inv_c = inv_all;
+    float* const inv_q = inv_all + (SYM ? CT : 0);
     __shared__ float red_v[WC][QT];
     __shared__ int32_t red_i[WC][QT];
-    __shared__ __attribute__((aligned(16))) float inv_q[SYM ? QT : 1];
     __shared__ float red_cv[SYM ? WQ : 1][SYM ? CT : 1];
     __shared__ int32_t red_ci[SYM ? WQ : 1][SYM ? CT : 1];
     // LOCAL: grid row [0] and column [1] of the item's candidates (0 .. CT-1) and queries (CT ..).
     __shared__ __attribute__((aligned(16))) int32_t win_rc[2][LOCAL ? CT + QT : 1];
+    __shared__ int32_t win_pos[LOCAL ? CT + QT : 1];  // ... their positions as given
     static_assert(!LOCAL || (!HALVES && QT == CT && CT + QT <= WC * WQ * kWave),
                   "window items: square blocks, one position per thread");
     static_assert(!SYM || QT == CT, "the symmetric schedule pairs equal blocks");
-    static_assert(CT + (SYM ? QT : 0) <= THREADS, "one given inverse norm per thread and item");
     static_assert(!GIVEN || S::kBytes == 2, "given norms: bfloat16 rows");
     constexpr bool given = GIVEN;
 
@@ -329,7 +337,7 @@ __global__ __launch_bounds__(WC * WQ * kWave, 2) void affinity_partial_kernel(  
                 it.thi = t;
                 if constexpr (LOCAL) {
                     // Candidate tiles whose grid rows can meet the block's window rows.
-                    auto grid_row = [&](int i) { return (win.pos ? win.pos[row0 + i] : i) / win.grid_w; };
+                    auto grid_row = [&](int i) { return win.grid_w(win.pos ? win.pos[row0 + i] : i); };
                     const int r_first = grid_row(qbase), r_last = grid_row(min(qbase + QT, n) - 1);
                     int tlo = 0, thi = (n - 1) / CT;
                     while (tlo < thi && grid_row(min((tlo + 1) * CT, n) - 1) < r_first - win.radius) ++tlo;
@@ -521,28 +529,66 @@ __global__ __launch_bounds__(WC * WQ * kWave, 2) void affinity_partial_kernel(  
     };
     Item ci = ii;  // compute cursor
     issue_next();  // prologue: the first chunk
-    // With given norms, thread t fetches the inverse norm of candidate row t (t < CT) or
-    // query row t - CT (symmetric schedule) of the compute cursor's item when the cursor
-    // reaches it; the value is written to LDS at the item's end. Rows past the image are
-    // clamped, as the loads are.
-    float inv_pre = 0.0f;
-    auto fetch_inv = [&](const Item& it) {
-        if (given && it.k < nitems) {
-            const int r = tid < CT ? it.cbase + tid : it.qbase + tid - CT;
-            if (tid < CT || (SYM && tid < CT + QT)) inv_pre = xinv[it.row0 + min(r, it.n - 1)];
-        }
+    // Values of the compute cursor's rows (one per candidate row, then one per query row) that
+    // its epilogue reads, loaded straight to LDS once the first chunk's barrier has retired
+    // them there: given inverse norms, given grid positions (LOCAL). They land before the next
+    // chunk's barrier, behind that chunk's MFMAs; loaded to a register before the chunk's own
+    // wait, they held every item up for their latency.
+    constexpr int VALUES = CT + (SYM ? QT : 0);
+    static_assert(VALUES % kWave == 0 && VALUES <= THREADS, "one value per thread at most");
+    auto fetch_rows = [&](const Item& it, const void* values, void* to) {
+        if (wave * kWave >= VALUES) return;  // uniform
+        const int r = min(tid < CT ? it.cbase + tid : it.qbase + tid - CT, it.n - 1);
+        const uint8_t* base = static_cast<const uint8_t*>(values) + 4L * it.row0;  // uniform
+        const uint32_t m0 =
+            (uint32_t)(size_t)(__attribute__((address_space(3))) uint8_t*)(static_cast<uint8_t*>(to) + wave * kWave * 4);
+        asm volatile("global_load_lds_dword %0, %1" ::"v"(4 * r), "s"(base), "{m0}"(m0) : "memory");
     };
-    // LOCAL: thread t fetches the grid position of candidate row t or query row t - CT of
-    // the compute cursor's tile; it goes to win_rc at the tile's end.
-    int pos_pre = 0;
-    auto fetch_pos = [&](const Item& it) {
-        if (LOCAL && it.k < nitems && tid < CT + QT) {
-            const int r = min(tid < CT ? it.cbase + tid : it.qbase + tid - CT, it.n - 1);
-            pos_pre = win.pos ? win.pos[it.row0 + r] : r;
-        }
+    auto fetch_item = [&](const Item& it) {
+        if constexpr (given) fetch_rows(it, xinv, inv_all);
+        if constexpr (LOCAL)
+            if (win.pos) fetch_rows(it, win.pos, win_pos);
     };
-    fetch_inv(ci);
-    fetch_pos(ci);
+    // The partials of an item are merged over the waves and stored at the next item's first
+    // chunk (after the loop for the last one): the chunk's barrier makes the waves' shares
+    // visible, so the epilogue has no barrier of its own for them, and the stores complete
+    // behind that chunk's MFMAs instead of ahead of its wait.
+    bool pend_fwd = false, pend_rev = false;
+    Item done = ci;
+    auto flush = [&]() {
+        const int n = done.n;
+        if (pend_fwd && tid < QT && done.qbase + tid < n) {
+            // The query block's partial: its tile's slot (LOCAL: the block's own slot, whose
+            // earlier slots take the reverse direction).
+            const int t = LOCAL ? done.qbase / QT : done.cbase / CT;
+            const int qi = done.qbase + tid;
+            float v = red_v[0][tid];
+            int32_t i = red_i[0][tid];
+#pragma unroll
+            for (int w = 1; w < WC; ++w) merge_pair(v, i, v, i, red_v[w][tid], red_i[w][tid]);
+            const long o = ((long)done.b * T + t) * N + qi;
+            pv[o] = v;
+            pi[o] = i;
+        }
+        if constexpr (SYM) {
+            // Candidate rows of the tile over the query block (the block's tile slot), on the
+            // threads without a query.
+            static_assert(THREADS >= CT + QT, "a thread per candidate row besides the queries'");
+            const int jl = tid - (THREADS - CT);
+            if (pend_rev && jl >= 0 && done.cbase + jl < n) {
+                float v = red_cv[0][jl];
+                int32_t i = red_ci[0][jl];
+#pragma unroll
+                for (int w = 1; w < WQ; ++w) merge_pair(v, i, v, i, red_cv[w][jl], red_ci[w][jl]);
+                // A row with no query of the block inside its window: -inf, and no index.
+                if (LOCAL && v == -__builtin_inff()) i = -1;
+                const long o = ((long)done.b * T + done.qbase / QT) * N + done.cbase + jl;
+                pv[o] = v;
+                pi[o] = i;
+            }
+        }
+        pend_fwd = pend_rev = false;
+    };
     // LOCAL: each query's best so far over the item's earlier tiles (this lane's n-tiles).
     float bv_run[LOCAL ? NT : 1];
     int32_t bi_run[LOCAL ? NT : 1];
@@ -554,9 +600,9 @@ __global__ __launch_bounds__(WC * WQ * kWave, 2) void affinity_partial_kernel(  
     int cchunk = 0;
     int consumed = 0;
     while (ci.k < nitems) {
-        // Chunk c has landed for this wave; after the barrier for every wave, and every
-        // wave is done with chunk c-1, whose stage then takes chunk c+1.
-        __builtin_amdgcn_s_waitcnt(0x0F70);
+        // Chunk c has landed for this wave (and its LDS writes are done); after the barrier for
+        // every wave, and every wave is done with chunk c-1, whose stage then takes chunk c+1.
+        __builtin_amdgcn_s_waitcnt(0x0070);  // vmcnt(0), lgkmcnt(0)
         if constexpr (TAIL) {
             if (cchunk == nchunks - 1) {
                 if (cchunk * CB + lcol >= rowbytes) {
@@ -570,6 +616,10 @@ __global__ __launch_bounds__(WC * WQ * kWave, 2) void affinity_partial_kernel(  
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
         read_frags(fa0, fq0, consumed, 0);
+        if (cchunk == 0) {
+            flush();
+            fetch_item(ci);
+        }
         advance();
         issue_begin();
 #pragma unroll
@@ -586,15 +636,13 @@ __global__ __launch_bounds__(WC * WQ * kWave, 2) void affinity_partial_kernel(  
         if (++cchunk < nchunks) continue;
 
         // ---- end of an item: norms, scores, per-query partial argmax ----
-        if (given) {
-            if (tid < CT) inv_c[tid] = inv_pre;
-            else if (SYM && tid < CT + QT) inv_q[SYM ? tid - CT : 0] = inv_pre;
-        } else {
+        if (nchunks == 1 && (given || LOCAL)) __builtin_amdgcn_s_waitcnt(0x0F70);  // the item's own values have landed
+        if constexpr (!given) {
 #pragma unroll
             for (int j = 0; j < NSC; ++j) {
                 const int mt = wq + j * WQ;
                 if (mt >= MT) break;
-                const float t = ss[j] + __shfl_xor(ss[j], 32);  // lanes l, l+32: the two k halves
+                const float t = half_sum(ss[j]);  // lanes l, l+32: the two k halves
                 if (khalf == 0) inv_c[wc * MT * 32 + mt * 32 + lrow] = 1.0f / fmaxf(sqrtf(t), 1e-12f);
             }
             if constexpr (SYM) {
@@ -602,7 +650,7 @@ __global__ __launch_bounds__(WC * WQ * kWave, 2) void affinity_partial_kernel(  
                 for (int j = 0; j < NSQ; ++j) {
                     const int nt = wc + j * WC;
                     if (nt >= NT) break;
-                    const float t = sq[j] + __shfl_xor(sq[j], 32);
+                    const float t = half_sum(sq[j]);
                     if (khalf == 0) inv_q[wq * NT * 32 + nt * 32 + lrow] = 1.0f / fmaxf(sqrtf(t), 1e-12f);
                 }
             }
@@ -613,11 +661,14 @@ __global__ __launch_bounds__(WC * WQ * kWave, 2) void affinity_partial_kernel(  
         for (int j = 0; j < NSQ; ++j) sq[j] = 0.0f;
         if constexpr (LOCAL) {
             if (tid < CT + QT) {
-                win_rc[0][tid] = pos_pre / win.grid_w;
-                win_rc[1][tid] = pos_pre % win.grid_w;
+                const int p = win.pos ? win_pos[tid] : min(tid < CT ? ci.cbase + tid : ci.qbase + tid - CT, ci.n - 1);
+                const int row = win.grid_w(p);
+                win_rc[0][tid] = row;
+                win_rc[1][tid] = p - row * (int)win.grid_w.d;
             }
         }
-        lds_barrier();
+        // Given norms are visible since the second chunk's barrier.
+        if (!given || LOCAL || nchunks == 1) lds_barrier();
         const float* iv = inv_c;
         const int n = ci.n;
         const int cb = ci.cbase;
@@ -844,84 +895,51 @@ __global__ __launch_bounds__(WC * WQ * kWave, 2) void affinity_partial_kernel(  
             }
         }
         if (item_end) {
-            // Merge the two lane halves, then the WC candidate waves (larger score, then smaller index).
+            // Merge the two lane halves (larger score, then smaller index); the waves' merge follows
+            // in flush(). Two n-tiles at a time: after the swap, a lane holds one half's entry of
+            // the first tile (lanes 0-31) or the second (32-63) and the other half's.
+            static_assert(NT == 1 || NT % 2 == 0, "n-tiles in pairs");
 #pragma unroll
-            for (int nt = 0; nt < NT; ++nt) {
-                float v = bv[nt];
-                int32_t i = bi[nt];
-                const float ov = __shfl_xor(v, 32);
-                const int32_t oi = __shfl_xor(i, 32);
-                if (ov > v || (ov == v && (uint32_t)oi < (uint32_t)i)) {
-                    v = ov;
-                    i = oi;
-                }
-                if (khalf == 0) {
-                    const int ql = wq * NT * 32 + nt * 32 + lrow;
+            for (int nt = 0; nt < NT; nt += 2) {
+                const int n2 = NT == 1 ? nt : nt + 1;
+                const auto sv = __builtin_amdgcn_permlane32_swap(__float_as_uint(bv[nt]), __float_as_uint(bv[n2]), false, false);
+                const auto si = __builtin_amdgcn_permlane32_swap((uint32_t)bi[nt], (uint32_t)bi[n2], false, false);
+                float v;
+                int32_t i;
+                merge_pair(v, i, __uint_as_float(sv[0]), (int32_t)si[0], __uint_as_float(sv[1]), (int32_t)si[1]);
+                const int ql = wq * NT * 32 + nt * 32 + (NT == 1 ? lrow : lane);
+                if (NT > 1 || khalf == 0) {
                     red_v[wc][ql] = v;
                     red_i[wc][ql] = i;
                 }
             }
         }
-        if (item_end || rev) lds_barrier();  // uniform
-        if (item_end) {
-            // The query block's partial: tile slot t (LOCAL: slot 0, or the block's own slot
-            // under the symmetric schedule, whose earlier slots take the reverse direction).
-            const int t = LOCAL ? (SYM ? ci.qbase / QT : 0) : cb / CT;
-            for (int ql = tid; ql < QT; ql += THREADS) {
-                const int qi = ci.qbase + ql;
-                if (qi >= n) continue;
-                float v = red_v[0][ql];
-                int32_t i = red_i[0][ql];
-#pragma unroll
-                for (int w = 1; w < WC; ++w) {
-                    const float ov = red_v[w][ql];
-                    const int32_t oi = red_i[w][ql];
-                    if (ov > v || (ov == v && (uint32_t)oi < (uint32_t)i)) {
-                        v = ov;
-                        i = oi;
-                    }
-                }
-                const long o = ((long)ci.b * T + t) * N + qi;
-                pv[o] = v;
-                pi[o] = i;
-                if constexpr (LOCAL && SYM) {
-                    // The slots no item writes for this block's rows: tiles before the band and
-                    // after the block (the band relation is symmetric, so the items that write
-                    // slot q for these rows are exactly the blocks q of the band before it).
-                    const int nq = (n + QT - 1) / QT;
-                    for (int q = 0; q < nq; ++q) {
-                        if (q >= ci.tlo && q <= t) continue;
-                        const long oq = ((long)ci.b * T + q) * N + qi;
-                        pv[oq] = -__builtin_inff();
-                        pi[oq] = -1;
-                    }
+        if constexpr (LOCAL) {
+            // The slots no item writes for this block's rows: tiles before the band and after
+            // the block (the band relation is symmetric, so the items that write slot q for
+            // these rows are exactly the blocks q of the band before it).
+            if (item_end && tid < QT && ci.qbase + tid < n) {
+                const int nq = (n + QT - 1) / QT, own = ci.qbase / QT;
+                for (int q = 0; q < nq; ++q) {
+                    if (q >= ci.tlo && q <= own) continue;
+                    const long oq = ((long)ci.b * T + q) * N + ci.qbase + tid;
+                    pv[oq] = -__builtin_inff();
+                    pi[oq] = -1;
                 }
             }
         }
-        if (rev) {
-            // Candidate rows of the tile over the query block: tile slot qbase / QT of their partials.
-            const int tq = ci.qbase / QT;
-            for (int jl = tid; jl < CT; jl += THREADS) {
-                const int j = cb + jl;
-                if (j >= n) continue;
-                float v = red_cv[0][jl];
-                int32_t i = red_ci[0][jl];
-#pragma unroll
-                for (int w = 1; w < WQ; ++w) merge_pair(v, i, v, i, red_cv[w][jl], red_ci[w][jl]);
-                // A row with no query of the block inside its window: -inf, and no index.
-                if (LOCAL && v == -__builtin_inff()) i = -1;
-                const long o = ((long)ci.b * T + tq) * N + j;
-                pv[o] = v;
-                pi[o] = i;
-            }
-        }
+        pend_fwd = item_end;
+        pend_rev = rev;
+        done = ci;
         cchunk = 0;
         ci = inext;  // loads run one chunk ahead: the chunk issued last is the next item's first
-        fetch_inv(ci);
-        fetch_pos(ci);
         if constexpr (HALVES) lq_off = (ci.qbase - ci.cbase + wq * NT * 32 + lrow) * CB;
     }
-    __builtin_amdgcn_s_waitcnt(0x0F70);  // the trailing loads land before the workgroup's LDS is released
+    __builtin_amdgcn_s_waitcnt(0x0070);
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    flush();
+    // (The waits above also cover the trailing loads, which land before the LDS is released.)
 }
 
 // Block shapes. 256 x 256 on 8 waves (two 64 KB stages, one workgroup per CU): the full
@@ -1250,7 +1268,7 @@ hipError_t launch_affinity(const void* x, const int32_t* x_off, int B, int N, in
     if (cus <= 0) return hipErrorInvalidDevice;
     const int xcds = cus % kXcds == 0 ? kXcds : 1;
     const AffinityArgs a{x, x_off, dt == kBf16 ? xinv : nullptr, B, N, D, T, xcds, pv, pi, stream, start, stop,
-                         Window{nullptr, 1, 0}};
+                         Window{nullptr, FixedDiv(1), 0}};
     switch (pick_blocks(B, N, D, dt, schedule, x_off != nullptr)) {
     case kBlocks64: launch_persistent<kTWC, kTWQ, kTMT, kTNT, false>(dt, a, cus * kTWGS); break;
     case kBlocks128: launch_persistent<kLWC, kLWQ, kLMT, kLNT, true>(dt, a, cus * kLWGS); break;
@@ -1272,7 +1290,7 @@ hipError_t launch_affinity_local(const void* x, const int32_t* x_off, const floa
     if (cus <= 0) return hipErrorInvalidDevice;
     const int xcds = cus % kXcds == 0 ? kXcds : 1;
     const AffinityArgs a{x, x_off, dt == kBf16 ? xinv : nullptr, B, N, D, T, xcds, pv, pi, stream, start, stop,
-                         Window{pos, grid_w, radius}};
+                         Window{pos, FixedDiv((uint32_t)grid_w), radius}};
     if (block_rows == kLCT) launch_persistent<kLWC, kLWQ, kLMT, kLNT, true, true>(dt, a, cus * kLWGS);
     else launch_persistent<kSWC, kSWQ, kSMT, kSNT, true, true>(dt, a, cus * kPWGS);
     return hipGetLastError();
