@@ -1083,11 +1083,12 @@ namespace {
 // workgroup per CU (the dense symmetric shape), or 128 x 128 blocks on 4 waves of 64 x 64,
 // two workgroups per CU. Smaller blocks cut a query block's window band more finely and
 // give twice the items; each small block costs about 0.357 of a large one (a quarter of
-// its matrix work at about 70% of its efficiency: half the flops per byte loaded).
+// its matrix work at about 70% of its efficiency: half the flops per byte loaded), of float32
+// rows 0.29 (they are bound by the matrix work).
 constexpr int kLWC = 2, kLWQ = 2, kLMT = 2, kLNT = 2, kLWGS = 2;
 constexpr int kLCT = kLWC * kLMT * 32;
 static_assert(kLWQ * kLNT * 32 == kLCT && kPCT % kLCT == 0 && kLCT % kTCT == 0, "square small window blocks");
-constexpr double kLSmallBlockCost = 0.357;
+constexpr double kLSmallBlockCost = 0.357, kLSmallBlockCostF32 = 0.29;
 
 // Estimated duration (in large-block times) of a locality-constrained launch with ts x ts
 // blocks, on a full raster grid (positions = token indices): per XCD group, the blocks of
@@ -1130,7 +1131,8 @@ int local_rows(int B, int N, int D, int dt, int grid_w, int radius, int requeste
     if (cus <= 0) return kPCT;
     const int xcds = cus % kXcds == 0 ? kXcds : 1;
     const double large = local_cost(B, N, grid_w, radius, kPCT, xcds, cus * kPWGS / xcds, kPWGS, 1.0);
-    const double small = local_cost(B, N, grid_w, radius, kLCT, xcds, cus * kLWGS / xcds, kLWGS, kLSmallBlockCost);
+    const double small = local_cost(B, N, grid_w, radius, kLCT, xcds, cus * kLWGS / xcds, kLWGS,
+                                    dt == kBf16 ? kLSmallBlockCost : kLSmallBlockCostF32);
     return small < large ? kLCT : kPCT;
 }
 
@@ -1191,6 +1193,32 @@ double estimate_us(Blocks k, double blocks64, double blocks128, double full256, 
     }
 }
 
+// float32 rows: a block's matrix work outweighs the rest of it at every row width, so only the
+// rounds count, in units of a round of 128 x 128 symmetric blocks (two per CU); one of 256 x 256
+// blocks takes 1.8. Up to four 64 x 64 blocks a CU run as fast as the rest of the chip allows
+// (they are whole rounds of a quarter of the work). Timed on 170 dense and 170 packed shapes, 1 to
+// 64 images of 100 to 4096 rows of 192 to 4096 bytes: 0.6% slower than the fastest of the four
+// shapes, against 59% for 64 x 64 blocks of at most 32 large blocks and 256 x 256 ones elsewhere.
+// Examples, 64 / 128 / 256 full / 256 symmetric, dense rows of 768 bytes: 4 images of 1024 rows
+// 19.1 / 19.5 / 49.0 / 52.5 us; 16 of 1024 rows 60.3 / 44.5 / 50.0 / 52.6; 32 of 1024 rows
+// - / 78.9 / 106.4 / 86.7; 46 of 1924 rows of 832 bytes - / 420.6 / 660.8 / 384.5.
+Blocks pick_blocks_f32(double blocks64, double blocks128, double sym256, double cus, bool packed)
+{
+    if (blocks64 <= 4 * cus) return kBlocks64;
+    const double r = blocks128 / (2 * cus), s = sym256 / cus;
+    double rounds128, rounds256;
+    if (packed) {  // lengths are only guessed: a part of a round is taken to cost its mean
+        rounds128 = 1.1 * r <= 0.5 ? 0.6 : 1.1 * r <= 1 ? 1.0 : r + 0.3;
+        rounds256 = 1.8 * (1.1 * s <= 1 ? 1.0 : s + 0.6);
+    } else {
+        const double f = r - std::floor(r), g = s - std::floor(s);
+        // The last round: alone on their CUs up to half of the slots; as half blocks.
+        rounds128 = std::floor(r) + (f <= 0 ? 0.0 : f <= 0.5 ? 0.6 : 0.95);
+        rounds256 = 1.8 * (std::floor(s) + (g <= 0 ? 0.0 : s > 1 && g <= 0.5 ? 0.6 : 1.0));
+    }
+    return rounds128 <= rounds256 ? kBlocks128 : kBlocksSym256;
+}
+
 Blocks pick_blocks(int B, int N, int D, int dt, int schedule, bool packed)
 {
     if (whole_64(D, dt)) {
@@ -1204,15 +1232,6 @@ Blocks pick_blocks(int B, int N, int D, int dt, int schedule, bool packed)
     };
     const double capacity64 = blocks(kTCT, kOrderFull, 100);
     const double full256 = blocks(kPCT, kOrderFull, 100);
-    if (dt != kBf16) {
-        // float32: a block's matrix work outweighs the rest of it, so only the rounds count (an
-        // off-diagonal symmetric item costs a fifth more for its reverse direction).
-        const double nqb = std::sqrt(full256 / B), xcds = cus % kXcds == 0 ? kXcds : 1;
-        if (full256 <= 32) return kBlocks64;
-        const double nimg = std::ceil(B / xcds), slots = cus / xcds;
-        return 5 * std::ceil(nimg * nqb * (nqb + 1) / 2 / slots) < 4 * std::ceil(nimg * nqb * nqb / slots) ? kBlocksSym256
-                                                                                                            : kBlocks256;
-    }
     const double c = std::ceil(2.0 * D / kChunkBytes);
     double b64 = capacity64, b128 = blocks(kLCT, kOrderSymmetric, 100), s256 = blocks(kPCT, kOrderSymmetric, 100);
     if (packed) {  // images as an earlier insertion leaves them: 80 to 90% of N tokens
@@ -1223,6 +1242,7 @@ Blocks pick_blocks(int B, int N, int D, int dt, int schedule, bool packed)
             s256 += blocks(kPCT, kOrderSymmetric, percent) / 3;
         }
     }
+    if (dt != kBf16) return pick_blocks_f32(b64, b128, s256, cus, packed);
     Blocks best = kBlocks128;
     double us = estimate_us(kBlocks128, b64, b128, full256, s256, c, cus, packed);
     for (Blocks k : {kBlocks64, kBlocks256, kBlocksSym256}) {

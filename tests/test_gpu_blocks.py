@@ -109,3 +109,21 @@ def test_picked_blocks_equal_full(B, N, D):
     fn, fb = mpm.argmax(x, with_best=True, schedule="full")
     torch.cuda.synchronize()
     assert torch.equal(nb, fn) and torch.equal(best.view(torch.int32), fb.view(torch.int32))
+
+
+# float32 batches on either side of each line of the pick: small blocks at most four a CU,
+# two rounds of middling blocks, one round of large ones, several rounds; two row widths that
+# end inside a chunk.
+@pytest.mark.parametrize("B,N,D", [(16, 512, 64), (17, 512, 64), (32, 1024, 36), (24, 990, 64), (1, 4096, 20)])
+def test_picked_blocks_equal_small_f32(B, N, D):
+    """Neighbours and cosines of a float32 batch do not depend on the blocks: bit for bit
+    those of the same images one by one (64 x 64 blocks), image 0 also against the oracle."""
+    rng = np.random.default_rng(B * N + D)
+    x = torch.stack([store(clustered(rng, N, D, k=20), "f32") for _ in range(B)]).to(DEV)
+    print(f"picked blocks f32 B={B} N={N} D={D}: {mpm.affinity_block_rows(B, N, D, torch.float32)} rows", flush=True)
+    nb, best = mpm.argmax(x, with_best=True)
+    for b in sorted({0, B // 2, B - 1}):
+        one, cos = mpm.argmax(x[b:b + 1].contiguous(), with_best=True)
+        torch.cuda.synchronize()
+        assert torch.equal(nb[b], one[0]) and torch.equal(best[b].view(torch.int32), cos[0].view(torch.int32)), b
+    check_nearest(to64(x[0].cpu()), nb[0].cpu().numpy())
