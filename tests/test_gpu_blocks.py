@@ -127,3 +127,28 @@ def test_picked_blocks_equal_small_f32(B, N, D):
         torch.cuda.synchronize()
         assert torch.equal(nb[b], one[0]) and torch.equal(best[b].view(torch.int32), cos[0].view(torch.int32)), b
     check_nearest(to64(x[0].cpu()), nb[0].cpu().numpy())
+
+
+# Tiles within, at and past the 16 lanes of a row; pieces short of the lanes, at four a lane
+# and one past; an empty and a one-token image.
+@pytest.mark.parametrize("dtype,D", [("bf16", 8), ("bf16", 512), ("bf16", 520), ("f32", 60), ("f32", 260)])
+def test_cosines_of_packed_rows(dtype, D):
+    rng = np.random.default_rng(D)
+    ns = [1100, 0, 1, 64, 1025]
+    print(f"cosines {dtype} D={D} ns={ns}", flush=True)
+    x = torch.from_numpy(rng.standard_normal((sum(ns), D)).astype(np.float32)).to(TORCH_DT[dtype])
+    off = np.concatenate([[0], np.cumsum(ns)]).astype(np.int32)
+    nb, best = mpm.argmax(x.to(DEV), torch.from_numpy(off).to(DEV), N=max(ns), with_best=True)
+    only = mpm.argmax(x.to(DEV), torch.from_numpy(off).to(DEV), N=max(ns))
+    torch.cuda.synchronize()
+    nb, only, best = nb.cpu().numpy(), only.cpu().numpy(), best.cpu().numpy()
+    for b, n in enumerate(ns):
+        assert np.array_equal(nb[b, :n], only[b, :n])
+        if n == 1:
+            assert nb[b, 0] == -1 and best[b, 0] == -np.inf
+        if n < 2:
+            continue
+        x64 = to64(x[off[b]:off[b + 1]])
+        for i in (0, 1, 15, 16, 63, n // 2, n - 1):
+            # float32 sums of D products and two float32 norms: below 3 (D + 4) 2^-24.
+            assert abs(best[b, i] - oracle.cosine(x64, i, int(nb[b, i]))) <= 3 * (D + 4) * 2.0 ** -24
