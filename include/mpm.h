@@ -342,6 +342,38 @@ int mpm_merge_local(const void* x, const int32_t* x_off, const float* x_inv, con
                     int32_t* y_off, float* y_inv, int32_t* y_pos, int32_t* map, void* ws, size_t ws_bytes,
                     void* start_event, void* stop_event, void* stream);
 
+/* The buffers of one insertion of mpm_run_schedule, as mpm_merge's arguments of the same
+ * names: y_inv may be NULL (the last insertion's is not written); y_pos is used (and needed)
+ * under the locality constraint only; nb and src are readable in ws after the call. */
+typedef struct mpm_insertion {
+    void* y;
+    int32_t* y_off;
+    float* y_inv;
+    int32_t* y_pos;
+    int32_t* map;
+    void* ws;
+} mpm_insertion;
+
+/*
+ * A whole schedule in one call: `insertions` (1 to 3) insertions with identity blocks in
+ * between (Sec. 3.3), the first on the dense tokens x, each next one on the packed rows,
+ * norms and positions of the one before; the composed map (Eq. 3) and the gather back to the
+ * grid (Eq. 4):
+ *   window < 0: each insertion as mpm_merge(..., schedule, ...) (grid_w, block_rows not used);
+ *   window >= 0: each as mpm_merge_local(..., grid_w, window, block_rows, ...);
+ *   ins[s]: insertion s's buffers, whose workspaces (ws_bytes bytes each) must not overlap;
+ *   rstar: the composed map, int32[B*N] in slot layout (not used, may be NULL, with one
+ *       insertion, whose map is the composed one);
+ *   out: [B][N][D], out[b][i] = the last insertion's merged row of token i.
+ * Results are those of the separate calls, bit for bit. The last pair average writes the
+ * merged rows and the grid in one pass. Errors as mpm_merge and mpm_merge_local, plus
+ * MPM_ERR_INVALID_ARG for insertions < 1 or overlapping workspaces and MPM_ERR_UNSUPPORTED
+ * for more than 3 insertions.
+ */
+int mpm_run_schedule(const void* x, int32_t B, int32_t N, int32_t D, int32_t dt, int32_t schedule, int32_t grid_w,
+                     int32_t window, int32_t block_rows, const mpm_insertion* ins, int32_t insertions,
+                     size_t ws_bytes, int32_t* rstar, void* out, void* stream);
+
 /*
  * Padded batch layout (the paper pads each batch to its longest image, Sec. 4.2): the
  * packed rows of B images (offsets z_off, int32[B+1], as the merges write them) to a

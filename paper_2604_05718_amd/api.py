@@ -338,6 +338,50 @@ class ScheduleResult:
     out: torch.Tensor     # reconstructed grid [B, N, D]
 
 
+MAX_FUSED = 3  # insertions mpm_run_schedule takes
+
+
+def _disjoint(workspaces, insertions) -> bool:
+    """Whether the given workspaces (None: new ones) share no memory."""
+    if workspaces is None or insertions == 1:
+        return True
+    spans = sorted((w.data_ptr(), w.numel()) for w in workspaces[:insertions] if w is not None)
+    return all(p + n <= q for (p, n), (q, _) in zip(spans, spans[1:]))
+
+
+def _run_fused(x, insertions, workspaces, schedule, grid_w, window, block_rows, norms) -> ScheduleResult:
+    """run_schedule through one mpm_run_schedule call."""
+    _, B, N, D = _rows(x, None, None)
+    dev, dt = x.device, _dt(x)
+    local = window is not None
+    sched = _lib.MPM_SCHEDULE_AUTO if local else _sched(schedule)
+    need = workspace_bytes(B, N)
+    stages, ptrs = [], []
+    for s in range(insertions):
+        ws = None if workspaces is None else workspaces[s]
+        if ws is None or ws.numel() < need:
+            ws = new_workspace(B, N, dev)
+        inv = norms and s + 1 < insertions
+        m = Merged(torch.empty((B * N, D), dtype=x.dtype, device=dev), torch.empty((B + 1,), dtype=torch.int32, device=dev),
+                   torch.empty((B, N), dtype=torch.int32, device=dev), ws, B, N,
+                   torch.empty((B * N,), dtype=torch.float32, device=dev) if inv else None,
+                   torch.empty((B * N,), dtype=torch.int32, device=dev) if local else None)
+        stages.append(m)
+        ptrs += _insertion_ptrs(m.y, m.y_off, m.y_inv, m.y_pos, m.map, ws)
+    rstar = torch.empty((B, N), dtype=torch.int32, device=dev) if insertions > 1 else stages[0].map
+    out = torch.empty((B, N, D), dtype=x.dtype, device=dev)
+    _lib.check("mpm_run_schedule", _lib.load().mpm_run_schedule(
+        _p(x), B, N, D, dt, sched, int(grid_w) if local else 0, int(window) if local else -1,
+        int(block_rows) if local else 0, (ctypes.c_void_p * len(ptrs))(*ptrs), insertions, need, _p(rstar), _p(out),
+        _stream()))
+    return ScheduleResult(stages, rstar, out)
+
+
+def _insertion_ptrs(y, y_off, y_inv, y_pos, m, ws) -> list:
+    """The fields of an mpm_insertion."""
+    return [None if t is None else t.data_ptr() for t in (y, y_off, y_inv, y_pos, m, ws)]
+
+
 def run_schedule(x, insertions: int = 2, workspaces=None, schedule: str = "auto", grid_w: int | None = None,
                  window: int | None = None, block_rows: int = 0) -> ScheduleResult:
     """Insertions with identity blocks in between (Sec. 3.3), composed maps
@@ -348,6 +392,8 @@ def run_schedule(x, insertions: int = 2, workspaces=None, schedule: str = "auto"
     ``block_rows``) on a grid of ``grid_w`` columns, the first on the raster positions."""
     B, N, D = x.shape
     norms = takes_norms(D, x.dtype)
+    if 1 <= insertions <= MAX_FUSED and (window is None or window >= 0) and _disjoint(workspaces, insertions):
+        return _run_fused(x, insertions, workspaces, schedule, grid_w, window, block_rows, norms)
     stages = []
     cur, cur_off, cur_inv, cur_pos = x, None, None, None
     rstar = None
@@ -370,10 +416,13 @@ class Schedule:
     """Preallocated MPM schedule for a fixed batch shape: every buffer is
     allocated once, so ``run`` only launches kernels (no allocation, no host
     synchronisation). Stage s consumes stage s-1's packed output (Sec. 3.3);
-    the composed map and the reconstruction follow (Eq. 3, Eq. 4). Each
-    insertion runs mpm_merge's two steps through their entry points (the fused
-    affinity + compaction, then the pair average), so they can be timed one by
-    one; the last composition runs inside the gather.
+    the composed map and the reconstruction follow (Eq. 3, Eq. 4). Up to
+    MAX_FUSED insertions run as one mpm_run_schedule call, whose last pair average
+    also writes the composed map and the grid. With ``marks`` or
+    ``affinity_events``, each insertion runs mpm_merge's two steps through their
+    entry points (the fused affinity + compaction, then the pair average), so they
+    can be timed one by one, and the last composition runs inside the gather; the
+    results are the same, bit for bit.
 
     ``run(x, marks=None, affinity_events=None)``: when ``marks`` is a list of
     ``n_marks()`` torch.cuda.Event objects, event k is recorded on the current
@@ -430,6 +479,16 @@ class Schedule:
         if x.shape != (self.B, self.N, self.D) or x.dtype != self.dtype or not x.is_contiguous():
             raise ValueError("input does not match the schedule's shape/dtype")
         lib, st, B, N, D, dt = self._lib, _stream(), self.B, self.N, self.D, self._dt
+        local = self.window is not None
+        if marks is None and affinity_events is None and self.insertions <= MAX_FUSED and not (local and self.window < 0):
+            ptrs = []
+            for s in range(self.insertions):
+                ptrs += _insertion_ptrs(self.y[s], self.y_off[s], self.y_inv[s], self.y_pos[s], self.map[s], self.ws[s])
+            _lib.check("mpm_run_schedule", lib.mpm_run_schedule(
+                _p(x), B, N, D, dt, self.schedule, self.grid_w if local else 0, self.window if local else -1, 0,
+                (ctypes.c_void_p * len(ptrs))(*ptrs), self.insertions, self.ws[0].numel(), _p(self.rstar),
+                _p(self.out), st))
+            return self.out
         k = 0
 
         def mark():

@@ -549,6 +549,69 @@ int mpm_merge_local(const void* x, const int32_t* x_off, const float* x_inv, con
     return hip_status(e);
 }
 
+int mpm_run_schedule(const void* x, int32_t B, int32_t N, int32_t D, int32_t dt, int32_t schedule, int32_t grid_w,
+                     int32_t window, int32_t block_rows, const mpm_insertion* ins, int32_t insertions,
+                     size_t ws_bytes, int32_t* rstar, void* out, void* stream)
+{
+    int s = check_affinity(x, nullptr, nullptr, B, N, D, dt, schedule);
+    if (s != MPM_OK) return s;
+    if (insertions < 1 || ins == nullptr || !ok_rows_ptr(out) || (insertions > 1 && !ok_int_ptr(rstar)))
+        return MPM_ERR_INVALID_ARG;
+    if (insertions > mpm::kMaxScatterDepth) return MPM_ERR_UNSUPPORTED;
+    const bool local = window >= 0;
+    if (local && (grid_w < 1 || grid_w > MPM_MAX_N || !mpm::valid_local_block_rows(block_rows)))
+        return MPM_ERR_INVALID_ARG;
+    Workspace w[mpm::kMaxScatterDepth];
+    for (int k = 0; k < insertions; ++k) {
+        const mpm_insertion& m = ins[k];
+        if (!ok_rows_ptr(m.y) || !ok_int_ptr(m.y_off) || !ok_opt_int_ptr(m.y_inv) || !ok_opt_int_ptr(m.y_pos) ||
+            !ok_int_ptr(m.map) || (local && m.y_pos == nullptr))
+            return MPM_ERR_INVALID_ARG;
+        if (k + 1 < insertions && m.y_inv && !mpm::affinity_takes_norms(D, dt)) return MPM_ERR_UNSUPPORTED;
+        if ((s = carve(m.ws, ws_bytes, B, N, &w[k])) != MPM_OK) return s;
+        // Every insertion's sources are read at the end.
+        const uintptr_t p = reinterpret_cast<uintptr_t>(m.ws), need = workspace_offsets(B, N).total;
+        for (int j = 0; j < k; ++j) {
+            const uintptr_t q = reinterpret_cast<uintptr_t>(ins[j].ws);
+            if (p < q + need && q < p + need) return MPM_ERR_INVALID_ARG;
+        }
+    }
+    MPM_LAUNCH_GATE();
+    const hipStream_t st = as_stream(stream);
+    const int32_t* src[mpm::kMaxScatterDepth];
+    const void* cur = x;
+    const int32_t *off = nullptr, *pos = nullptr;
+    const float* inv = nullptr;
+    for (int k = 0; k < insertions; ++k) {
+        const mpm_insertion& m = ins[k];
+        src[k] = w[k].src;
+        MPM_DATA_CHECK(checked_rows(cur, off, inv, pos, local ? grid_w : 1, B, N, D, dt, st));
+        hipError_t e;
+        if (local) {
+            const int rows = mpm::local_tile_width(B, N, D, dt, grid_w, window, block_rows);
+            e = mpm::launch_affinity_local(cur, off, inv, pos, grid_w, window, rows, B, N, D, dt, w[k].pv, w[k].pi, st,
+                                           nullptr, nullptr);
+            if (e == hipSuccess) e = compact_partials_ct(w[k], off, B, N, D, dt, rows, m.map, m.y_off, st);
+        } else {
+            e = affinity_compact(cur, off, inv, B, N, D, dt, schedule, m.map, m.y_off, w[k], nullptr, nullptr, st);
+        }
+        int32_t* y_pos = local ? m.y_pos : nullptr;
+        if (e == hipSuccess) {
+            if (k + 1 < insertions)
+                e = mpm::launch_pair_average(cur, off, w[k].src, m.y_off, B, N, D, dt, m.y, m.y_inv, st, pos, y_pos);
+            else
+                e = mpm::launch_pair_average_scatter(cur, off, src, insertions, m.y_off, B, N, D, dt, m.y, pos, y_pos,
+                                                     insertions > 1 ? rstar : nullptr, out, st);
+        }
+        if (e != hipSuccess) return hip_status(e);
+        cur = m.y;
+        off = m.y_off;
+        inv = m.y_inv;
+        pos = y_pos;
+    }
+    return MPM_OK;
+}
+
 int mpm_pad(const void* z, const int32_t* z_off, int32_t B, int32_t P, int32_t row_bytes, void* out, void* stream)
 {
     if (B < 1 || P < 1 || row_bytes < 16 || row_bytes % 16 != 0) return MPM_ERR_INVALID_ARG;

@@ -58,6 +58,13 @@ hipError_t launch_zero_words(int32_t* p, long words, hipStream_t stream);
 hipError_t launch_pair_average(const void* x, const int32_t* x_off, const int32_t* src, const int32_t* y_off, int B,
                                int N, int D, int dt, void* y, float* y_inv, hipStream_t stream,
                                const int32_t* pos = nullptr, int32_t* y_pos = nullptr);
+// The last pair average of a schedule (y, y_pos as launch_pair_average's) that also writes the
+// grid out, dense [B][N][D], and the composed map (map_ab, may be null). src[s]: the sources of
+// insertion s (of `depth`, at most kMaxScatterDepth), whose first one's input was dense.
+constexpr int kMaxScatterDepth = 3;  // a merged row then stands for at most 8 tokens
+hipError_t launch_pair_average_scatter(const void* x, const int32_t* x_off, const int32_t* const* src, int depth,
+                                       const int32_t* y_off, int B, int N, int D, int dt, void* y, const int32_t* pos,
+                                       int32_t* y_pos, int32_t* map_ab, void* out, hipStream_t stream);
 // The affinity partials under the locality constraint (Sec. 5): candidates of each token
 // restricted to the cells within `radius` rows and columns of its own on a grid of
 // grid_w columns (pos: raster positions packed like x, or null for each token's index;

@@ -218,3 +218,31 @@ def test_noalloc_rejects_before_any_device_use(lib):
     assert lib.mpm_merge_noalloc(A, None, None, 2, 16, 64, 1, AUTO, A2, A2, None, None, None) == 1   # map NULL
     assert lib.mpm_merge_noalloc(A, None, A, 2, 16, 64, 0, AUTO, A2, A2, None, A2, None) == 2        # f32 norms
     assert lib.mpm_last_hip_error() == 0
+
+
+def test_run_schedule_rejects(lib):
+    """mpm_run_schedule's own checks, all before anything touches the GPU."""
+    need = lib.mpm_workspace_bytes(4, 64)
+    ptr = lambda *v: (ctypes.c_void_p * len(v))(*v)
+    ok = [0x20000, 0x30000, None, None, 0x40000]
+    far = 0x10000000
+
+    def call(ins, n, window=-1, grid_w=0, block_rows=0, D=64, ws_bytes=need, rstar=A, out=A2, schedule=AUTO):
+        return lib.mpm_run_schedule(A, 4, 64, D, 1, schedule, grid_w, window, block_rows, ptr(*ins), n, ws_bytes, rstar,
+                                    out, None)
+
+    one, two = ok + [far], ok + [far] + ok + [far + 0x10000000]
+    assert call(one, 0) == 1
+    assert call(one * 4, 4) == 2                                    # at most three insertions
+    assert call(one, 1, out=None) == 1
+    assert call(two, 2, rstar=None) == 1
+    assert call(one, 1, D=63) == 1
+    assert call(one, 1, schedule=9) == 1
+    assert call(one, 1, ws_bytes=need - 1) == 3
+    assert call(ok + [far] + ok + [far + (need - 1) // 256 * 256], 2) == 1  # workspaces overlap
+    assert call([MIS.value] + ok[1:] + [far], 1) == 1               # y misaligned
+    assert call(ok[:1] + [None] + ok[2:] + [far], 1) == 1           # no y_off
+    assert call(one, 1, window=2, grid_w=8) == 1                    # a window needs y_pos
+    with_pos = ok[:3] + [0x50000, 0x40000, far]
+    assert call(with_pos, 1, window=2, grid_w=0) == 1
+    assert call(with_pos, 1, window=2, grid_w=8, block_rows=64) == 1
