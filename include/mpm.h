@@ -149,9 +149,9 @@ int mpm_last_hip_error(void);
  *                               for token i at (b*T + t)*N + i; a launch fills the
  *                               first ceil(n_b / w) slots, w = the block width it
  *                               runs (mpm_affinity_block_rows).
- * The sync region must be zero before a workspace's first use by
- * mpm_affinity_compact or mpm_merge (mpm_workspace_init); every call leaves it
- * zero again (an interrupted call may not). Returns 0 for B < 1 or N < 1.
+ * A workspace needs no preparation: each call sets what it counts in to zero
+ * first, and leaves the words of the sync region that it used zero (an
+ * interrupted call may not). Returns 0 for B < 1 or N < 1.
  */
 size_t mpm_workspace_bytes(int32_t B, int32_t N);
 
@@ -162,7 +162,7 @@ int mpm_workspace_offsets(int32_t B, int32_t N, size_t* sync, size_t* nb, size_t
 /*
  * Zeroes the sync region of a workspace of ws_bytes bytes (at least the
  * region's 256 KB) with a fill kernel on `stream` (no memset node, so it may
- * be captured in a HIP graph). Needed once after allocating a workspace.
+ * be captured in a HIP graph). Not needed: calls clear the words they use.
  */
 int mpm_workspace_init(void* ws, size_t ws_bytes, void* stream);
 
@@ -199,15 +199,16 @@ int mpm_affinity(const void* x, const int32_t* x_off, const float* x_inv, int32_
  * image's partials to nb (larger score, then smaller index; images with more
  * than a few candidate tiles are reduced by a separate parallel launch first),
  * tests the pairs for mutuality, marks representatives and assigns compact ids
- * by a left-to-right scan, one workgroup per image; the workgroup that finishes
- * the last image (found with the arrival counter in the workspace's sync
- * region, no waiting) turns the per-image cluster counts into offsets. Writes
+ * by a left-to-right scan, one workgroup per image. Each image's workgroup adds
+ * its cluster count to the offsets of the images after it (y_off is cleared by
+ * the affinity launch, so it must not alias x_off); beyond 256 images the one
+ * that finishes the last image (found with the arrival counter in the
+ * workspace's sync region, no waiting) turns the counts into offsets. Writes
  *   map[b*N + i] = r(i) for i < n_b, -1 for n_b <= i < N;
  *   y_off[0] = 0, y_off[b+1] = y_off[b] + n'_b (int32[B+1]);
  *   the workspace's nb and src regions (src read by mpm_pair_average).
  * The timing events are bound to the affinity kernel's dispatches only.
- * Arguments as mpm_affinity otherwise; the workspace's sync region must be zero
- * (mpm_workspace_init).
+ * Arguments as mpm_affinity otherwise.
  */
 int mpm_affinity_compact(const void* x, const int32_t* x_off, const float* x_inv, int32_t B, int32_t N, int32_t D,
                          int32_t dt, int32_t schedule, int32_t* map, int32_t* y_off, void* ws, size_t ws_bytes,
@@ -299,9 +300,8 @@ int mpm_pair_average(const void* x, const int32_t* x_off, const int32_t* src, co
  *   y, y_off: merged tokens, packed (capacity B*N rows), offsets int32[B+1];
  *   y_inv (may be NULL): inverse norms of the merged rows, as in mpm_pair_average;
  *   map: int32[B*N] merge map in slot layout (-1 beyond n_b);
- *   ws: workspace of at least mpm_workspace_bytes(B, N) bytes whose sync
- *       region is zero (mpm_workspace_init); nb and src are readable there
- *       after the call.
+ *   ws: workspace of at least mpm_workspace_bytes(B, N) bytes; nb and src are
+ *       readable there after the call.
  * Feed (y, y_off, y_inv) as (x, x_off, x_inv) of the next insertion.
  */
 int mpm_merge(const void* x, const int32_t* x_off, const float* x_inv, int32_t B, int32_t N, int32_t D, int32_t dt,

@@ -77,8 +77,11 @@ def new_workspace(B: int, N: int, device) -> torch.Tensor:
 
 
 def _workspace(B, N, device, ws=None):
-    if ws is None or ws.numel() < workspace_bytes(B, N):
-        ws = new_workspace(B, N, device)
+    """``ws``, or a new workspace if it is missing or too small. A new one need not be
+    cleared: the affinity launch of every call clears what its compaction counts in."""
+    need = workspace_bytes(B, N)
+    if ws is None or ws.numel() < need:
+        ws = torch.empty((need,), dtype=torch.uint8, device=device)
     return ws
 
 
@@ -358,9 +361,7 @@ def _run_fused(x, insertions, workspaces, schedule, grid_w, window, block_rows, 
     need = workspace_bytes(B, N)
     stages, ptrs = [], []
     for s in range(insertions):
-        ws = None if workspaces is None else workspaces[s]
-        if ws is None or ws.numel() < need:
-            ws = new_workspace(B, N, dev)
+        ws = _workspace(B, N, dev, None if workspaces is None else workspaces[s])
         inv = norms and s + 1 < insertions
         m = Merged(torch.empty((B * N, D), dtype=x.dtype, device=dev), torch.empty((B + 1,), dtype=torch.int32, device=dev),
                    torch.empty((B, N), dtype=torch.int32, device=dev), ws, B, N,

@@ -235,7 +235,8 @@ template <class S, int WC, int WQ, int MT, int NT, bool SYM, bool HALVES, bool L
           bool COUNTED>
 __global__ __launch_bounds__(WC * WQ * kWave, 2) void affinity_partial_kernel(  // 2 waves per SIMD
     const uint8_t* __restrict__ x, const int32_t* __restrict__ x_off, int B, int N, int D, int T, int log_xcds,
-    int slots, WorkShape shape, float* __restrict__ pv, int32_t* __restrict__ pi, const float* __restrict__ xinv, Window win)
+    int slots, WorkShape shape, float* __restrict__ pv, int32_t* __restrict__ pi, const float* __restrict__ xinv, Window win,
+    Clear clear)
 {
     constexpr int THREADS = WC * WQ * kWave;
     constexpr int WAVES = WC * WQ;
@@ -272,6 +273,9 @@ __global__ __launch_bounds__(WC * WQ * kWave, 2) void affinity_partial_kernel(  
     constexpr bool given = GIVEN;
 
     const int tid = threadIdx.x;
+    // The words the compaction counts in start at zero, whatever the workspace held.
+    if (!HALVES && blockIdx.x == 0)
+        for (int k = tid; k < clear.words; k += THREADS) clear.p[k] = 0;
     const int lane = tid & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);  // wave-uniform: scalar registers and branches
     const int wc = wave % WC;
@@ -999,6 +1003,7 @@ struct AffinityArgs {
     hipStream_t stream;
     hipEvent_t start, stop;
     Window win;
+    Clear clear;
 };
 
 template <class S, int WC, int WQ, int MT, int NT, bool SYM, bool LOCAL, bool GIVEN, bool TAIL, bool COUNTED>
@@ -1014,12 +1019,12 @@ void launch_counted(const AffinityArgs& a, int slots, const WorkShape& shape)
     const bool halves = SPLIT && defers_diagonals(COUNTED, a.B, a.N, log_xcds, slots);
     hipExtLaunchKernelGGL((affinity_partial_kernel<S, WC, WQ, MT, NT, SYM, false, LOCAL, GIVEN, TAIL, COUNTED>), grid,
                           block, 0, a.stream, a.start, halves ? nullptr : a.stop, 0, xb, a.x_off, a.B, a.N, a.D, a.T,
-                          log_xcds, slots, shape, a.pv, a.pi, a.xinv, a.win);
+                          log_xcds, slots, shape, a.pv, a.pi, a.xinv, a.win, a.clear);
     if constexpr (SPLIT) {
         if (halves)
             hipExtLaunchKernelGGL((affinity_partial_kernel<S, WC, WQ, MT, NT / 2, false, true, false, GIVEN, TAIL, COUNTED>),
                                   grid, block, 0, a.stream, nullptr, a.stop, 0, xb, a.x_off, a.B, a.N, a.D, a.T,
-                                  log_xcds, slots, shape, a.pv, a.pi, a.xinv, a.win);
+                                  log_xcds, slots, shape, a.pv, a.pi, a.xinv, a.win, Clear{});
     }
 }
 
@@ -1280,7 +1285,8 @@ hipError_t affinity_schedule(int B, int N, int D, int dt, int schedule, int* use
 }
 
 hipError_t launch_affinity(const void* x, const int32_t* x_off, int B, int N, int D, int dt, int schedule, float* pv,
-                           int32_t* pi, hipStream_t stream, hipEvent_t start, hipEvent_t stop, const float* xinv)
+                           int32_t* pi, hipStream_t stream, hipEvent_t start, hipEvent_t stop, const float* xinv,
+                           Clear clear)
 {
     const int T = partial_tiles(N);
     if (xinv && !affinity_takes_norms(D, dt)) return hipErrorInvalidValue;  // those kernels sum their own norms
@@ -1288,7 +1294,7 @@ hipError_t launch_affinity(const void* x, const int32_t* x_off, int B, int N, in
     if (cus <= 0) return hipErrorInvalidDevice;
     const int xcds = cus % kXcds == 0 ? kXcds : 1;
     const AffinityArgs a{x, x_off, dt == kBf16 ? xinv : nullptr, B, N, D, T, xcds, pv, pi, stream, start, stop,
-                         Window{nullptr, FixedDiv(1), 0}};
+                         Window{nullptr, FixedDiv(1), 0}, clear};
     switch (pick_blocks(B, N, D, dt, schedule, x_off != nullptr)) {
     case kBlocks64: launch_persistent<kTWC, kTWQ, kTMT, kTNT, false>(dt, a, cus * kTWGS); break;
     case kBlocks128: launch_persistent<kLWC, kLWQ, kLMT, kLNT, true>(dt, a, cus * kLWGS); break;
@@ -1301,7 +1307,7 @@ hipError_t launch_affinity(const void* x, const int32_t* x_off, int B, int N, in
 hipError_t launch_affinity_local(const void* x, const int32_t* x_off, const float* xinv, const int32_t* pos,
                                  int grid_w, int radius, int block_rows,
                                  int B, int N, int D, int dt, float* pv, int32_t* pi, hipStream_t stream,
-                                 hipEvent_t start, hipEvent_t stop)
+                                 hipEvent_t start, hipEvent_t stop, Clear clear)
 {
     // The persistent kernel on the symmetric schedule, one item per query block and the
     // tiles of its band from its own on (given norms: bf16 only), with blocks of block_rows.
@@ -1310,7 +1316,7 @@ hipError_t launch_affinity_local(const void* x, const int32_t* x_off, const floa
     if (cus <= 0) return hipErrorInvalidDevice;
     const int xcds = cus % kXcds == 0 ? kXcds : 1;
     const AffinityArgs a{x, x_off, dt == kBf16 ? xinv : nullptr, B, N, D, T, xcds, pv, pi, stream, start, stop,
-                         Window{pos, FixedDiv((uint32_t)grid_w), radius}};
+                         Window{pos, FixedDiv((uint32_t)grid_w), radius}, clear};
     if (block_rows == kLCT) launch_persistent<kLWC, kLWQ, kLMT, kLNT, true, true>(dt, a, cus * kLWGS);
     else launch_persistent<kSWC, kSWQ, kSMT, kSNT, true, true>(dt, a, cus * kPWGS);
     return hipGetLastError();

@@ -282,7 +282,8 @@ hipError_t affinity_compact(const void* x, const int32_t* x_off, const float* x_
                             int32_t D, int32_t dt, int32_t schedule, int32_t* map, int32_t* y_off,
                             const Workspace& w, hipEvent_t start, hipEvent_t stop, hipStream_t st)
 {
-    hipError_t e = mpm::launch_affinity(x, x_off, B, N, D, dt, schedule, w.pv, w.pi, st, start, stop, x_inv);
+    hipError_t e = mpm::launch_affinity(x, x_off, B, N, D, dt, schedule, w.pv, w.pi, st, start, stop, x_inv,
+                                        mpm::compact_clears(B, y_off, w.sync));
     if (e == hipSuccess) e = compact_from_partials(w, x_off, B, N, D, dt, schedule, map, y_off, st);
     return e;
 }
@@ -383,7 +384,7 @@ int mpm_affinity(const void* x, const int32_t* x_off, const float* x_inv, int32_
     MPM_DATA_CHECK(checked_rows(x, x_off, x_inv, nullptr, 1, B, N, D, dt, as_stream(stream)));
     return hip_status(mpm::launch_affinity(x, x_off, B, N, D, dt, schedule, w.pv, w.pi, as_stream(stream),
                                            static_cast<hipEvent_t>(start_event), static_cast<hipEvent_t>(stop_event),
-                                           x_inv));
+                                           x_inv, mpm::Clear{}));
 }
 
 int mpm_affinity_compact(const void* x, const int32_t* x_off, const float* x_inv, int32_t B, int32_t N, int32_t D,
@@ -449,7 +450,8 @@ int mpm_argmax(const void* x, const int32_t* x_off, int32_t B, int32_t N, int32_
     MPM_LAUNCH_GATE();
     MPM_DATA_CHECK(checked_rows(x, x_off, nullptr, nullptr, 1, B, N, D, dt, as_stream(stream)));
     const hipStream_t st = as_stream(stream);
-    hipError_t e = mpm::launch_affinity(x, x_off, B, N, D, dt, schedule, w.pv, w.pi, st, nullptr, nullptr, nullptr);
+    hipError_t e = mpm::launch_affinity(x, x_off, B, N, D, dt, schedule, w.pv, w.pi, st, nullptr, nullptr, nullptr,
+                                        mpm::Clear{});
     if (e == hipSuccess)
         e = mpm::launch_reduce_partials(w.pv, w.pi,
                                         mpm::partial_tile_width(B, D, dt, N, schedule, x_off != nullptr), x, x_off, B,
@@ -541,7 +543,7 @@ int mpm_merge_local(const void* x, const int32_t* x_off, const float* x_inv, con
     const int rows = mpm::local_tile_width(B, N, D, dt, grid_w, window, block_rows);
     hipError_t e = mpm::launch_affinity_local(x, x_off, x_inv, pos, grid_w, window, rows, B, N, D, dt, w.pv, w.pi, st,
                                               static_cast<hipEvent_t>(start_event),
-                                              static_cast<hipEvent_t>(stop_event));
+                                              static_cast<hipEvent_t>(stop_event), mpm::compact_clears(B, y_off, w.sync));
     if (e == hipSuccess)
         e = compact_partials_ct(w, x_off, B, N, D, dt, rows, map, y_off, st);
     if (e == hipSuccess)
@@ -590,7 +592,7 @@ int mpm_run_schedule(const void* x, int32_t B, int32_t N, int32_t D, int32_t dt,
         if (local) {
             const int rows = mpm::local_tile_width(B, N, D, dt, grid_w, window, block_rows);
             e = mpm::launch_affinity_local(cur, off, inv, pos, grid_w, window, rows, B, N, D, dt, w[k].pv, w[k].pi, st,
-                                           nullptr, nullptr);
+                                           nullptr, nullptr, mpm::compact_clears(B, m.y_off, w[k].sync));
             if (e == hipSuccess) e = compact_partials_ct(w[k], off, B, N, D, dt, rows, m.map, m.y_off, st);
         } else {
             e = affinity_compact(cur, off, inv, B, N, D, dt, schedule, m.map, m.y_off, w[k], nullptr, nullptr, st);

@@ -13,13 +13,22 @@ enum Dtype : int { kF32 = 0, kBf16 = 1 };
 enum AffinitySchedule : int { kScheduleAuto = 0, kScheduleFull = 1, kScheduleSymmetric = 2, kScheduleFull64 = 3 };
 bool valid_schedule(int schedule);
 
+// Device words an affinity launch sets to zero for the compaction that follows it.
+struct Clear {
+    int32_t* p = nullptr;
+    int words = 0;
+};
+// Those of a batch of B images with offsets y_off and arrival counters sync.
+Clear compact_clears(int B, int32_t* y_off, int32_t* sync);
+
 // Affinity + per-candidate-tile argmax partials: pv/pi are [B][partial_tiles(N)][N].
 // start/stop (may be null) are bound to the first and last of its dispatches (hipExtLaunchKernel).
 // xinv (may be null): given inverse row norms, one float per row of x (packed like x); the
 // kernels then do not sum the norms themselves. Only where affinity_takes_norms(D, dt)
 // (hipErrorInvalidValue otherwise).
 hipError_t launch_affinity(const void* x, const int32_t* x_off, int B, int N, int D, int dt, int schedule, float* pv,
-                           int32_t* pi, hipStream_t stream, hipEvent_t start, hipEvent_t stop, const float* xinv);
+                           int32_t* pi, hipStream_t stream, hipEvent_t start, hipEvent_t stop, const float* xinv,
+                           Clear clear);
 // Whether launch_affinity takes given inverse norms for rows of D values of dtype dt
 // (bfloat16 rows a whole number of 64 bytes: the persistent kernels).
 bool affinity_takes_norms(int D, int dt);
@@ -43,8 +52,8 @@ hipError_t affinity_schedule(int B, int N, int D, int dt, int schedule, int* use
 hipError_t launch_reduce_partials(const float* pv, const int32_t* pi, int ct, const void* x, const int32_t* x_off,
                                   int B, int N, int D, int dt, int32_t* nb, float* best, hipStream_t stream);
 // Compaction (map, src, offsets) from the partials (reduced first) or from nb. sync (may be
-// null): the workspace's arrival counters, zero on entry and exit; with them the last
-// image's workgroup scans the offsets, without them a second launch does.
+// null): the workspace's arrival counters; with them the one launch does the offsets too, and
+// the words of compact_clears must be zero on entry; without them a second launch does.
 hipError_t launch_pair_compact_partials(const float* pv, const int32_t* pi, int T, int ct, int32_t* nb,
                                         const int32_t* x_off, int B, int N, int32_t* map, int32_t* src,
                                         int32_t* y_off, int32_t* sync, hipStream_t stream);
@@ -74,7 +83,7 @@ hipError_t launch_pair_average_scatter(const void* x, const int32_t* x_off, cons
 hipError_t launch_affinity_local(const void* x, const int32_t* x_off, const float* xinv, const int32_t* pos,
                                  int grid_w, int radius, int block_rows,
                                  int B, int N, int D, int dt, float* pv, int32_t* pi, hipStream_t stream,
-                                 hipEvent_t start, hipEvent_t stop);
+                                 hipEvent_t start, hipEvent_t stop, Clear clear);
 
 // Padded batch layout: packed rows (offsets z_off) to [B][P] rows of rowbytes bytes, zero
 // rows past each image (unpad = false), or back to the packed layout (unpad = true).

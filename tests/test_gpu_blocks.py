@@ -152,3 +152,33 @@ def test_cosines_of_packed_rows(dtype, D):
         for i in (0, 1, 15, 16, 63, n // 2, n - 1):
             # float32 sums of D products and two float32 norms: below 3 (D + 4) 2^-24.
             assert abs(best[b, i] - oracle.cosine(x64, i, int(nb[b, i]))) <= 3 * (D + 4) * 2.0 ** -24
+
+
+# One image, the most whose counts are added to the offsets directly, one more.
+@pytest.mark.parametrize("B", [1, 2, 256, 257])
+def test_offsets_in_an_unprepared_workspace(B):
+    """Offsets, maps and sources of an insertion in a workspace and an offsets buffer that hold
+    anything, twice in a row, equal those of the neighbours' own compaction (whose offsets are
+    a second launch); some images empty."""
+    from paper_2604_05718_amd import _lib, api
+
+    rng = np.random.default_rng(B)
+    ns = [int(n) for n in rng.integers(0, 70, B)]
+    ns[0], ns[-1], N = 70, 70, 70
+    print(f"offsets B={B}", flush=True)
+    x = store(clustered(rng, sum(ns), 32, k=300), "bf16").to(DEV)
+    off = torch.from_numpy(np.concatenate([[0], np.cumsum(ns)]).astype(np.int32)).to(DEV)
+    want = mpm.pair_compact(mpm.argmax(x, off, N=N), x_off=off)
+    ws = torch.full((mpm.workspace_bytes(B, N),), 0xA5, dtype=torch.uint8, device=DEV)
+    for _ in range(2):
+        m = torch.full((B, N), -9, dtype=torch.int32, device=DEV)
+        y_off = torch.full((B + 1,), 12345, dtype=torch.int32, device=DEV)
+        _lib.check("mpm_affinity_compact", _lib.load().mpm_affinity_compact(
+            api._p(x), api._p(off), None, B, N, 32, api._dt(x), 0, api._p(m), api._p(y_off), api._p(ws), ws.numel(), None,
+            None, api._stream()))
+        torch.cuda.synchronize()
+        assert torch.equal(y_off, want[2]) and torch.equal(m, want[0])
+        src = api.ws_view(ws, B, N, "src")
+        for b in (0, B // 2, B - 1):
+            c = int(y_off[b + 1] - y_off[b])
+            assert torch.equal(src[b, :c], want[1][b, :c])
