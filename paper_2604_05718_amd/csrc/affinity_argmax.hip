@@ -126,6 +126,19 @@ __device__ __forceinline__ float half_sum(float x)
     const auto s = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
     return __uint_as_float(s[0]) + __uint_as_float(s[1]);
 }
+// The larger values (of finite or infinite ones; a NaN loses).
+__device__ __forceinline__ float max_of(float a, float b)
+{
+    float r;
+    asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+__device__ __forceinline__ float max_of(float a, float b, float c)
+{
+    float r;
+    asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+    return r;
+}
 // (v, i) = the lexicographic maximum of (av, ai) and (bv, bi): larger score, then
 // smaller index (as unsigned, so -1 loses every tie). Branch-free.
 __device__ __forceinline__ void merge_pair(float& v, int32_t& i, float av, int32_t ai, float bv, int32_t bi)
@@ -687,10 +700,13 @@ __global__ __launch_bounds__(WC * WQ * kWave, 2) void affinity_partial_kernel(  
         const bool diag = ci.qbase >= cb && ci.qbase < cb + CT;
         const int self_tile0 = (ci.qbase - cb) / 32;
         // Accumulator element r = 4g+e of this lane is candidate row 8g + 4*khalf + e of
-        // its 32-row tile, so rows ascend with r. Each 16-value group is reduced by a
-        // tournament in which the left (lower) entry wins ties, then merged into the
-        // running best in ascending tile order with a strict >: the lowest index
-        // wins among equal scores, as in a left-to-right scan.
+        // its 32-row tile, so rows ascend with r. The 32 values of two tiles are reduced together:
+        // first their maximum, by value alone (two to three values an instruction), then the
+        // first value equal to it, so the lowest index wins among equal scores; pairs of tiles
+        // are merged into the running best in ascending order with a strict >. A tournament that
+        // carried an index through every comparison took a compare and two selects a value and
+        // waited for most of its compares: whole schedules were 1.4 to 2.4% slower with it, the
+        // neighbour query of 16 images of 1024 768-byte rows 3.8%.
         float bv[NT];
         int32_t bi[NT];
 #pragma unroll
@@ -731,36 +747,39 @@ __global__ __launch_bounds__(WC * WQ * kWave, 2) void affinity_partial_kernel(  
                         }
                 }
         }
+        // Candidate tiles reduced together (one where the window's state leaves no registers for two).
+        constexpr int MP = MT >= 2 && !(LOCAL && MT * NT >= 8) ? 2 : 1;
+        constexpr int SC = MP * 16, GR = SC / 4;
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt) {
-            if (mt >= mt_lim) break;
-            const int jt = cb + wc * MT * 32 + mt * 32 + 4 * khalf;  // candidate of r = 0
-            f32x4 ivv[4];
+        for (int mp = 0; mp < MT; mp += MP) {
+            if (mp >= mt_lim) break;
+            const int jt = cb + wc * MT * 32 + mp * 32 + 4 * khalf;  // candidate of r = 0
+            f32x4 ivv[4 * MP];
 #pragma unroll
-            for (int g = 0; g < 4; ++g)
-                ivv[g] = *reinterpret_cast<const f32x4*>(&iv[wc * MT * 32 + mt * 32 + 8 * g + 4 * khalf]);
-            const bool partial = cb + wc * MT * 32 + mt * 32 + 32 > n;  // some rows of this tile are past the image
+            for (int g = 0; g < 4 * MP; ++g)
+                ivv[g] = *reinterpret_cast<const f32x4*>(&iv[wc * MT * 32 + mp * 32 + 8 * g + 4 * khalf]);
+            const bool partial = cb + wc * MT * 32 + mp * 32 + MP * 32 > n;  // some rows of these tiles are past the image
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt) {
                 if (nt >= nt_lim) break;
-                float sc[16];
+                float sc[SC];
 #pragma unroll
-                for (int g = 0; g < 4; ++g)
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) sc[4 * g + e] = acc[mt][nt][4 * g + e] * ivv[g][e];
+                for (int r = 0; r < SC; ++r) sc[r] = acc[mp + r / 16][nt][r % 16] * ivv[r / 4][r % 4];
                 if (partial) {
 #pragma unroll
-                    for (int r = 0; r < 16; ++r)
-                        sc[r] = jt + 8 * (r >> 2) + (r & 3) < n ? sc[r] : -__builtin_inff();
+                    for (int r = 0; r < SC; ++r) sc[r] = jt + 8 * (r >> 2) + (r & 3) < n ? sc[r] : -__builtin_inff();
                 }
-                if (diag && wc * MT + mt == self_tile0 + wq * NT + nt) {  // the tile holding each lane's own query
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) sc[r] = r == self_r ? -__builtin_inff() : sc[r];
+                for (int m = 0; m < MP; ++m) {
+                    if (diag && wc * MT + mp + m == self_tile0 + wq * NT + nt) {  // the tile holding each lane's own query
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) sc[16 * m + r] = r == self_r ? -__builtin_inff() : sc[16 * m + r];
+                    }
                 }
                 if constexpr (LOCAL && !SYM) {
 #pragma unroll
-                    for (int g = 0; g < 4; ++g) {
-                        const int jl = wc * MT * 32 + mt * 32 + 8 * g + 4 * khalf;
+                    for (int g = 0; g < GR; ++g) {
+                        const int jl = wc * MT * 32 + mp * 32 + 8 * g + 4 * khalf;
                         const int4 cr = *reinterpret_cast<const int4*>(&win_rc[0][jl]);
                         const int4 cc = *reinterpret_cast<const int4*>(&win_rc[1][jl]);
                         const int crv[4] = {cr.x, cr.y, cr.z, cr.w}, ccv[4] = {cc.x, cc.y, cc.z, cc.w};
@@ -771,38 +790,34 @@ __global__ __launch_bounds__(WC * WQ * kWave, 2) void affinity_partial_kernel(  
                         }
                     }
                 }
-                float v8[8];
-                int r8[8];
+                // The best of each group of four, then of the groups, by value alone; then the first
+                // group that holds it and the first of its four.
+                float gm[GR];
 #pragma unroll
-                for (int k = 0; k < 8; ++k) {
-                    const bool c = sc[2 * k + 1] > sc[2 * k];
-                    v8[k] = c ? sc[2 * k + 1] : sc[2 * k];
-                    r8[k] = c ? 2 * k + 1 : 2 * k;
-                }
-                float v4[4];
-                int r4[4];
+                for (int k = 0; k < GR; ++k) gm[k] = max_of(max_of(sc[4 * k], sc[4 * k + 1], sc[4 * k + 2]), sc[4 * k + 3]);
+                float v1 = max_of(gm[0], gm[1], gm[2]);
 #pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    const bool c = v8[2 * k + 1] > v8[2 * k];
-                    v4[k] = c ? v8[2 * k + 1] : v8[2 * k];
-                    r4[k] = c ? r8[2 * k + 1] : r8[2 * k];
+                for (int k = 3; k + 1 < GR; k += 2) v1 = max_of(v1, gm[k], gm[k + 1]);
+                static_assert(GR % 2 == 0, "the last group alone");
+                v1 = max_of(v1, gm[GR - 1]);
+                float x[4] = {sc[SC - 4], sc[SC - 3], sc[SC - 2], sc[SC - 1]};
+                int r1 = SC - 4;
+#pragma unroll
+                for (int k = GR - 2; k >= 0; --k) {
+                    const bool c = gm[k] == v1;
+#pragma unroll
+                    for (int e = 0; e < 3; ++e) x[e] = c ? sc[4 * k + e] : x[e];
+                    r1 = c ? 4 * k : r1;
                 }
-                const bool c0 = v4[1] > v4[0];
-                const float v20 = c0 ? v4[1] : v4[0];
-                const int r20 = c0 ? r4[1] : r4[0];
-                const bool c1 = v4[3] > v4[2];
-                const float v21 = c1 ? v4[3] : v4[2];
-                const int r21 = c1 ? r4[3] : r4[2];
-                const bool cf = v21 > v20;
-                const float v1 = cf ? v21 : v20;
-                int r1 = cf ? r21 : r20;
+                const int e1 = x[0] == v1 ? 0 : x[1] == v1 ? 1 : x[2] == v1 ? 2 : 3;
+                r1 += e1;
                 // Materialise the winning index before the merge: otherwise the compiler moves
                 // the index selection into a divergent branch per tile, which serialises the
-                // tiles' tournaments (measured slower).
+                // tiles' reductions (measured slower).
                 asm volatile("" : "+v"(r1));
                 const bool up = v1 > bv[nt];
                 bv[nt] = up ? v1 : bv[nt];
-                bi[nt] = up ? jt + r1 + 4 * (r1 >> 2) : bi[nt];  // row 8*(r/4) + r%4 of the tile
+                bi[nt] = up ? jt + r1 + 4 * (r1 >> 2) : bi[nt];  // row 8*(r/4) + r%4 from the first tile's
             }
         }
         // Reverse direction of an off-diagonal item (query block before the candidate
