@@ -34,11 +34,11 @@ AFFINITY_REPS = 5    # such batches per insertion; the median is taken
 # HBM traffic of one affinity step (the whole-block launch and, where the schedule
 # defers diagonal blocks, the half-block launch; the two insertions averaged) from
 # rocprofv3 FETCH_SIZE / WRITE_SIZE runs on each workload, calibrated with a copy
-# kernel (profiles/<workload>_rocprof.md). Valid only for the kernel source it was
+# kernel (profiles/schedule_cases.md). Valid only for the kernel source it was
 # measured on, with the default schedule.
-TRAFFIC = {"source_sha256": "1dae8e815f91dc3ce104e116133adef4251abc9e32c244ab1520b8269f69403b",
-           "bytes_per_launch": {"vit_ti_512": 6556890, "vit_s_512": 25826025, "vit_b_512": 151433431,
-                                "vit_l_1024": 510617954, "stress_768": 182226447}}
+TRAFFIC = {"source_sha256": "9d65d811b35a8a66ad606ca51c7ceef13a8f8fa9c3b0bb881c336aa5329cc1bb",
+           "bytes_per_launch": {"vit_ti_512": 6523936, "vit_s_512": 27672064, "vit_b_512": 128419793,
+                                "vit_l_1024": 484617755, "stress_768": 134597907}}
 
 
 def log(*a):
