@@ -25,7 +25,8 @@ def tokens(B, N, D, dtype, seed):
 # pieces) and one more; images shorter than, at and past the rows of a workgroup; the least rows
 # that keep 8 lanes each, and fewer.
 CASES = [("bf16", 3, 33, 8), ("f32", 2, 40, 28), ("bf16", 5, 64, 64), ("bf16", 2, 257, 72), ("f32", 3, 90, 256),
-         ("bf16", 9, 130, 520), ("bf16", 8, 1030, 128), ("bf16", 7, 1000, 128), ("f32", 2, 19, 2048), ("bf16", 2, 21, 4104), ("bf16", 4, 1, 64), ("f32", 3, 2, 36)]
+         ("bf16", 9, 130, 520), ("bf16", 8, 1030, 128), ("bf16", 7, 1000, 128), ("f32", 2, 19, 2048),
+         ("bf16", 2, 21, 4104), ("bf16", 4, 1, 64), ("f32", 3, 2, 36)]
 
 
 @pytest.mark.parametrize("window", [None, 2])
