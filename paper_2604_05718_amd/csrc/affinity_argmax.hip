@@ -1247,8 +1247,8 @@ Blocks pick_blocks(int B, int N, int D, int dt, int schedule, bool packed)
         if (schedule == kScheduleFull64) return kBlocks64;
     }
     const int cus = std::max(1, device_cus());
-    auto blocks = [&](int w, WorkOrder order, int percent) {
-        return (double)B * work_items(order, (int)(((long)N * percent / 100 + w - 1) / w));
+    auto blocks = [&](int w, WorkOrder order, int percent) {  // of images of at least one token
+        return (double)B * work_items(order, (int)((std::max(1L, (long)N * percent / 100) + w - 1) / w));
     };
     const double capacity64 = blocks(kTCT, kOrderFull, 100);
     const double full256 = blocks(kPCT, kOrderFull, 100);

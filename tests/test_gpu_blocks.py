@@ -182,3 +182,14 @@ def test_offsets_in_an_unprepared_workspace(B):
         for b in (0, B // 2, B - 1):
             c = int(y_off[b + 1] - y_off[b])
             assert torch.equal(src[b, :c], want[1][b, :c])
+
+
+@pytest.mark.parametrize("D", [64, 1024])
+def test_packed_pick_of_the_shortest_images(D):
+    """A packed batch of images of one or two tokens runs the small blocks, as the dense one
+    does (its guessed lengths are at least one token)."""
+    for B in (1, 8, 31):
+        for N in (1, 2):
+            print(f"pick of short images B={B} N={N} D={D}", flush=True)
+            dense, packed = (mpm.affinity_block_rows(B, N, D, torch.bfloat16, packed=p) for p in (False, True))
+            assert dense == packed == 64
