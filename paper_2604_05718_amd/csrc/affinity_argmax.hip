@@ -86,6 +86,17 @@ struct Mfma<F32> {
 
 constexpr int kChunkBytes = 128;  // bytes of each row per LDS stage
 constexpr int kSplitRows = 256;   // block rows of the symmetric schedule that has a half-block launch
+// Fewest bfloat16 chunks of K from which a share of single-block images, fewer than half of its
+// slots, runs as half blocks only (float32 blocks: any): half of a round has to outweigh the
+// second launch. Neighbour queries of 1 to 128 images of at most 256 rows, whole / half blocks:
+// bfloat16 rows of 128 and 384 bytes 8 to 20% and 9% faster whole, of 768 bytes 13.9 / 15.7 us
+// (the other way round), of 2048 bytes 19.7 / 27.8; float32 rows of 3072 bytes 96 / 181 us.
+constexpr int kLoneSplitChunks = 6;
+template <class S>
+__host__ __device__ constexpr bool splits_lone(int nchunks)
+{
+    return S::kBytes == 4 || nchunks >= kLoneSplitChunks;
+}
 constexpr int kXcds = 8;  // MI355X: workgroups are dealt round-robin to 8 XCDs, each with its own L2
 
 // Workgroup barrier that waits only for this wave's LDS operations (not for
@@ -329,11 +340,12 @@ __global__ __launch_bounds__(WC * WQ * kWave, 2) void affinity_partial_kernel(  
     }
     const int group = blockIdx.x & ((1 << log_xcds) - 1);
     const int slot = blockIdx.x >> log_xcds;
-    const WorkShare share = work_share(counts, B, group, log_xcds, slots, SPLIT || HALVES);
-    const int nitems = HALVES ? 2 * share.ndef : share.cnt - share.ndef;
-    if (slot >= nitems) return;  // uniform over the workgroup
     const long rowbytes = (long)D * S::kBytes;
     const int nchunks = (int)((rowbytes + CB - 1) / CB);
+    const WorkShare share =
+        work_share(counts, B, group, log_xcds, slots, SPLIT || HALVES, !COUNTED && splits_lone<S>(nchunks));
+    const int nitems = HALVES ? 2 * share.ndef : share.cnt - share.ndef;
+    if (slot >= nitems) return;  // uniform over the workgroup
 
     // Item cursor; all fields are uniform over the workgroup.
     struct Item {
@@ -997,14 +1009,14 @@ int device_cus()
 
 // Whether a symmetric launch may defer diagonal blocks in any XCD group (images whose
 // lengths only the device knows: any may).
-bool defers_diagonals(bool counted, int B, int N, int log_xcds, int slots)
+bool defers_diagonals(bool counted, int B, int N, int log_xcds, int slots, bool lone)
 {
     if (counted) return true;
     const int nb = (N + kPCT - 1) / kPCT;
     const WorkShape shape(kOrderSymmetric, B, nb);
     const WorkCounts<false> counts{shape, nullptr, nullptr};
     for (int g = 0; g < 1 << log_xcds; ++g)
-        if (work_share(counts, B, g, log_xcds, slots, true).ndef > 0) return true;
+        if (work_share(counts, B, g, log_xcds, slots, true, lone).ndef > 0) return true;
     return false;
 }
 
@@ -1021,6 +1033,12 @@ struct AffinityArgs {
     Clear clear;
 };
 
+template <class S>
+constexpr int chunks_of(int D)
+{
+    return (int)(((long)D * S::kBytes + kChunkBytes - 1) / kChunkBytes);
+}
+
 template <class S, int WC, int WQ, int MT, int NT, bool SYM, bool LOCAL, bool GIVEN, bool TAIL, bool COUNTED>
 void launch_counted(const AffinityArgs& a, int slots, const WorkShape& shape)
 {
@@ -1031,7 +1049,7 @@ void launch_counted(const AffinityArgs& a, int slots, const WorkShape& shape)
     // The symmetric schedule's deferred diagonal blocks, as half blocks, in a second launch
     // (one item per slot); the timing events then span both.
     constexpr bool SPLIT = SYM && !LOCAL && WC * MT * 32 == kSplitRows;
-    const bool halves = SPLIT && defers_diagonals(COUNTED, a.B, a.N, log_xcds, slots);
+    const bool halves = SPLIT && defers_diagonals(COUNTED, a.B, a.N, log_xcds, slots, splits_lone<S>(chunks_of<S>(a.D)));
     hipExtLaunchKernelGGL((affinity_partial_kernel<S, WC, WQ, MT, NT, SYM, false, LOCAL, GIVEN, TAIL, COUNTED>), grid,
                           block, 0, a.stream, a.start, halves ? nullptr : a.stop, 0, xb, a.x_off, a.B, a.N, a.D, a.T,
                           log_xcds, slots, shape, a.pv, a.pi, a.xinv, a.win, a.clear);
@@ -1046,14 +1064,17 @@ void launch_counted(const AffinityArgs& a, int slots, const WorkShape& shape)
 template <class S, int WC, int WQ, int MT, int NT, bool SYM, bool LOCAL, bool GIVEN, bool TAIL>
 void launch_persistent_as(const AffinityArgs& a, int groups)
 {
-    // No more slots than a group can have items (images of N tokens), and no count of the
-    // images' own blocks when every item has its slot (the count costs each workgroup 0.8 us).
+    // No more slots than a group can have items (images of N tokens; two a diagonal block that
+    // may run as halves), and no count of the images' own blocks when every item has its slot
+    // (the count costs each workgroup 0.8 us).
     constexpr int CT = WC * MT * 32;
+    constexpr bool SPLIT = SYM && !LOCAL && CT == kSplitRows;
     constexpr WorkOrder ORDER = LOCAL ? kOrderBand : SYM ? kOrderSymmetric : kOrderFull;
     const int nb = (a.N + CT - 1) / CT;
     const long total = (long)a.B * work_items(ORDER, nb);
     const int most = groups / a.xcds;
-    const int slots = (int)std::min<long>(most, (total + a.xcds - 1) / a.xcds);
+    const long each = (total + a.xcds - 1) / a.xcds;
+    const int slots = (int)std::min<long>(most, SPLIT && splits_lone<S>(chunks_of<S>(a.D)) ? 2 * each : each);
     const WorkShape shape(ORDER, a.B, nb);
     if (a.x_off != nullptr && a.B <= kMaxCountedImages && total > (long)most * a.xcds)
         launch_counted<S, WC, WQ, MT, NT, SYM, LOCAL, GIVEN, TAIL, true>(a, slots, shape);

@@ -124,10 +124,11 @@ MPM_HD int work_diags_before(const WorkCounts<TAB>& c, int B, int p)
 }
 
 // Group g of 2^log_groups. When the share's items leave a last round of 0 < 2m <= slots
-// after at least one whole round, and it has at least m diagonal blocks, its last m are
-// deferred (`split`).
+// after at least one whole round (`lone`: or are m diagonal blocks and no more), and it has
+// at least m diagonal blocks, its last m are deferred (`split`).
 template <bool TAB>
-MPM_HD WorkShare work_share(const WorkCounts<TAB>& c, int B, int g, int log_groups, int slots, bool split)
+MPM_HD WorkShare work_share(const WorkCounts<TAB>& c, int B, int g, int log_groups, int slots, bool split,
+                            bool lone = false)
 {
     const int64_t total = c.items(B);
     WorkShare s;
@@ -136,7 +137,7 @@ MPM_HD WorkShare work_share(const WorkCounts<TAB>& c, int B, int g, int log_grou
     s.cnt = hi - s.lo;
     s.ndef = 0;
     s.dstart = 0;
-    if (split && s.cnt > slots) {
+    if (split && (lone || s.cnt > slots)) {
         const int m = s.cnt % slots;
         if (m > 0 && 2 * m <= slots) {
             const int dhi = work_diags_before(c, B, hi);

@@ -193,3 +193,24 @@ def test_packed_pick_of_the_shortest_images(D):
             print(f"pick of short images B={B} N={N} D={D}", flush=True)
             dense, packed = (mpm.affinity_block_rows(B, N, D, torch.bfloat16, packed=p) for p in (False, True))
             assert dense == packed == 64
+
+
+# Images of one 256-row block, fewer than half of the slots: whole blocks, or (float32, and
+# bfloat16 rows of at least six chunks) half blocks only; odd counts, 128 (halves on every
+# slot) and one more; rows that end inside a chunk cannot have the schedule forced.
+@pytest.mark.parametrize("dtype,B,N,D", [("f32", 7, 2, 768), ("f32", 128, 40, 32), ("f32", 129, 256, 48),
+                                         ("bf16", 5, 200, 768), ("bf16", 63, 130, 384), ("bf16", 64, 256, 320),
+                                         ("bf16", 128, 129, 416), ("f32", 1, 1, 64)])
+def test_single_block_images_on_the_symmetric_schedule(dtype, B, N, D):
+    """Neighbours and cosines, dense and packed, are those of the full schedule bit for bit."""
+    rng = np.random.default_rng(B * N + D)
+    print(f"single blocks {dtype} B={B} N={N} D={D}", flush=True)
+    x = torch.stack([store(clustered(rng, N, D), dtype) for _ in range(B)]).to(DEV)
+    off = torch.arange(0, (B + 1) * N, N, dtype=torch.int32, device=DEV)
+    nf, bf = mpm.argmax(x, with_best=True, schedule="full")
+    for args in (dict(), dict(x_off=off, N=N)):
+        nb, best = mpm.argmax(x.view(B * N, D) if args else x, with_best=True, schedule="symmetric", **args)
+        torch.cuda.synchronize()
+        assert torch.equal(nb, nf) and torch.equal(best.view(torch.int32), bf.view(torch.int32))
+    if N > 1:
+        check_nearest(to64(x[B // 2].cpu()), nf[B // 2].cpu().numpy())

@@ -112,15 +112,69 @@ int main()
 """
 
 
-def test_every_block_exactly_once(tmp_path):
+def _run(tmp_path, text):
+    """The driver's output (it counts the batches it checked)."""
     if shutil.which("g++") is None:
         pytest.skip("no host compiler")
     src = tmp_path / "work.cpp"
-    src.write_text(DRIVER)
+    src.write_text(text)
     exe = tmp_path / "work"
     csrc = os.path.join(ROOT, "paper_2604_05718_amd", "csrc")
     subprocess.run(["g++", "-O1", "-std=c++17", "-Wall", "-Werror", "-fsanitize=undefined,address", "-I", csrc,
                     str(src), "-o", str(exe)], check=True)
     r = subprocess.run([str(exe)], capture_output=True, text=True)
     assert r.returncode == 0, r.stdout + r.stderr
-    assert int(r.stdout) > 1000
+    return int(r.stdout)
+
+
+def test_every_block_exactly_once(tmp_path):
+    assert _run(tmp_path, DRIVER) > 1000
+
+
+# Shares below one round of the slots: with `lone`, those of single-block images whose halves
+# all have a slot run as halves; no others.
+LONE_MAIN = r"""
+int main()
+{
+    for (int B = 1; B <= 70; ++B)
+        for (int nb : {1, 2, 3})
+            for (int slots : {1, 2, 5, 16, 32}) {
+                const WorkShape shape(kOrderSymmetric, B, nb);
+                const WorkCounts<false> c{shape, nullptr, nullptr};
+                std::map<std::tuple<int, int, int>, int> seen;
+                for (int g = 0; g < 8; ++g) {
+                    const WorkShare s = work_share(c, B, g, 3, slots, true, true);
+                    const WorkShare t = work_share(c, B, g, 3, slots, true, false);
+                    const int m = s.cnt % slots;
+                    const int diags = work_diags_before(c, B, s.lo + s.cnt) - work_diags_before(c, B, s.lo);
+                    const bool defers = m > 0 && 2 * m <= slots && diags >= m;
+                    if (s.ndef != (defers ? m : 0) || t.ndef != (defers && s.cnt > slots ? m : 0)) {
+                        std::printf("B=%d nb=%d slots=%d", B, nb, slots);
+                        return 1;
+                    }
+                    if (s.cnt < slots && s.ndef && s.ndef != s.cnt) { std::printf("a part"); return 1; }
+                    for (int r = 0; r < s.cnt - s.ndef; ++r) {
+                        const WorkBlock k = work_block<kOrderSymmetric, true>(c, s, r, 0);
+                        ++seen[{k.b, k.q, k.t}];
+                    }
+                    for (int e = 0; e < s.ndef; ++e) {
+                        const WorkBlock k = work_deferred(c, B, s, e);
+                        if (k.q != k.t) { std::printf("off the diagonal"); return 1; }
+                        ++seen[{k.b, k.q, k.t}];
+                    }
+                }
+                if ((int)seen.size() != B * nb * (nb + 1) / 2) { std::printf("%zu blocks", seen.size()); return 1; }
+                for (auto& e : seen)
+                    if (e.second != 1) { std::printf("taken twice"); return 1; }
+                ++shapes;
+            }
+    std::printf("%ld", shapes);
+    return 0;
+}
+"""
+
+
+def test_lone_diagonals_are_deferred_once(tmp_path):
+    # The driver's batch checks stay in the program, unused.
+    head = DRIVER[:DRIVER.index("int main()")].replace("static void", "[[maybe_unused]] static void")
+    assert _run(tmp_path, head + LONE_MAIN) == 70 * 3 * 5
