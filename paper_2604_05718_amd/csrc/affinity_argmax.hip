@@ -1260,18 +1260,20 @@ Blocks pick_blocks_f32(double blocks64, double blocks128, double sym256, double 
     return rounds128 <= rounds256 ? kBlocks128 : kBlocksSym256;
 }
 
-Blocks pick_blocks(int B, int N, int D, int dt, int schedule, bool packed)
+Blocks pick_blocks(int B, int N, int D, int dt, int schedule, bool packed, int device_cu_count)
 {
     if (whole_64(D, dt)) {
         if (schedule == kScheduleFull) return kBlocks256;
         if (schedule == kScheduleSymmetric) return kBlocksSym256;
         if (schedule == kScheduleFull64) return kBlocks64;
     }
-    const int cus = std::max(1, device_cus());
+    const int cus = std::max(1, device_cu_count);
     auto blocks = [&](int w, WorkOrder order, int percent) {  // of images of at least one token
         return (double)B * work_items(order, (int)((std::max(1L, (long)N * percent / 100) + w - 1) / w));
     };
     const double capacity64 = blocks(kTCT, kOrderFull, 100);
+    // A small block a CU is the fastest by every estimate below (host time of the smallest calls).
+    if (capacity64 <= cus) return kBlocks64;
     const double full256 = blocks(kPCT, kOrderFull, 100);
     const double c = std::ceil(2.0 * D / kChunkBytes);
     double b64 = capacity64, b128 = blocks(kLCT, kOrderSymmetric, 100), s256 = blocks(kPCT, kOrderSymmetric, 100);
@@ -1304,15 +1306,16 @@ int block_rows(Blocks k) { return k == kBlocks64 ? kTCT : k == kBlocks128 ? kLCT
 
 int partial_tile_width(int B, int D, int dt, int N, int schedule, bool packed)
 {
-    return block_rows(pick_blocks(B, N, D, dt, schedule, packed));
+    return block_rows(pick_blocks(B, N, D, dt, schedule, packed, device_cus()));
 }
 
 hipError_t affinity_schedule(int B, int N, int D, int dt, int schedule, int* used)
 {
     *used = kScheduleFull;
     if (!whole_64(D, dt)) return hipSuccess;  // no choice of schedule
-    if (device_cus() <= 0) return hipErrorInvalidDevice;
-    switch (pick_blocks(B, N, D, dt, schedule, false)) {
+    const int cus = device_cus();
+    if (cus <= 0) return hipErrorInvalidDevice;
+    switch (pick_blocks(B, N, D, dt, schedule, false, cus)) {
     case kBlocks64: *used = kScheduleFull64; break;
     case kBlocks256: *used = kScheduleFull; break;
     default: *used = kScheduleSymmetric; break;
@@ -1322,7 +1325,7 @@ hipError_t affinity_schedule(int B, int N, int D, int dt, int schedule, int* use
 
 hipError_t launch_affinity(const void* x, const int32_t* x_off, int B, int N, int D, int dt, int schedule, float* pv,
                            int32_t* pi, hipStream_t stream, hipEvent_t start, hipEvent_t stop, const float* xinv,
-                           Clear clear)
+                           Clear clear, int* tile_width)
 {
     const int T = partial_tiles(N);
     if (xinv && !affinity_takes_norms(D, dt)) return hipErrorInvalidValue;  // those kernels sum their own norms
@@ -1331,7 +1334,9 @@ hipError_t launch_affinity(const void* x, const int32_t* x_off, int B, int N, in
     const int xcds = cus % kXcds == 0 ? kXcds : 1;
     const AffinityArgs a{x, x_off, dt == kBf16 ? xinv : nullptr, B, N, D, T, xcds, pv, pi, stream, start, stop,
                          Window{nullptr, FixedDiv(1), 0}, clear};
-    switch (pick_blocks(B, N, D, dt, schedule, x_off != nullptr)) {
+    const Blocks blocks = pick_blocks(B, N, D, dt, schedule, x_off != nullptr, cus);
+    *tile_width = block_rows(blocks);
+    switch (blocks) {
     case kBlocks64: launch_persistent<kTWC, kTWQ, kTMT, kTNT, false>(dt, a, cus * kTWGS); break;
     case kBlocks128: launch_persistent<kLWC, kLWQ, kLMT, kLNT, true>(dt, a, cus * kLWGS); break;
     case kBlocksSym256: launch_persistent<kSWC, kSWQ, kSMT, kSNT, true>(dt, a, cus * kPWGS); break;

@@ -270,21 +270,15 @@ hipError_t compact_partials_ct(const Workspace& w, const int32_t* x_off, int32_t
     return e;
 }
 
-hipError_t compact_from_partials(const Workspace& w, const int32_t* x_off, int32_t B, int32_t N, int32_t D,
-                                 int32_t dt, int32_t schedule, int32_t* map, int32_t* y_off, hipStream_t st)
-{
-    return compact_partials_ct(w, x_off, B, N, D, dt, mpm::partial_tile_width(B, D, dt, N, schedule, x_off != nullptr), map,
-                               y_off, st);
-}
-
 // One insertion's affinity (events bound to its launches) and compaction into the carved workspace.
 hipError_t affinity_compact(const void* x, const int32_t* x_off, const float* x_inv, int32_t B, int32_t N,
                             int32_t D, int32_t dt, int32_t schedule, int32_t* map, int32_t* y_off,
                             const Workspace& w, hipEvent_t start, hipEvent_t stop, hipStream_t st)
 {
+    int ct = 0;
     hipError_t e = mpm::launch_affinity(x, x_off, B, N, D, dt, schedule, w.pv, w.pi, st, start, stop, x_inv,
-                                        mpm::compact_clears(B, y_off, w.sync));
-    if (e == hipSuccess) e = compact_from_partials(w, x_off, B, N, D, dt, schedule, map, y_off, st);
+                                        mpm::compact_clears(B, y_off, w.sync), &ct);
+    if (e == hipSuccess) e = compact_partials_ct(w, x_off, B, N, D, dt, ct, map, y_off, st);
     return e;
 }
 
@@ -382,9 +376,10 @@ int mpm_affinity(const void* x, const int32_t* x_off, const float* x_inv, int32_
     if ((s = carve(ws, ws_bytes, B, N, &w)) != MPM_OK) return s;
     MPM_LAUNCH_GATE();
     MPM_DATA_CHECK(checked_rows(x, x_off, x_inv, nullptr, 1, B, N, D, dt, as_stream(stream)));
+    int ct = 0;
     return hip_status(mpm::launch_affinity(x, x_off, B, N, D, dt, schedule, w.pv, w.pi, as_stream(stream),
                                            static_cast<hipEvent_t>(start_event), static_cast<hipEvent_t>(stop_event),
-                                           x_inv, mpm::Clear{}));
+                                           x_inv, mpm::Clear{}, &ct));
 }
 
 int mpm_affinity_compact(const void* x, const int32_t* x_off, const float* x_inv, int32_t B, int32_t N, int32_t D,
@@ -450,12 +445,10 @@ int mpm_argmax(const void* x, const int32_t* x_off, int32_t B, int32_t N, int32_
     MPM_LAUNCH_GATE();
     MPM_DATA_CHECK(checked_rows(x, x_off, nullptr, nullptr, 1, B, N, D, dt, as_stream(stream)));
     const hipStream_t st = as_stream(stream);
+    int ct = 0;
     hipError_t e = mpm::launch_affinity(x, x_off, B, N, D, dt, schedule, w.pv, w.pi, st, nullptr, nullptr, nullptr,
-                                        mpm::Clear{});
-    if (e == hipSuccess)
-        e = mpm::launch_reduce_partials(w.pv, w.pi,
-                                        mpm::partial_tile_width(B, D, dt, N, schedule, x_off != nullptr), x, x_off, B,
-                                        N, D, dt, nb, best, st);
+                                        mpm::Clear{}, &ct);
+    if (e == hipSuccess) e = mpm::launch_reduce_partials(w.pv, w.pi, ct, x, x_off, B, N, D, dt, nb, best, st);
     return hip_status(e);
 }
 

@@ -25,17 +25,19 @@ Clear compact_clears(int B, int32_t* y_off, int32_t* sync);
 // start/stop (may be null) are bound to the first and last of its dispatches (hipExtLaunchKernel).
 // xinv (may be null): given inverse row norms, one float per row of x (packed like x); the
 // kernels then do not sum the norms themselves. Only where affinity_takes_norms(D, dt)
-// (hipErrorInvalidValue otherwise).
+// (hipErrorInvalidValue otherwise). *tile_width receives the candidate rows covered by one
+// partial of the blocks it picked (one pick a call: the pick and its device queries are host
+// time that small calls wait for).
 hipError_t launch_affinity(const void* x, const int32_t* x_off, int B, int N, int D, int dt, int schedule, float* pv,
                            int32_t* pi, hipStream_t stream, hipEvent_t start, hipEvent_t stop, const float* xinv,
-                           Clear clear);
+                           Clear clear, int* tile_width);
 // Whether launch_affinity takes given inverse norms for rows of D values of dtype dt
 // (bfloat16 rows a whole number of 64 bytes: the persistent kernels).
 bool affinity_takes_norms(int D, int dt);
 // Partial slots per token in the workspace (the tile stride of pv/pi): ceil(N / 64).
 int partial_tiles(int N);
-// Candidate rows covered by one partial of the blocks launch_affinity picks for this call
-// (packed: with offsets).
+// Candidate rows covered by one partial of the blocks launch_affinity picks for a call of this
+// shape (packed: with offsets), for reporting.
 int partial_tile_width(int B, int D, int dt, int N, int schedule, bool packed);
 // ... and of launch_affinity_local's kernel: the rows of its square blocks on the
 // persistent kernel's symmetric schedule (`requested`, 128 or 256; 0: whichever an
