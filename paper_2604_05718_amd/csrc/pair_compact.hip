@@ -277,14 +277,25 @@ __global__ __launch_bounds__(256) void reduce_partials_kernel(const float* __res
     nb[g] = j;
 }
 
+// Lanes a row of the reduction with cosines, by the row's 16-byte pieces: sixteen leave most
+// lanes of a narrow row without a piece, one reads a wide row line by line. 1 / 4 / 16 lanes on
+// 2000 images of 1024 rows of 16 bytes 19.5 / 53.6 / 159 us, of 64 bytes 30.8 / 54.0 / 157, of
+// 128 bytes 76.7 / 59.8 / 169, of 384 bytes 258 / 153 / 212; 64 images of 512-byte rows
+// - / 7.3 / 8.8, 16 of 768-byte rows - / 5.2 / 4.0.
+constexpr int kBestLanes = 16, kFewLanes = 4;
+constexpr int kThreadPieces = 4, kFewPieces = 32;
+// Workgroups at most; a larger batch's rows are taken in turn, so that rows past their image's
+// end cost a test and no workgroup each (1380 images of at most 3487 rows, a twentieth of them
+// filled, on 16 lanes: 136 us with a workgroup for each 16 rows, 88 with these, 96 with 4096).
+constexpr long kBestGroups = 1L << 14;
+
 // The same reduction with the cosine of the chosen pair: the score divided by the query's own
-// norm. Sixteen lanes take a row: lane l its partial tiles l, l + 16, ... and its 16-byte
-// pieces l, l + 16, ..., four of them in flight; a butterfly over the 16 lanes merges the
-// partials and adds the squares. One thread a row read the rows one line per lane, a piece
-// at a time: 12.0 us on 16 images of 1024 768-byte rows (12.6 MB), 4.0 us so.
-constexpr int kBestLanes = 16;
-constexpr int kBestRows = 256 / kBestLanes;
-template <class S>
+// norm. LANES lanes take a row: lane l its partial tiles l, l + LANES, ... and its 16-byte
+// pieces l, l + LANES, ..., four of either in flight; a butterfly over the lanes merges the
+// partials and adds the squares. Bound by memory: one thread a row read long rows one line per
+// lane, a piece at a time: 12.0 us on 16 images of 1024 768-byte rows (12.6 MB), 4.0 us on 16
+// lanes.
+template <class S, int LANES>
 __global__ __launch_bounds__(256) void reduce_best_kernel(const float* __restrict__ pv,
                                                           const int32_t* __restrict__ pi,
                                                           const uint8_t* __restrict__ x,
@@ -292,9 +303,10 @@ __global__ __launch_bounds__(256) void reduce_best_kernel(const float* __restric
                                                           int T, int ct, int32_t* __restrict__ nb,
                                                           float* __restrict__ best)
 {
-    const int lane = threadIdx.x % kBestLanes;
-    for (long g = (long)blockIdx.x * kBestRows + threadIdx.x / kBestLanes; g < (long)B * N;
-         g += (long)gridDim.x * kBestRows) {
+    constexpr int ROWS = 256 / LANES;
+    constexpr int TILES = LANES >= 16 ? 1 : 4;  // partial tiles a lane loads together
+    const int lane = threadIdx.x % LANES;
+    for (long g = (long)blockIdx.x * ROWS + threadIdx.x / LANES; g < (long)B * N; g += (long)gridDim.x * ROWS) {
         const int b = (int)(g / N);
         const int i = (int)(g - (long)b * N);
         const int row0 = x_off ? x_off[b] : b * N;
@@ -303,30 +315,39 @@ __global__ __launch_bounds__(256) void reduce_best_kernel(const float* __restric
         const int tiles = (n + ct - 1) / ct;
         float v = -__builtin_inff();
         int32_t j = -1;
-        for (int t = lane; t < tiles; t += kBestLanes) {
-            const long o = ((long)b * T + t) * N + i;
-            const float ov = pv[o];
-            const int32_t oi = pi[o];
-            if (ov > v || (ov == v && (uint32_t)oi < (uint32_t)j)) {
-                v = ov;
-                j = oi;
+        for (int t0 = lane; t0 < tiles; t0 += TILES * LANES) {
+            float ov[TILES];
+            int32_t oi[TILES];
+#pragma unroll
+            for (int u = 0; u < TILES; ++u) {
+                const int t = t0 + u * LANES;
+                const long o = ((long)b * T + t) * N + i;
+                ov[u] = t < tiles ? pv[o] : -__builtin_inff();
+                oi[u] = t < tiles ? pi[o] : -1;
+            }
+#pragma unroll
+            for (int u = 0; u < TILES; ++u) {
+                if (ov[u] > v || (ov[u] == v && (uint32_t)oi[u] < (uint32_t)j)) {
+                    v = ov[u];
+                    j = oi[u];
+                }
             }
         }
         const int pieces = (int)((long)D * S::kBytes / 16);
         const uint8_t* xr = x + ((long)row0 + i) * ((long)D * S::kBytes);
         float t2 = 0.0f;
-        for (int c0 = lane; c0 < pieces; c0 += 4 * kBestLanes) {
+        for (int c0 = lane; c0 < pieces; c0 += 4 * LANES) {
             u32x4 w[4];
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
-                const int c = c0 + u * kBestLanes;
+                const int c = c0 + u * LANES;
                 w[u] = c < pieces ? load16(xr + 16 * c) : u32x4{0u, 0u, 0u, 0u};
             }
 #pragma unroll
             for (int u = 0; u < 4; ++u) t2 = sumsq16(w[u], t2, S{});
         }
 #pragma unroll
-        for (int o = kBestLanes / 2; o > 0; o >>= 1) {
+        for (int o = LANES / 2; o > 0; o >>= 1) {
             const float ov = __shfl_xor(v, o);
             const int32_t oi = __shfl_xor(j, o);
             const bool c = ov > v || (ov == v && (uint32_t)oi < (uint32_t)j);
@@ -366,6 +387,23 @@ hipError_t launch_compact_t(const float* pv, const int32_t* pi, int T, int ct, i
     return hipGetLastError();
 }
 
+template <class S>
+void launch_best(int lanes, const float* pv, const int32_t* pi, const void* x, const int32_t* x_off, int B, int N, int D,
+                 int T, int ct, int32_t* nb, float* best, hipStream_t stream)
+{
+    const uint8_t* xp = static_cast<const uint8_t*>(x);
+    const long rows = 256 / lanes;
+    const dim3 grid((unsigned)std::min<long>(((long)B * N + rows - 1) / rows, kBestGroups)), block(256);
+    if (lanes == 1)
+        hipLaunchKernelGGL((reduce_best_kernel<S, 1>), grid, block, 0, stream, pv, pi, xp, x_off, B, N, D, T, ct, nb, best);
+    else if (lanes == kFewLanes)
+        hipLaunchKernelGGL((reduce_best_kernel<S, kFewLanes>), grid, block, 0, stream, pv, pi, xp, x_off, B, N, D, T, ct,
+                           nb, best);
+    else
+        hipLaunchKernelGGL((reduce_best_kernel<S, kBestLanes>), grid, block, 0, stream, pv, pi, xp, x_off, B, N, D, T, ct,
+                           nb, best);
+}
+
 }  // namespace
 
 Clear compact_clears(int B, int32_t* y_off, int32_t* sync)
@@ -397,15 +435,10 @@ hipError_t launch_reduce_partials(const float* pv, const int32_t* pi, int ct, co
                            x_off, B, N, T, ct, nb);
         return hipGetLastError();
     }
-    // A launch holds fewer than 2^32 threads; larger batches take the rows in turn.
-    const dim3 grid((unsigned)std::min<long>((total + kBestRows - 1) / kBestRows, 1L << 20));
-    const uint8_t* xp = static_cast<const uint8_t*>(x);
-    if (dt == kBf16)
-        hipLaunchKernelGGL(reduce_best_kernel<Bf16>, grid, dim3(256), 0, stream, pv, pi, xp, x_off, B, N, D, T, ct, nb,
-                           best);
-    else
-        hipLaunchKernelGGL(reduce_best_kernel<F32>, grid, dim3(256), 0, stream, pv, pi, xp, x_off, B, N, D, T, ct, nb,
-                           best);
+    const int pieces = D * (dt == kBf16 ? 2 : 4) / 16;
+    const int lanes = pieces <= kThreadPieces ? 1 : pieces <= kFewPieces ? kFewLanes : kBestLanes;
+    if (dt == kBf16) launch_best<Bf16>(lanes, pv, pi, x, x_off, B, N, D, T, ct, nb, best, stream);
+    else launch_best<F32>(lanes, pv, pi, x, x_off, B, N, D, T, ct, nb, best, stream);
     return hipGetLastError();
 }
 

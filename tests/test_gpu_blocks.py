@@ -214,3 +214,32 @@ def test_single_block_images_on_the_symmetric_schedule(dtype, B, N, D):
         assert torch.equal(nb, nf) and torch.equal(best.view(torch.int32), bf.view(torch.int32))
     if N > 1:
         check_nearest(to64(x[B // 2].cpu()), nf[B // 2].cpu().numpy())
+
+
+# Rows of one, four, five, 32 and 33 16-byte pieces (one, four and sixteen lanes a row), of
+# more and fewer partial tiles than the lanes take together; more rows than the launch has
+# lanes for (taken in turn), most of them past their image's end.
+@pytest.mark.parametrize("dtype,D,ns", [(dt, p * (8 if dt == "bf16" else 4), [1300, 0, 1, 65, 300])
+                                        for dt in ("bf16", "f32") for p in (1, 4, 5, 32, 33)] +
+                                       [("bf16", 8, [1500] + [3, 0, 1, 40] * 700), ("f32", 100, [2000] + [2, 0, 1] * 50)])
+def test_cosines_of_narrow_rows(dtype, D, ns):
+    rng = np.random.default_rng(D + len(ns))
+    print(f"cosines of narrow rows {dtype} D={D} images {len(ns)}", flush=True)
+    x = torch.from_numpy(rng.standard_normal((sum(ns), D)).astype(np.float32)).to(TORCH_DT[dtype])
+    off = np.concatenate([[0], np.cumsum(ns)]).astype(np.int32)
+    args = (x.to(DEV), torch.from_numpy(off).to(DEV), max(ns))
+    nb, best = mpm.argmax(*args, with_best=True)
+    only = mpm.argmax(*args)
+    torch.cuda.synchronize()
+    nb, only, best = nb.cpu().numpy(), only.cpu().numpy(), best.cpu().numpy()
+    for b, n in enumerate(ns):
+        assert np.array_equal(nb[b, :n], only[b, :n]), b
+        x64 = to64(x[off[b]:off[b + 1]])
+        for i in sorted({0, 1, 15, 63, n // 2, n - 1}):
+            if not 0 <= i < n:
+                continue
+            if n == 1:
+                assert nb[b, 0] == -1 and best[b, 0] == -np.inf
+                continue
+            # float32 sums of D products and two float32 norms: below 3 (D + 4) 2^-24.
+            assert abs(best[b, i] - oracle.cosine(x64, i, int(nb[b, i]))) <= 3 * (D + 4) * 2.0 ** -24, (b, i)
