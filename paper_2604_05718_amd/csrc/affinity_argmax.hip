@@ -206,8 +206,9 @@ __device__ __forceinline__ void exchange_half(float* v, int32_t* ix, int upper)
 // row of x too), and each lane overwrites the pieces it loaded there with zeros in LDS
 // before the barrier that makes the chunk visible, so the chunk loop itself is the same.
 // Zero pieces add nothing to the products or norms: the scores are bit-identical to a
-// K loop that ends with the row. The chunk is computed whole (400-byte rows issue 512 bytes
-// of products); cutting its empty k-groups off would put a branch into the chunk loop. 24
+// K loop that ends with the row. Of a last chunk that ends in its first half only that half is
+// computed, which a uniform branch a chunk decides: computed whole, 64-byte float32 rows, half
+// of a chunk, took 1.3 times as long (1903 images of 400: 288 us). 24
 // packed images of 346 to 990 rows of 400 bytes: 20 us, against 59 us for a kernel that
 // staged such rows through registers, one workgroup per query block.
 //
@@ -515,6 +516,10 @@ __global__ __launch_bounds__(WC * WQ * kWave, 2) void affinity_partial_kernel(  
         sq[j] = 0.0f;
         own_q[j] = min(wc + j * WC, NT - 1) * 32 * CB;  // from lq_off
     }
+    // TAIL: whether the last chunk of a row ends in its first half.
+    // (The large window blocks of bfloat16 rows have no registers left for the branch.)
+    constexpr bool CUT = TAIL && !(LOCAL && MT * NT >= 8 && S::kBytes == 2);
+    const bool half_tail = CUT && rowbytes - (long)(nchunks - 1) * CB <= CB / 2;
     // One load part before every PSTEP-th MFMA of a chunk, over the first half of its MFMAs (the
     // loads must land before the chunk ends).
     constexpr int PGROUPS = KG * MT * NT;  // MFMAs per chunk
@@ -522,6 +527,7 @@ __global__ __launch_bounds__(WC * WQ * kWave, 2) void affinity_partial_kernel(  
     static_assert(PSPAN >= 1, "load parts per MFMA");
     constexpr int PSTEP = PSPAN >= LOADS ? PSPAN / LOADS : 1;              // MFMAs between load slots
     constexpr int PPER = PSPAN >= LOADS ? 1 : (LOADS + PSPAN - 1) / PSPAN;  // loads per slot (small tiles)
+    static_assert((LOADS - 1) / PPER * PSTEP < PSPAN, "every load in the first half");
     auto mma_issue = [&](const u32x4 (&fa)[MT], const u32x4 (&fq)[NT], int chunk, int g) {
         u32x4 oc[NSC], oq[NSQ];
         if constexpr (!given) {
@@ -651,14 +657,22 @@ __global__ __launch_bounds__(WC * WQ * kWave, 2) void affinity_partial_kernel(  
         }
         advance();
         issue_begin();
+        auto groups = [&](int g0, int g1) {
 #pragma unroll
-        for (int g = 0; g < KG; ++g) {
-            if (g + 1 < KG) {
-                if ((g & 1) == 0) read_frags(fa1, fq1, consumed, g + 1);
-                else read_frags(fa0, fq0, consumed, g + 1);
+            for (int g = g0; g < g1; ++g) {
+                if (g + 1 < KG) {
+                    if ((g & 1) == 0) read_frags(fa1, fq1, consumed, g + 1);
+                    else read_frags(fa0, fq0, consumed, g + 1);
+                }
+                if ((g & 1) == 0) mma_issue(fa0, fq0, consumed, g);
+                else mma_issue(fa1, fq1, consumed, g);
             }
-            if ((g & 1) == 0) mma_issue(fa0, fq0, consumed, g);
-            else mma_issue(fa1, fq1, consumed, g);
+        };
+        if constexpr (CUT) {
+            groups(0, KG / 2);  // with all of the next chunk's loads
+            if (cchunk < nchunks - 1 || !half_tail) groups(KG / 2, KG);
+        } else {
+            groups(0, KG);
         }
         issue_end();
         ++consumed;

@@ -243,3 +243,24 @@ def test_cosines_of_narrow_rows(dtype, D, ns):
                 continue
             # float32 sums of D products and two float32 norms: below 3 (D + 4) 2^-24.
             assert abs(best[b, i] - oracle.cosine(x64, i, int(nb[b, i]))) <= 3 * (D + 4) * 2.0 ** -24, (b, i)
+
+
+# Rows whose last chunk ends in its first half (computed as half a chunk), at its middle, one
+# piece past it and at its end, on one chunk and on three; forced schedules where the width
+# allows them, each block shape against the small blocks bit for bit.
+@pytest.mark.parametrize("dtype,D", [(dt, (c * 128 + e) // (2 if dt == "bf16" else 4)) for dt in ("bf16", "f32")
+                                     for c in (0, 2) for e in (16, 48, 64, 80, 112)])
+def test_half_chunks(dtype, D):
+    rng = np.random.default_rng(D)
+    print(f"half chunks {dtype} D={D}", flush=True)
+    x = torch.stack([store(clustered(rng, 700, D, k=20), dtype) for _ in range(33)]).to(DEV)
+    nb, best = mpm.argmax(x, with_best=True)
+    for b in (0, 16, 32):
+        one, cos = mpm.argmax(x[b:b + 1].contiguous(), with_best=True)
+        torch.cuda.synchronize()
+        assert torch.equal(nb[b], one[0]) and torch.equal(best[b].view(torch.int32), cos[0].view(torch.int32))
+    check_nearest(to64(x[0].cpu()), nb[0].cpu().numpy())
+    for schedule in ("full", "symmetric") if D * x.element_size() % 64 == 0 else ():
+        fn, fb = mpm.argmax(x, with_best=True, schedule=schedule)
+        torch.cuda.synchronize()
+        assert torch.equal(nb, fn) and torch.equal(best.view(torch.int32), fb.view(torch.int32)), schedule
