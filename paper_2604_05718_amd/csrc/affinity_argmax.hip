@@ -1248,30 +1248,40 @@ double estimate_us(Blocks k, double blocks64, double blocks128, double full256, 
     }
 }
 
-// float32 rows: a block's matrix work outweighs the rest of it at every row width, so only the
-// rounds count, in units of a round of 128 x 128 symmetric blocks (two per CU); one of 256 x 256
-// blocks takes 1.8. Up to four 64 x 64 blocks a CU run as fast as the rest of the chip allows
+// float32 rows: a block's matrix work outweighs the rest of it, so only the rounds count, in
+// units of a round of 128 x 128 symmetric blocks (two per CU); one of 256 x 256 blocks takes 1.8. Up to four 64 x 64 blocks a CU run as fast as the rest of the chip allows
 // (they are whole rounds of a quarter of the work). Timed on 170 dense and 170 packed shapes, 1 to
 // 64 images of 100 to 4096 rows of 192 to 4096 bytes: 0.6% slower than the fastest of the four
 // shapes, against 59% for 64 x 64 blocks of at most 32 large blocks and 256 x 256 ones elsewhere.
 // Examples, 64 / 128 / 256 full / 256 symmetric, dense rows of 768 bytes: 4 images of 1024 rows
 // 19.1 / 19.5 / 49.0 / 52.5 us; 16 of 1024 rows 60.3 / 44.5 / 50.0 / 52.6; 32 of 1024 rows
 // - / 78.9 / 106.4 / 86.7; 46 of 1924 rows of 832 bytes - / 420.6 / 660.8 / 384.5.
-Blocks pick_blocks_f32(double blocks64, double blocks128, double sym256, double cus, bool packed)
+// Rows of at most one and a half chunks (c, in halves) are too narrow for that: their items' fixed
+// parts count, and a single round of full 256 x 256 blocks is the fastest of the large shapes.
+// 240 packed images of 196 to 230 64-byte rows, 128 / 256 full / 256 symmetric: 15.8 / 10.3 / 11.4
+// us; 16 of 1024 rows 13.2 / 10.3 / 13.0; 1000 packed of 2304 at most 1725 / 1816 / 1431. Over
+// 190 shapes each of rows of 64, 128 and 192 bytes the pick is 1.0, 1.0 and 0.8% slower than the
+// fastest (by rounds alone 3.2, 1.5 and 1.3%).
+Blocks pick_blocks_f32(double blocks64, double blocks128, double full256, double sym256, double c, double cus,
+                       bool packed)
 {
     if (blocks64 <= 4 * cus) return kBlocks64;
     const double r = blocks128 / (2 * cus), s = sym256 / cus;
     double rounds128, rounds256;
     if (packed) {  // lengths are only guessed: a part of a round is taken to cost its mean
         rounds128 = 1.1 * r <= 0.5 ? 0.6 : 1.1 * r <= 1 ? 1.0 : r + 0.3;
-        rounds256 = 1.8 * (1.1 * s <= 1 ? 1.0 : s + 0.6);
+        rounds256 = 1.1 * s <= 1 ? 1.0 : s + 0.6;
     } else {
         const double f = r - std::floor(r), g = s - std::floor(s);
         // The last round: alone on their CUs up to half of the slots; as half blocks.
         rounds128 = std::floor(r) + (f <= 0 ? 0.0 : f <= 0.5 ? 0.6 : 0.95);
-        rounds256 = 1.8 * (std::floor(s) + (g <= 0 ? 0.0 : s > 1 && g <= 0.5 ? 0.6 : 1.0));
+        rounds256 = std::floor(s) + (g <= 0 ? 0.0 : s > 1 && g <= 0.5 ? 0.6 : 1.0);
     }
-    return rounds128 <= rounds256 ? kBlocks128 : kBlocksSym256;
+    if (c > 1.5) return rounds128 <= 1.8 * rounds256 ? kBlocks128 : kBlocksSym256;
+    const double us128 = round_us(2.5, 4.6 + 3.5 * c, rounds128), us256 = round_us(2.0, 6.0 + 7.1 * c, rounds256);
+    const bool full = !packed || full256 <= cus;
+    if (full && round_us(2.5, 3.4 + 7.05 * c, std::ceil(full256 / cus)) < std::min(us128, us256)) return kBlocks256;
+    return us128 <= us256 ? kBlocks128 : kBlocksSym256;
 }
 
 Blocks pick_blocks(int B, int N, int D, int dt, int schedule, bool packed, int device_cu_count)
@@ -1299,7 +1309,8 @@ Blocks pick_blocks(int B, int N, int D, int dt, int schedule, bool packed, int d
             s256 += blocks(kPCT, kOrderSymmetric, percent) / 3;
         }
     }
-    if (dt != kBf16) return pick_blocks_f32(b64, b128, s256, cus, packed);
+    if (dt != kBf16)
+        return pick_blocks_f32(b64, b128, full256, s256, std::ceil(4.0 * D / (kChunkBytes / 2)) / 2, cus, packed);
     Blocks best = kBlocks128;
     double us = estimate_us(kBlocks128, b64, b128, full256, s256, c, cus, packed);
     for (Blocks k : {kBlocks64, kBlocks256, kBlocksSym256}) {

@@ -264,3 +264,24 @@ def test_half_chunks(dtype, D):
         fn, fb = mpm.argmax(x, with_best=True, schedule=schedule)
         torch.cuda.synchronize()
         assert torch.equal(nb, fn) and torch.equal(best.view(torch.int32), fb.view(torch.int32)), schedule
+
+
+@pytest.mark.parametrize("B,N,D,packed,rows", [(240, 256, 16, True, 256), (16, 1024, 16, False, 256),
+                                               (16, 1024, 48, False, 256), (16, 1024, 64, False, 128),
+                                               (600, 1024, 16, True, 256)])
+def test_pick_of_narrow_f32_rows(B, N, D, packed, rows):
+    """float32 rows of at most a chunk and a half: a single round of full 256-row blocks, and
+    many rounds of symmetric ones, where they are faster; equal to the small blocks."""
+    if torch.cuda.get_device_properties(DEV).multi_processor_count != 256:
+        pytest.skip("the picks are for a 256-CU device")
+    print(f"narrow f32 pick B={B} N={N} D={D} packed={packed}", flush=True)
+    assert mpm.affinity_block_rows(B, N, D, torch.float32, packed=packed) == rows
+    rng = np.random.default_rng(B + D)
+    ns = [int(v) for v in rng.integers(int(0.8 * N), int(0.9 * N), B)] if packed else [N] * B
+    x = torch.cat([store(clustered(rng, n, D, k=40), "f32") for n in ns]).to(DEV)
+    off = torch.from_numpy(np.concatenate([[0], np.cumsum(ns)]).astype(np.int32)).to(DEV)
+    args = (x, off, N) if packed else (x.view(B, N, D),)
+    nb, small = mpm.argmax(*args), mpm.argmax(*args, schedule="full_64")
+    torch.cuda.synchronize()
+    for b in range(B):
+        assert torch.equal(nb[b, :ns[b]], small[b, :ns[b]]), b
