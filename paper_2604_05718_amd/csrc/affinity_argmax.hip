@@ -1038,7 +1038,7 @@ struct AffinityArgs {
     const void* x;
     const int32_t* x_off;
     const float* xinv;
-    int B, N, D, T, xcds;
+    int B, N, D, T, cus, xcds;
     float* pv;
     int32_t* pi;
     hipStream_t stream;
@@ -1076,7 +1076,7 @@ void launch_counted(const AffinityArgs& a, int slots, const WorkShape& shape)
 }
 
 template <class S, int WC, int WQ, int MT, int NT, bool SYM, bool LOCAL, bool GIVEN, bool TAIL>
-void launch_persistent_as(const AffinityArgs& a, int groups)
+void launch_persistent_as(AffinityArgs a, int groups)
 {
     // No more slots than a group can have items (images of N tokens; two a diagonal block that
     // may run as halves), and no count of the images' own blocks when every item has its slot
@@ -1086,11 +1086,22 @@ void launch_persistent_as(const AffinityArgs& a, int groups)
     constexpr WorkOrder ORDER = LOCAL ? kOrderBand : SYM ? kOrderSymmetric : kOrderFull;
     const int nb = (a.N + CT - 1) / CT;
     const long total = (long)a.B * work_items(ORDER, nb);
+    const bool counted = a.x_off != nullptr && a.B <= kMaxCountedImages && total > groups / a.xcds * (long)a.xcds;
+    // Fewer images than XCDs: one group, so that the shares are the chip's.
+    // - Blocks that may run as halves: an early share of a large image has too few diagonal
+    //   blocks to defer and takes another round, and no share waits for the others. One image
+    //   of 5835 rows of 2048 bytes, 276 blocks on 256 slots, in 8 groups / one: 84.5 / 58.5 us.
+    // - Ragged images with a slot for each item, several slots a CU: the long image's items
+    //   would all run on its share's XCDs. 1288 and 80 float32 rows of 4096 bytes: 81 / 45 us;
+    //   three images of 2000, 100 and 100 rows of 1536 bytes 19 / 15. At a slot a CU at most,
+    //   images of about N rows are up to 8% slower in one group (their rows pass through every
+    //   L2), as are counted shares.
+    if (a.B < kXcds && (SPLIT || (!LOCAL && a.x_off != nullptr && !counted && total > a.cus))) a.xcds = 1;
     const int most = groups / a.xcds;
     const long each = (total + a.xcds - 1) / a.xcds;
     const int slots = (int)std::min<long>(most, SPLIT && splits_lone<S>(chunks_of<S>(a.D)) ? 2 * each : each);
     const WorkShape shape(ORDER, a.B, nb);
-    if (a.x_off != nullptr && a.B <= kMaxCountedImages && total > (long)most * a.xcds)
+    if (counted)
         launch_counted<S, WC, WQ, MT, NT, SYM, LOCAL, GIVEN, TAIL, true>(a, slots, shape);
     else
         launch_counted<S, WC, WQ, MT, NT, SYM, LOCAL, GIVEN, TAIL, false>(a, slots, shape);
@@ -1357,7 +1368,7 @@ hipError_t launch_affinity(const void* x, const int32_t* x_off, int B, int N, in
     const int cus = device_cus();
     if (cus <= 0) return hipErrorInvalidDevice;
     const int xcds = cus % kXcds == 0 ? kXcds : 1;
-    const AffinityArgs a{x, x_off, dt == kBf16 ? xinv : nullptr, B, N, D, T, xcds, pv, pi, stream, start, stop,
+    const AffinityArgs a{x, x_off, dt == kBf16 ? xinv : nullptr, B, N, D, T, cus, xcds, pv, pi, stream, start, stop,
                          Window{nullptr, FixedDiv(1), 0}, clear};
     const Blocks blocks = pick_blocks(B, N, D, dt, schedule, x_off != nullptr, cus);
     *tile_width = block_rows(blocks);
@@ -1381,7 +1392,7 @@ hipError_t launch_affinity_local(const void* x, const int32_t* x_off, const floa
     const int cus = device_cus();
     if (cus <= 0) return hipErrorInvalidDevice;
     const int xcds = cus % kXcds == 0 ? kXcds : 1;
-    const AffinityArgs a{x, x_off, dt == kBf16 ? xinv : nullptr, B, N, D, T, xcds, pv, pi, stream, start, stop,
+    const AffinityArgs a{x, x_off, dt == kBf16 ? xinv : nullptr, B, N, D, T, cus, xcds, pv, pi, stream, start, stop,
                          Window{pos, FixedDiv((uint32_t)grid_w), radius}, clear};
     if (block_rows == kLCT) launch_persistent<kLWC, kLWQ, kLMT, kLNT, true, true>(dt, a, cus * kLWGS);
     else launch_persistent<kSWC, kSWQ, kSMT, kSNT, true, true>(dt, a, cus * kPWGS);

@@ -285,3 +285,25 @@ def test_pick_of_narrow_f32_rows(B, N, D, packed, rows):
     torch.cuda.synchronize()
     for b in range(B):
         assert torch.equal(nb[b, :ns[b]], small[b, :ns[b]]), b
+
+
+# Fewer images than XCDs: large blocks (one image whose last round runs as half blocks, two
+# images, a part of a round), ragged small and middling blocks with a slot for each item.
+@pytest.mark.parametrize("dtype,D,ns,N", [("bf16", 64, [5835], 5835), ("bf16", 64, [4500], 5400),
+                                          ("bf16", 64, [3700, 3650], 4096), ("f32", 64, [4096, 3300], 4096),
+                                          ("f32", 64, [1288, 80], 1288), ("bf16", 384, [2000, 100, 100], 2000),
+                                          ("bf16", 64, [3, 1704, 0, 90, 1], 1704)])
+def test_few_images(dtype, D, ns, N):
+    rng = np.random.default_rng(sum(ns))
+    rows = mpm.affinity_block_rows(len(ns), N, D, TORCH_DT[dtype], packed=True)
+    print(f"few images {dtype} D={D} ns={ns} N={N}: {rows} rows", flush=True)
+    imgs = [store(clustered(rng, n, D, k=40), dtype) for n in ns]
+    off = torch.from_numpy(np.concatenate([[0], np.cumsum(ns)]).astype(np.int32)).to(DEV)
+    x = torch.cat(imgs).to(DEV)
+    nb = {s: mpm.argmax(x, off, N=N, schedule=s) for s in ("auto", "full", "symmetric", "full_64")}
+    torch.cuda.synchronize()
+    for b, n in enumerate(ns):
+        for s in ("full", "symmetric", "full_64"):
+            assert torch.equal(nb["auto"][b, :n], nb[s][b, :n]), (b, s)
+    b = int(np.argmax(ns))
+    check_nearest(to64(imgs[b]), nb["auto"][b, :ns[b]].cpu().numpy())
