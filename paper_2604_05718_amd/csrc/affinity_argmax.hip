@@ -187,7 +187,8 @@ __device__ __forceinline__ void exchange_half(float* v, int32_t* ix, int upper)
 // lockstep over K, and each block of rows is fetched from HBM once and re-read from that
 // XCD's L2 by the other items that use it, instead of being refetched once per candidate
 // tile. Packed images are counted by their own lengths: the workgroup tabulates the block
-// counts of up to kMaxCountedImages images first (one wave, 64 offsets at a time).
+// counts of up to kMaxCountedImages images first (one image a thread: by one wave, 64 images
+// at a time, 402 images took 5 us of a launch of 17).
 //
 // Pipeline. The chunks of all the workgroup's items form one stream. The barrier before
 // chunk c makes chunk c visible and retires chunk c-1's stage; chunk c's first fragments
@@ -315,28 +316,41 @@ __global__ __launch_bounds__(WC * WQ * kWave, 2) void affinity_partial_kernel(  
     __shared__ int32_t items_tab[COUNTED ? kMaxCountedImages + 1 : 1], diags_tab[COUNTED ? kMaxCountedImages + 1 : 1];
     const WorkCounts<COUNTED> counts{shape, items_tab, diags_tab};
     if constexpr (COUNTED) {
-        if (wave == 0) {
-            int items = 0, diags = 0;  // of the images so far
-            for (int b0 = 0; b0 < B; b0 += kWave) {
-                const int b = b0 + lane;
-                const int im = work_place(b, shape.run);
-                const int nb = b < B ? (x_off[im + 1] - x_off[im] + CT - 1) / CT : 0;
-                int si = work_items(ORDER, nb), sd = nb;
+        // One image a thread: inclusive sums over the wave, then over the waves before it.
+        __shared__ int32_t part[2][WAVES];
+        int items = 0, diags = 0;  // of the images of earlier passes
+        for (int b0 = 0; b0 < B; b0 += THREADS) {
+            const int b = b0 + tid;
+            const int im = work_place(b, shape.run);
+            const int nb = b < B ? (x_off[im + 1] - x_off[im] + CT - 1) / CT : 0;
+            int si = work_items(ORDER, nb), sd = nb;
 #pragma unroll
-                for (int o = 1; o < kWave; o <<= 1) {
-                    const int yi = __shfl_up(si, o), yd = __shfl_up(sd, o);
-                    si += lane >= o ? yi : 0;
-                    sd += lane >= o ? yd : 0;
-                }
-                if (b < B) {
-                    items_tab[b + 1] = items + si;
-                    diags_tab[b + 1] = diags + sd;
-                }
-                items += __shfl(si, kWave - 1);
-                diags += __shfl(sd, kWave - 1);
+            for (int o = 1; o < kWave; o <<= 1) {
+                const int yi = __shfl_up(si, o), yd = __shfl_up(sd, o);
+                si += lane >= o ? yi : 0;
+                sd += lane >= o ? yd : 0;
             }
-            if (lane == 0) items_tab[0] = diags_tab[0] = 0;
+            if (b0 > 0) __syncthreads();  // the last pass's sums are read
+            if (lane == kWave - 1) {
+                part[0][wave] = si;
+                part[1][wave] = sd;
+            }
+            __syncthreads();
+            int pi0 = items, pd0 = diags;
+#pragma unroll
+            for (int w = 0; w < WAVES; ++w) {
+                const int ci = part[0][w], cd = part[1][w];
+                pi0 += w < wave ? ci : 0;
+                pd0 += w < wave ? cd : 0;
+                items += ci;
+                diags += cd;
+            }
+            if (b < B) {
+                items_tab[b + 1] = pi0 + si;
+                diags_tab[b + 1] = pd0 + sd;
+            }
         }
+        if (tid == 0) items_tab[0] = diags_tab[0] = 0;
         __syncthreads();
     }
     const int group = blockIdx.x & ((1 << log_xcds) - 1);

@@ -154,8 +154,11 @@ struct WorkBlock {
     int b, q, t;  // image, query block, candidate tile (band order: the block's own)
 };
 
+constexpr int kWaveLanes = 64;
+
 // The r-th item of the share that is not deferred (r < cnt - ndef). `from`: an image at or
-// before the item's, to start looking at.
+// before the item's, to start looking at. On the device a whole wave calls it with the same
+// arguments where images are tabulated; elsewhere each lane may ask for another item.
 template <WorkOrder ORDER, bool SPLIT, bool TAB>
 MPM_HD WorkBlock work_block(const WorkCounts<TAB>& c, const WorkShare& s, int r, int from)
 {
@@ -185,13 +188,34 @@ MPM_HD WorkBlock work_block(const WorkCounts<TAB>& c, const WorkShare& s, int r,
         }
     } else {
         int b = from;
-        int start = c.items(b) - (defers && c.diags(b) > s.dstart ? c.diags(b) - s.dstart : 0);
+        int start;
+#if defined(__HIP_DEVICE_COMPILE__)
+        // 64 images at a time, one a lane (one after the other, a batch of one-block images cost
+        // each item as many reads as its group has slots). The entry past the last image lies
+        // past p, so the first one that does is found before any entry that was never written.
+        const int lane = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+        for (;;) {
+            const int i = b + lane < kMaxCountedImages ? b + lane : kMaxCountedImages;
+            const int di = c.diags_tab[i];
+            const int at = c.items_tab[i] - (defers && di > s.dstart ? di - s.dstart : 0);
+            const uint64_t past = __ballot(at > p);
+            if (past != 0) {
+                const int f = (int)__builtin_ctzll(past);
+                b += f - 1;
+                start = __builtin_amdgcn_readlane(at, f - 1);  // f >= 1: `from` starts at or before p
+                break;
+            }
+            b += kWaveLanes - 1;
+        }
+#else
+        start = c.items(b) - (defers && c.diags(b) > s.dstart ? c.diags(b) - s.dstart : 0);
         for (;;) {
             const int next = c.items(b + 1) - (defers && c.diags(b + 1) > s.dstart ? c.diags(b + 1) - s.dstart : 0);
             if (p < next) break;
             start = next;
             ++b;
         }
+#endif
         k.b = b;
         w = p - start;
     }

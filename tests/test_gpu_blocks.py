@@ -307,3 +307,44 @@ def test_few_images(dtype, D, ns, N):
             assert torch.equal(nb["auto"][b, :n], nb[s][b, :n]), (b, s)
     b = int(np.argmax(ns))
     check_nearest(to64(imgs[b]), nb["auto"][b, :ns[b]].cpu().numpy())
+
+
+# Batches whose items lie far apart: counted ones with runs of more than 64 images without an
+# item of the slot's, empty images at either end, 512 images and one less; batches past the
+# counted limit, most of whose items lie past their image's end (more than 64 of a slot's in a
+# row), the last image the only long one.
+SPARSE = {
+    "counted_runs": [300] + [0] * 90 + [600] + [1, 0, 2] * 100 + [0] * 60 + [900] + [0] * 20,
+    "counted_limit": [0] + [3] * 500 + [0] * 5 + [700, 1, 0, 513, 0, 0],
+    "below_the_limit": [40, 0, 1] * 170 + [900],
+    "past_the_limit": [1400] + [0, 5, 0, 1, 70] * 130 + [1300],
+    "last_long": [0] * 600 + [1, 1500],
+}
+
+
+@pytest.mark.parametrize("dtype,D", [("bf16", 32), ("f32", 16), ("bf16", 72)])
+@pytest.mark.parametrize("name", list(SPARSE))
+def test_items_far_apart(name, dtype, D):
+    """Every schedule gives the same neighbours as the small blocks; the long images and some
+    short ones against the oracle; the window (every item a band) too."""
+    ns = SPARSE[name]
+    rng = np.random.default_rng(len(ns))
+    print(f"items far apart {name} {dtype} D={D}: {len(ns)} images", flush=True)
+    x = store(clustered(rng, sum(ns), D, k=60), dtype).to(DEV)
+    off = torch.from_numpy(np.concatenate([[0], np.cumsum(ns)]).astype(np.int32)).to(DEV)
+    N = max(ns)
+    nb = {s: mpm.argmax(x, off, N=N, schedule=s) for s in ("full_64", "auto", "full", "symmetric")}
+    torch.cuda.synchronize()
+    keep = torch.arange(N, device=DEV)[None, :] < torch.diff(off)[:, None]
+    for s in ("auto", "full", "symmetric"):
+        assert torch.equal(nb[s][keep], nb["full_64"][keep]), s
+    offh = off.cpu().numpy()
+    for b in sorted(set(np.argsort(ns)[-2:].tolist() + [1, len(ns) // 2])):
+        if ns[b]:
+            check_nearest(to64(x[offh[b]:offh[b + 1]].cpu()), nb["auto"][b, :ns[b]].cpu().numpy())
+    # A window over the whole grid is the dense method.
+    one = mpm.merge(x, off, N=N)
+    for rows in (128, 256) if D * x.element_size() % 64 == 0 else (0,):
+        m = mpm.merge_local(x, N, N, x_off=off, N=N, block_rows=rows)
+        torch.cuda.synchronize()
+        assert torch.equal(m.y_off, one.y_off) and torch.equal(m.map, one.map)
