@@ -394,6 +394,29 @@ __global__ __launch_bounds__(WC * WQ * kWave, 2) void affinity_partial_kernel(  
                 }
                 return it;
             }
+            if constexpr (!COUNTED && !HALVES) {
+                // An item past its image's end, in a batch whose images are not counted: the
+                // slot's next item inside its image, 64 of them at a time. One after the other
+                // took half a microsecond each: 1380 images of up to 3487 rows, a twentieth of
+                // them filled, 566 items a slot.
+                int k0 = k + slots;
+                for (; k0 < nitems; k0 += kWave * slots) {
+                    const int kl = k0 + lane * slots;
+                    bool inside = false;
+                    if (kl < nitems) {
+                        const WorkBlock v = work_block<ORDER, SPLIT>(counts, share, kl, 0);
+                        const int bv = work_place(v.b, shape.run);
+                        const int nv = x_off[bv + 1] - x_off[bv];  // with offsets: dense items are never past the end
+                        inside = v.q * QT < nv && v.t * CT < nv;
+                    }
+                    const uint64_t found = __ballot(inside);
+                    if (found != 0) {
+                        k0 += (int)__builtin_ctzll(found) * slots;
+                        break;
+                    }
+                }
+                k = k0 - slots;
+            }
         }
         it.k = nitems; it.b = 0; it.place = 0; it.qbase = 0; it.cbase = 0; it.n = 1; it.row0 = 0; it.tlo = 0; it.thi = 0;
         return it;
