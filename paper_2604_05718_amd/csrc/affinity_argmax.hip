@@ -1272,7 +1272,17 @@ enum Blocks : int { kBlocks64, kBlocks128, kBlocks256, kBlocksSym256 };
 // of 1536 bytes: 8 images of 400 rows 10.0 / 13.5 / 21.2 / 24.2 us; 12 of 1024 rows 35.8 /
 // 18.0 / 22.6 / 24.7; 24 of 1024 rows 67.7 / 32.3 / 41.9 / 27.1; 16 of 1024 rows of 384 bytes
 // - / 15.7 / 11.3 / 14.6.
+// Batches past those, up to 1000 images (430 shapes of rows of 64 to 2048 bytes): after some
+// rounds of large symmetric blocks the workgroups no longer start theirs together, and a round
+// costs a tenth less; a packed batch takes the full 256 x 256 blocks where its images have one
+// block (no reverse direction) or rows of a chunk at most. Against the pick of 64 x 64 blocks for
+// at most 32 large ones and 256 x 256 ones elsewhere 10% faster, 19 shapes more than 4% slower
+// and none more than 13% (without these 46, and 37%). 1000 packed images of 196 rows of 128
+// bytes, 128 / 256 full: 25.4 / 18.6 us; 500 of 400 rows of 768 bytes, 128 / 256 symmetric:
+// 86.5 / 78.5.
 double round_us(double fixed, double round, double rounds) { return fixed + round * rounds; }
+
+double settled(double rounds) { return std::min(rounds, 4.0) + 0.9 * std::max(0.0, rounds - 4.0); }
 
 double estimate_us(Blocks k, double blocks64, double blocks128, double full256, double sym256, double c, double cus,
                    bool counted)
@@ -1294,9 +1304,9 @@ double estimate_us(Blocks k, double blocks64, double blocks128, double full256, 
     case kBlocks256: return round_us(2.5, 4.3 + 1.43 * c, std::ceil(full256 / cus));
     default: {
         const double round = 9.0 + 1.31 * c, r = sym256 / cus;
-        if (counted) return round_us(2.0, round, 1.1 * r <= 1 ? 1 : r + 0.62) + (1.1 * r <= 1 ? 0 : 3.0);
+        if (counted) return round_us(2.0, round, 1.1 * r <= 1 ? 1 : settled(r + 0.62)) + (1.1 * r <= 1 ? 0 : 3.0);
         const double f = r - std::floor(r);  // a short last round runs as half blocks
-        return round_us(2.0, round, std::floor(r) + (f <= 0 ? 0 : r > 1 && f <= 0.5 ? 0.82 : 1.0));
+        return round_us(2.0, round, settled(std::floor(r) + (f <= 0 ? 0 : r > 1 && f <= 0.5 ? 0.82 : 1.0)));
     }
     }
 }
@@ -1368,7 +1378,8 @@ Blocks pick_blocks(int B, int N, int D, int dt, int schedule, bool packed, int d
     double us = estimate_us(kBlocks128, b64, b128, full256, s256, c, cus, packed);
     for (Blocks k : {kBlocks64, kBlocks256, kBlocksSym256}) {
         if (k == kBlocks64 && capacity64 > 2.5 * cus) continue;  // beyond, 128 x 128 blocks are as fast
-        if (k == kBlocks256 && packed && full256 > cus) continue;  // a round of whole images or the symmetric blocks
+        // A round of whole images, images of one block, narrow rows; or the symmetric blocks.
+        if (k == kBlocks256 && packed && full256 > cus && N > kPCT && c > 1) continue;
         const double e = estimate_us(k, b64, b128, full256, s256, c, cus, packed);
         if (e < us) {
             us = e;

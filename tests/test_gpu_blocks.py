@@ -348,3 +348,28 @@ def test_items_far_apart(name, dtype, D):
         m = mpm.merge_local(x, N, N, x_off=off, N=N, block_rows=rows)
         torch.cuda.synchronize()
         assert torch.equal(m.y_off, one.y_off) and torch.equal(m.map, one.map)
+
+
+@pytest.mark.parametrize("B,N,D,packed,used", [(1000, 196, 64, True, "full"), (500, 400, 384, False, "symmetric"),
+                                               (1000, 256, 384, True, "full"), (64, 1024, 768, False, "symmetric")])
+def test_pick_of_large_batches(B, N, D, packed, used):
+    """Batches of many rounds run the large blocks where they are faster; neighbours equal to
+    the small blocks' (a sample of the images against the oracle)."""
+    if torch.cuda.get_device_properties(DEV).multi_processor_count != 256:
+        pytest.skip("the picks are for a 256-CU device")
+    print(f"pick of a large batch B={B} N={N} D={D} packed={packed}", flush=True)
+    assert mpm.affinity_block_rows(B, N, D, torch.bfloat16, packed=packed) == 256
+    if not packed:
+        assert mpm.affinity_schedule_used(B, N, D, torch.bfloat16) == used
+    g = torch.Generator(device=DEV).manual_seed(B + D)
+    ns = [int(v) for v in np.random.default_rng(B).integers(int(0.8 * N), int(0.9 * N), B)] if packed else [N] * B
+    x = torch.randn((sum(ns), D), generator=g, device=DEV).to(torch.bfloat16)
+    off = torch.from_numpy(np.concatenate([[0], np.cumsum(ns)]).astype(np.int32)).to(DEV)
+    args = (x, off, N) if packed else (x.view(B, N, D),)
+    nb, small = mpm.argmax(*args), mpm.argmax(*args, schedule="full_64")
+    torch.cuda.synchronize()
+    keep = torch.arange(N, device=DEV)[None, :] < torch.diff(off)[:, None]
+    assert torch.equal(nb[keep], small[keep])
+    o = off.cpu().numpy()
+    for b in (0, B - 1):
+        check_nearest(to64(x[o[b]:o[b + 1]].cpu()), nb[b, :ns[b]].cpu().numpy())
