@@ -28,6 +28,7 @@
 #include <cmath>
 #include <vector>
 
+#include "../../include/mpm.h"
 #include "mpm_device.h"
 #include "mpm_launch.h"
 #include "mpm_work.h"
@@ -1445,8 +1446,10 @@ hipError_t launch_affinity_local(const void* x, const int32_t* x_off, const floa
     const int cus = device_cus();
     if (cus <= 0) return hipErrorInvalidDevice;
     const int xcds = cus % kXcds == 0 ? kXcds : 1;
+    // No two cells of a grid are further apart (the kernel adds the radius to a row).
+    const int reach = std::min(radius, MPM_MAX_N);
     const AffinityArgs a{x, x_off, dt == kBf16 ? xinv : nullptr, B, N, D, T, cus, xcds, pv, pi, stream, start, stop,
-                         Window{pos, FixedDiv((uint32_t)grid_w), radius}, clear};
+                         Window{pos, FixedDiv((uint32_t)grid_w), reach}, clear};
     if (block_rows == kLCT) launch_persistent<kLWC, kLWQ, kLMT, kLNT, true, true>(dt, a, cus * kLWGS);
     else launch_persistent<kSWC, kSWQ, kSMT, kSNT, true, true>(dt, a, cus * kPWGS);
     return hipGetLastError();

@@ -251,3 +251,26 @@ def test_local_block_choice():
     assert picks == {("vit_l_1024", 4): 256, ("vit_l_1024", 2): 128, ("vit_b_512", 3): 128, ("stress_768", 4): 128}
     assert mpm.local_block_rows(16, 4096, 1024, torch.bfloat16, 64, 4, block_rows=128) == 128
     assert mpm.local_block_rows(16, 4096, 40, torch.bfloat16, 64, 4) == 4096   # 80-byte rows: the staged kernel
+
+
+@pytest.mark.parametrize("block_rows", [128, 256])
+def test_largest_windows_are_dense(block_rows):
+    """Windows as wide as the grid and wider, up to the largest the ABI takes, are the dense
+    method on every row of the grid (an image of four 256-row blocks), also on given positions
+    in the grid's last rows."""
+    rng = np.random.default_rng(5)
+    N, D, gw = 1000, 64, 25
+    cent = rng.standard_normal((30, D))
+    x = store(cent[rng.integers(0, 30, N)] + 0.3 * rng.standard_normal((N, D)), "bf16").to(DEV)
+    dense = mpm.merge(x[None])
+    off = torch.tensor([0, N], dtype=torch.int32, device=DEV)
+    last = torch.arange(N, dtype=torch.int32, device=DEV) + (16384 * gw - N)
+    for window in (40, 16383, 16384, 1 << 20, 2 ** 31 - 1):
+        print(f"largest windows {window} blocks {block_rows}", flush=True)
+        m = mpm.merge_local(x[None], gw, window, block_rows=block_rows)
+        p = mpm.merge_local(x, gw, window, x_off=off, N=N, pos=last, block_rows=block_rows)
+        torch.cuda.synchronize()
+        total = int(dense.y_off[1])
+        for r in (m, p):
+            assert torch.equal(r.y_off, dense.y_off) and torch.equal(r.map, dense.map)
+            assert torch.equal(r.y[:total].view(torch.int16), dense.y[:total].view(torch.int16))
