@@ -65,7 +65,8 @@
  *   for a one-token image), merged-row sources (in [0, n_b)) and maps (in [-1, N),
  *   or [-1, n_z) where they index merged rows). Offsets are validated first; the
  *   rows they address must exist. On a violation the call returns
- *   MPM_ERR_INVALID_ARG and launches nothing of its operation. A checked call
+ *   MPM_ERR_INVALID_ARG and launches nothing of its operation (mpm_run_schedule
+ *   checks each insertion's input so, and may have run those before it). A checked call
  *   synchronises its stream (it reads the verdict back; so not under graph
  *   capture), and checked calls are serialised by a lock. Without the variable
  *   nothing of this runs.
@@ -368,7 +369,10 @@ typedef struct mpm_insertion {
  * Results are those of the separate calls, bit for bit. The last pair average writes the
  * merged rows and the grid in one pass. Errors as mpm_merge and mpm_merge_local, plus
  * MPM_ERR_INVALID_ARG for insertions < 1 or overlapping workspaces and MPM_ERR_UNSUPPORTED
- * for more than 3 insertions.
+ * for more than 3 insertions. In checked mode each insertion's input is validated before that
+ * insertion, as the separate calls do: x before anything is launched; where finite tokens
+ * overflow in a merged row or its norm, the next insertion is refused, with the buffers of the
+ * insertions before it written and the others, rstar and out, not.
  */
 int mpm_run_schedule(const void* x, int32_t B, int32_t N, int32_t D, int32_t dt, int32_t schedule, int32_t grid_w,
                      int32_t window, int32_t block_rows, const mpm_insertion* ins, int32_t insertions,

@@ -50,7 +50,8 @@ int injected_failure() { return hip_status(hipErrorLaunchFailure); }
 // every entry point validates the data-dependent preconditions it would otherwise take
 // on trust, on the device, before launching its operation: packed offsets first (their
 // verdict read back), then the values the operation indexes with. A failure returns
-// MPM_ERR_INVALID_ARG with nothing of the operation launched. The verdict is one device
+// MPM_ERR_INVALID_ARG with nothing of the operation launched (a schedule's operations are
+// its insertions). The verdict is one device
 // word per GPU (a file-scope array: its address is looked up once per device, as for
 // the allocation-free entry point's array); checked calls synchronise their stream and
 // are serialised by a lock.

@@ -79,6 +79,32 @@ int main(void)
         EXPECT(mpm_local_block_rows(2, 64, 64, MPM_BF16, MPM_MAX_N + 1, 1, 0, &rows), MPM_ERR_INVALID_ARG);
         if (rows != -7) return 1;
     }
+    /* Whole schedules: three insertions in disjoint workspaces of exactly the size needed. */
+    mpm_insertion ins[3];
+    const size_t need = mpm_workspace_bytes(2, 64);
+    for (int s = 0; s < 3; ++s) {
+        ins[s].y = A;
+        ins[s].y_off = (int32_t*)A2;
+        ins[s].y_inv = NULL;
+        ins[s].y_pos = (int32_t*)A2;
+        ins[s].map = (int32_t*)A2;
+        ins[s].ws = (void*)((uintptr_t)0x10000000 + (size_t)s * ((need + 255) / 256 * 256));
+    }
+    EXPECT(mpm_run_schedule(A, 2, 64, 64, MPM_BF16, 0, 0, -1, 0, ins, 0, need, A2, A, NULL), MPM_ERR_INVALID_ARG);
+    EXPECT(mpm_run_schedule(A, 2, 64, 64, MPM_BF16, 0, 0, -1, 0, NULL, 1, need, A2, A, NULL), MPM_ERR_INVALID_ARG);
+    EXPECT(mpm_run_schedule(A, 2, 64, 64, MPM_BF16, 0, 0, -1, 0, ins, 4, need, A2, A, NULL), MPM_ERR_UNSUPPORTED);
+    EXPECT(mpm_run_schedule(A, 2, 64, 64, MPM_BF16, 0, 0, -1, 0, ins, 3, need - 1, A2, A, NULL), MPM_ERR_WORKSPACE);
+    EXPECT(mpm_run_schedule(A, 2, 64, 64, MPM_BF16, 0, 0, -1, 0, ins, 3, need, NULL, A, NULL), MPM_ERR_INVALID_ARG);
+    EXPECT(mpm_run_schedule(A, 2, 64, 64, MPM_BF16, 0, 0, 1, 0, ins, 3, need, A2, A, NULL), MPM_ERR_INVALID_ARG);
+    EXPECT(mpm_run_schedule(A, 2, 64, 64, MPM_BF16, 0, 8, 1, 64, ins, 3, need, A2, A, NULL), MPM_ERR_INVALID_ARG);
+    EXPECT(mpm_run_schedule(A, MPM_MAX_B, MPM_MAX_N, MPM_MAX_D, MPM_BF16, 0, 0, -1, 0, ins, 1, need, A2, A, NULL),
+           MPM_ERR_WORKSPACE);
+    ins[0].y_inv = (float*)A; /* norms of 80-byte rows: the next insertion does not take them */
+    EXPECT(mpm_run_schedule(A, 2, 64, 40, MPM_BF16, 0, 0, -1, 0, ins, 2, need, A2, A, NULL), MPM_ERR_UNSUPPORTED);
+    ins[0].y_inv = NULL;
+    ins[1].ws = (void*)((uintptr_t)ins[0].ws + (need - 1) / 256 * 256);
+    EXPECT(mpm_run_schedule(A, 2, 64, 64, MPM_BF16, 0, 0, -1, 0, ins, 2, need, A2, A, NULL), MPM_ERR_INVALID_ARG);
+    ins[1].ws = (void*)((uintptr_t)ins[0].ws + (need + 255) / 256 * 256);
     EXPECT(mpm_pad(A, A2, 2, 8, 40, A, NULL), MPM_ERR_INVALID_ARG);
     EXPECT(mpm_unpad(A, NULL, 2, 8, 64, A, NULL), MPM_ERR_INVALID_ARG);
     EXPECT(mpm_last_hip_error(), 0);
@@ -102,6 +128,10 @@ int main(void)
         EXPECT(mpm_compose_unmerge(A, NULL, A2, A2, NULL, NULL, 0, 2, 16, 64, MPM_BF16, A, NULL), MPM_ERR_HIP);
         EXPECT(mpm_merge_local(A, NULL, NULL, NULL, 2, 64, 64, MPM_BF16, 8, 1, 0, A2, A2, NULL, A2, A2, A, big, NULL,
                                NULL, NULL), MPM_ERR_HIP);
+        for (int n = 1; n <= 3; ++n) {
+            EXPECT(mpm_run_schedule(A, 2, 64, 64, MPM_BF16, 0, 0, -1, 0, ins, n, need, A2, A, NULL), MPM_ERR_HIP);
+            EXPECT(mpm_run_schedule(A, 2, 64, 64, MPM_BF16, 0, 8, 1, 128, ins, n, need, A2, A, NULL), MPM_ERR_HIP);
+        }
         EXPECT(mpm_pad(A, A2, 2, 8, 64, A, NULL), MPM_ERR_HIP);
         EXPECT(mpm_unpad(A, A2, 2, 8, 64, A, NULL), MPM_ERR_HIP);
         EXPECT(mpm_last_hip_error(), hip_launch_failure);

@@ -203,3 +203,91 @@ def test_checked_mode(tmp_path):
     assert np.array_equal(got["y_off"], y_off)
     assert np.array_equal(got["map"], res.map.cpu().numpy())
     assert np.array_equal(got["y"][: y_off[-1]], res.y[: y_off[-1]].view(torch.int16).cpu().numpy())
+
+
+SCHEDULE_CHILD = r"""
+import json, sys
+import numpy as np
+import torch
+sys.path.insert(0, sys.argv[1])
+import paper_2604_05718_amd as mpm
+from paper_2604_05718_amd import api
+
+dev = torch.device("cuda:0")
+B, N, D = 3, 300, 64
+results = {}
+rng = np.random.default_rng(6)
+cent = rng.standard_normal((3, 40, D))
+x = np.stack([cent[b][rng.integers(0, 40, N)] for b in range(B)]) + 0.3 * rng.standard_normal((B, N, D))
+x = torch.from_numpy(x.astype(np.float32)).to(torch.bfloat16).to(dev)
+
+def blank(s):
+    for t in s.y_off + s.map + [s.rstar]:
+        t.fill_(-7)
+    s.out.fill_(3.0)
+    return s
+
+def run(xx, **kw):
+    s = blank(api.Schedule(B, N, D, xx.dtype, insertions=2, device=dev, **kw))
+    try:
+        s.run(xx)
+        rc = 0
+    except mpm.MPMError as e:
+        rc = e.status
+    torch.cuda.synchronize()
+    ran = [bool((o.cpu() != -7).any()) for o in s.y_off]
+    return s, rc, ran, bool((s.out.float().cpu() == 3.0).all() and (s.rstar.cpu() == -7).all())
+
+for name, kw in (("dense", {}), ("window", dict(grid_w=20, window=2))):
+    s, rc, ran, untouched = run(x, **kw)
+    results["valid_" + name] = [rc, ran]
+    np.savez(sys.argv[2] + name + ".npz", out=s.out.view(torch.int16).cpu().numpy(), rstar=s.rstar.cpu().numpy())
+    xn = x.clone(); xn[1, 7, 3] = float("nan")
+    results["nan_" + name] = list(run(xn, **kw)[1:])
+    # Finite rows whose squares overflow: the carried inverse norms are zero.
+    big = (x.float() * 1e25).to(torch.bfloat16)
+    results["overflow_" + name] = list(run(big, **kw)[1:])
+    try:  # ... as the separate calls refuse them
+        m = mpm.merge(big, want_inv=True) if name == "dense" else mpm.merge_local(big, 20, 2, want_inv=True)
+        if name == "dense":
+            mpm.merge(m.y, m.y_off, N=N, x_inv=m.y_inv)
+        else:
+            mpm.merge_local(m.y, 20, 2, x_off=m.y_off, N=N, pos=m.y_pos, x_inv=m.y_inv)
+        results["steps_" + name] = 0
+    except mpm.MPMError as e:
+        results["steps_" + name] = e.status
+    torch.cuda.synchronize()
+print("RESULTS " + json.dumps(results), flush=True)
+"""
+
+
+def test_checked_schedule(tmp_path):
+    """A whole schedule in checked mode: valid input gives the unchecked grid bit for bit; a
+    bad token is refused before anything is launched; merged rows that the next insertion
+    cannot take are refused there, as the separate calls refuse them, with the first
+    insertion's buffers written and the grid and composed map untouched."""
+    from paper_2604_05718_amd import api
+
+    env = dict(os.environ, MPM_CHECKED="1", PYTHONPATH=ROOT)
+    env.pop("MPM_FAULT_INJECT", None)
+    print("checked schedule: child process with MPM_CHECKED=1", flush=True)
+    p = subprocess.run([sys.executable, "-c", SCHEDULE_CHILD, ROOT, str(tmp_path / "s_")], capture_output=True, text=True,
+                       env=env, timeout=300)
+    assert p.returncode == 0, p.stdout[-3000:] + p.stderr[-3000:]
+    r = json.loads([ln for ln in p.stdout.splitlines() if ln.startswith("RESULTS ")][-1][len("RESULTS "):])
+    B, N, D = 3, 300, 64
+    rng = np.random.default_rng(6)
+    cent = rng.standard_normal((3, 40, D))
+    x = np.stack([cent[b][rng.integers(0, 40, N)] for b in range(B)]) + 0.3 * rng.standard_normal((B, N, D))
+    x = torch.from_numpy(x.astype(np.float32)).to(torch.bfloat16).to("cuda:0")
+    for name, kw in (("dense", {}), ("window", dict(grid_w=20, window=2))):
+        assert r["valid_" + name] == [0, [True, True]]
+        assert r["nan_" + name] == [1, [False, False], True]
+        assert r["overflow_" + name] == [1, [True, False], True]
+        assert r["steps_" + name] == 1
+        s = api.Schedule(B, N, D, torch.bfloat16, insertions=2, device="cuda:0", **kw)
+        s.run(x)
+        torch.cuda.synchronize()
+        got = np.load(str(tmp_path / f"s_{name}.npz"))
+        assert np.array_equal(got["out"], s.out.view(torch.int16).cpu().numpy())
+        assert np.array_equal(got["rstar"], s.rstar.cpu().numpy())
