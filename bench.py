@@ -46,26 +46,28 @@ def log(*a):
 
 
 def kernel_source_hash() -> str:
-    """Hash of the affinity kernel's source, to tell whether stored counters still apply."""
-    p = os.path.join(ROOT, "paper_2604_05718_amd", "csrc", "affinity_argmax.hip")
-    return hashlib.sha256(open(p, "rb").read()).hexdigest()
+    """Hash of the affinity kernel's source and of the order its items are dealt in, to tell
+    whether stored counters still apply."""
+    h = hashlib.sha256()
+    for name in ("affinity_argmax.hip", "mpm_work.h"):
+        with open(os.path.join(ROOT, "paper_2604_05718_amd", "csrc", name), "rb") as f:
+            h.update(f.read())
+    return h.hexdigest()
 
 
-def executed_affinity_flops(cfg, counts, schedule, rows=None):
+def executed_affinity_flops(cfg, counts, plans):
     """Matrix-core flops each affinity launch issues: 2 * w^2 * D per w x w block,
     nb^2 blocks per image of nb = ceil(n / w) blocks under the full schedules,
-    nb (nb + 1) / 2 under the symmetric one (padding rows included). rows: w of each
-    insertion's launch (64: the full schedule, 128: the symmetric one), where the
-    library picks it; default the schedule's own."""
+    nb (nb + 1) / 2 under the symmetric one (padding rows included). plans: the
+    schedule and w of each insertion's launch (mpm.affinity_plan)."""
     out = []
     n_in = [cfg.N] * cfg.B
     for st in range(cfg.insertions):
-        w = rows[st] if rows is not None else 64 if schedule == "full_64" else 256
-        sym = schedule == "symmetric" if w == 256 else w == 128
+        schedule, w = plans[st]
         blocks = 0
         for n in n_in:
             nb = (n + w - 1) // w
-            blocks += nb * (nb + 1) // 2 if sym else nb * nb
+            blocks += nb * (nb + 1) // 2 if schedule == "symmetric" else nb * nb
         out.append(blocks * 2.0 * w * w * cfg.D)
         n_in = counts[st]
     return out
@@ -423,9 +425,8 @@ def main() -> int:
     if args.window is not None:
         rows = mpm.local_block_rows(cfg.B, cfg.N, cfg.D, dtype, cfg.G, args.window)
         schedule = f"window {args.window}, {rows}-row blocks"
-    rows = [mpm.affinity_block_rows(cfg.B, cfg.N, cfg.D, dtype, args.schedule, packed=st > 0)
-            for st in range(cfg.insertions)]
-    executed = executed_affinity_flops(cfg, counts, schedule, rows) if args.window is None else None
+    plans = [mpm.affinity_plan(cfg.B, cfg.N, cfg.D, dtype, args.schedule, packed=st > 0) for st in range(cfg.insertions)]
+    executed = executed_affinity_flops(cfg, counts, plans) if args.window is None else None
     kernels = []
     for name, ms, (kind, amount) in zip(names, per_kernel_ms, work):
         ent = {"name": name, "us": round(ms * 1e3, 2)}

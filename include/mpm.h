@@ -222,11 +222,11 @@ int mpm_affinity_compact(const void* x, const int32_t* x_off, const float* x_inv
  * device, written to *used (a host pointer). For reporting the matrix-core
  * work a call issues: about 2 * w^2 * D flops per w x w block, nb^2 blocks per
  * image of nb = ceil(n_b / w) blocks under the full schedules and nb (nb + 1) / 2
- * under the symmetric one, w = mpm_affinity_block_rows. A call with offsets may
- * pick another schedule than the one reported, that of a call without. Rows whose byte length is not a multiple of 64, for which the
- * argument is not taken, always report MPM_SCHEDULE_FULL. Returns MPM_OK, MPM_ERR_INVALID_ARG for bad sizes, an
- * unknown schedule or a NULL pointer, or MPM_ERR_HIP when the device cannot be
- * queried.
+ * under the symmetric one, w = mpm_affinity_block_rows. This is the schedule of a call
+ * without offsets, and MPM_SCHEDULE_FULL for rows whose byte length is not a multiple of
+ * 64, which do not take the argument; mpm_affinity_plan reports what any call runs.
+ * Returns MPM_OK, MPM_ERR_INVALID_ARG for bad sizes, an unknown schedule or a NULL
+ * pointer, or MPM_ERR_HIP when the device cannot be queried.
  */
 int mpm_affinity_schedule_used(int32_t B, int32_t N, int32_t D, int32_t dt, int32_t schedule, int32_t* used);
 
@@ -242,17 +242,34 @@ int mpm_affinity_block_rows(int32_t B, int32_t N, int32_t D, int32_t dt, int32_t
                             int32_t* rows);
 
 /*
+ * What mpm_affinity runs for such a call, rows of any width, without offsets (packed = 0)
+ * or with them: the schedule to *used (MPM_SCHEDULE_FULL, MPM_SCHEDULE_SYMMETRIC or
+ * MPM_SCHEDULE_FULL_64) and the rows of its square blocks to *rows, as
+ * mpm_affinity_block_rows. Returns as mpm_affinity_block_rows.
+ */
+int mpm_affinity_plan(int32_t B, int32_t N, int32_t D, int32_t dt, int32_t schedule, int32_t packed, int32_t* used,
+                      int32_t* rows);
+
+/*
  * The block size mpm_merge_local's affinity runs for this shape, window and requested
  * block_rows on the current device, written to *rows (a host pointer): 256 or 128
  * (square blocks on the symmetric schedule; with block_rows 0, whichever an estimate of
  * the launch on a full raster grid of grid_w columns, at this window, finds faster), or
- * N for rows whose byte length is not a multiple of 64 (the argument is not taken and
- * the library's pick not reported). For reporting. Returns MPM_OK, MPM_ERR_INVALID_ARG for bad
- * sizes, grid_w, window or block_rows (as mpm_merge_local) or a NULL pointer, or
- * MPM_ERR_HIP when the device cannot be queried.
+ * N for rows whose byte length is not a multiple of 64, which do not take the argument
+ * (mpm_local_tile_rows reports their blocks too). For reporting. Returns MPM_OK,
+ * MPM_ERR_INVALID_ARG for bad sizes, grid_w, window or block_rows (as mpm_merge_local) or
+ * a NULL pointer, or MPM_ERR_HIP when the device cannot be queried.
  */
 int mpm_local_block_rows(int32_t B, int32_t N, int32_t D, int32_t dt, int32_t grid_w, int32_t window,
                          int32_t block_rows, int32_t* rows);
+
+/*
+ * The rows of the square blocks mpm_merge_local's affinity runs, and the token width of one
+ * partial in its workspace, for rows of any width: 128 or 256. Otherwise as
+ * mpm_local_block_rows.
+ */
+int mpm_local_tile_rows(int32_t B, int32_t N, int32_t D, int32_t dt, int32_t grid_w, int32_t window,
+                        int32_t block_rows, int32_t* rows);
 
 /*
  * Nearest neighbours: mpm_affinity (norms summed in the kernel), then the

@@ -44,6 +44,10 @@ SIGNATURES = {
                                             _vp]),
     "mpm_affinity_schedule_used": (ctypes.c_int, [_i32, _i32, _i32, _i32, _i32, ctypes.POINTER(ctypes.c_int32)]),
     "mpm_affinity_block_rows": (ctypes.c_int, [_i32, _i32, _i32, _i32, _i32, _i32, ctypes.POINTER(ctypes.c_int32)]),
+    "mpm_affinity_plan": (ctypes.c_int, [_i32, _i32, _i32, _i32, _i32, _i32, ctypes.POINTER(ctypes.c_int32),
+                                         ctypes.POINTER(ctypes.c_int32)]),
+    "mpm_local_tile_rows": (ctypes.c_int, [_i32, _i32, _i32, _i32, _i32, _i32, _i32,
+                                           ctypes.POINTER(ctypes.c_int32)]),
     "mpm_local_block_rows": (ctypes.c_int, [_i32, _i32, _i32, _i32, _i32, _i32, _i32,
                                             ctypes.POINTER(ctypes.c_int32)]),
     "mpm_argmax": (ctypes.c_int, [_vp, _vp, _i32, _i32, _i32, _i32, _i32, _vp, _vp, _vp, _sz, _vp]),

@@ -143,7 +143,9 @@ SCHEDULES = {"auto": _lib.MPM_SCHEDULE_AUTO, "full": _lib.MPM_SCHEDULE_FULL, "sy
 
 def affinity_schedule_used(B: int, N: int, D: int, dtype: torch.dtype, schedule: str = "auto") -> str:
     """The schedule ("full", "symmetric" or "full_64") the affinity kernel runs for
-    this shape and requested schedule on the current device."""
+    this shape without offsets and requested schedule on the current device ("full" for rows
+    that are no whole number of 64 bytes, which do not take a schedule); affinity_plan
+    covers every call."""
     out = ctypes.c_int32()
     _lib.check("mpm_affinity_schedule_used",
                _lib.load().mpm_affinity_schedule_used(B, N, D, _DTYPES[dtype], _sched(schedule), ctypes.byref(out)))
@@ -160,11 +162,29 @@ def affinity_block_rows(B: int, N: int, D: int, dtype: torch.dtype, schedule: st
     return out.value
 
 
+def affinity_plan(B: int, N: int, D: int, dtype: torch.dtype, schedule: str = "auto", packed: bool = False) -> tuple:
+    """(schedule, block rows) the affinity runs for this shape, rows of any width, with
+    offsets (``packed``) or without, on the current device."""
+    used, rows = ctypes.c_int32(), ctypes.c_int32()
+    _lib.check("mpm_affinity_plan",
+               _lib.load().mpm_affinity_plan(B, N, D, _DTYPES[dtype], _sched(schedule), int(packed), ctypes.byref(used),
+                                             ctypes.byref(rows)))
+    return {v: k for k, v in SCHEDULES.items()}[used.value], rows.value
+
+
+def local_tile_rows(B: int, N: int, D: int, dtype: torch.dtype, grid_w: int, window: int, block_rows: int = 0) -> int:
+    """Rows of the square blocks merge_local's affinity runs for rows of any width (128 or 256)."""
+    out = ctypes.c_int32()
+    _lib.check("mpm_local_tile_rows", _lib.load().mpm_local_tile_rows(B, N, D, _DTYPES[dtype], int(grid_w), int(window),
+                                                                      int(block_rows), ctypes.byref(out)))
+    return out.value
+
+
 def local_block_rows(B: int, N: int, D: int, dtype: torch.dtype, grid_w: int, window: int,
                      block_rows: int = 0) -> int:
     """Rows of the square blocks merge_local's affinity runs for this shape, window and
     requested block_rows (0: the library's pick) on the current device (256 or 128; N
-    for rows the persistent kernel does not take)."""
+    for rows that do not take the argument, whose blocks local_tile_rows reports)."""
     out = ctypes.c_int32()
     _lib.check("mpm_local_block_rows", _lib.load().mpm_local_block_rows(B, N, D, _DTYPES[dtype], int(grid_w),
                                                                         int(window), int(block_rows),

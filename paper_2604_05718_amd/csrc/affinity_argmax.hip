@@ -1399,18 +1399,22 @@ int partial_tile_width(int B, int D, int dt, int N, int schedule, bool packed)
     return block_rows(pick_blocks(B, N, D, dt, schedule, packed, device_cus()));
 }
 
+hipError_t affinity_plan(int B, int N, int D, int dt, int schedule, bool packed, int* used, int* rows)
+{
+    const int cus = device_cus();
+    if (cus <= 0) return hipErrorInvalidDevice;
+    const Blocks k = pick_blocks(B, N, D, dt, schedule, packed, cus);
+    *used = k == kBlocks64 ? kScheduleFull64 : k == kBlocks256 ? kScheduleFull : kScheduleSymmetric;
+    *rows = block_rows(k);
+    return hipSuccess;
+}
+
 hipError_t affinity_schedule(int B, int N, int D, int dt, int schedule, int* used)
 {
     *used = kScheduleFull;
     if (!whole_64(D, dt)) return hipSuccess;  // no choice of schedule
-    const int cus = device_cus();
-    if (cus <= 0) return hipErrorInvalidDevice;
-    switch (pick_blocks(B, N, D, dt, schedule, false, cus)) {
-    case kBlocks64: *used = kScheduleFull64; break;
-    case kBlocks256: *used = kScheduleFull; break;
-    default: *used = kScheduleSymmetric; break;
-    }
-    return hipSuccess;
+    int rows = 0;
+    return affinity_plan(B, N, D, dt, schedule, false, used, &rows);
 }
 
 hipError_t launch_affinity(const void* x, const int32_t* x_off, int B, int N, int D, int dt, int schedule, float* pv,

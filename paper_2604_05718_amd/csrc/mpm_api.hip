@@ -422,6 +422,34 @@ int mpm_affinity_block_rows(int32_t B, int32_t N, int32_t D, int32_t dt, int32_t
     return st;
 }
 
+int mpm_affinity_plan(int32_t B, int32_t N, int32_t D, int32_t dt, int32_t schedule, int32_t packed, int32_t* used,
+                      int32_t* rows)
+{
+    const int s = check_rows(B, N, D, dt);
+    if (s != MPM_OK) return s;
+    if (!used || !rows || !mpm::valid_schedule(schedule)) return MPM_ERR_INVALID_ARG;
+    int sc = 0, w = 0;
+    const int st = hip_status(mpm::affinity_plan(B, N, D, dt, schedule, packed != 0, &sc, &w));
+    if (st == MPM_OK) {
+        *used = sc;
+        *rows = w;
+    }
+    return st;
+}
+
+int mpm_local_tile_rows(int32_t B, int32_t N, int32_t D, int32_t dt, int32_t grid_w, int32_t window,
+                        int32_t block_rows, int32_t* rows)
+{
+    const int s = check_rows(B, N, D, dt);
+    if (s != MPM_OK) return s;
+    if (!rows || grid_w < 1 || grid_w > MPM_MAX_N || window < 0 || !mpm::valid_local_block_rows(block_rows))
+        return MPM_ERR_INVALID_ARG;
+    int dev = 0;
+    const int st = hip_status(hipGetDevice(&dev));
+    if (st == MPM_OK) *rows = mpm::local_tile_width(B, N, D, dt, grid_w, window, block_rows);
+    return st;
+}
+
 int mpm_local_block_rows(int32_t B, int32_t N, int32_t D, int32_t dt, int32_t grid_w, int32_t window,
                          int32_t block_rows, int32_t* rows)
 {

@@ -48,8 +48,11 @@ int local_block_rows(int B, int N, int D, int dt, int grid_w, int radius, int re
 bool valid_local_block_rows(int requested);
 int local_tile_width(int B, int N, int D, int dt, int grid_w, int radius, int requested);
 // The schedule (kScheduleFull, kScheduleSymmetric or kScheduleFull64) launch_affinity runs
-// for this shape and requested schedule on the current device.
+// for this shape without offsets and requested schedule on the current device (kScheduleFull
+// for rows that do not take the argument).
 hipError_t affinity_schedule(int B, int N, int D, int dt, int schedule, int* used);
+// ... and its block rows, for rows of any width, without offsets or with them (packed).
+hipError_t affinity_plan(int B, int N, int D, int dt, int schedule, bool packed, int* used, int* rows);
 
 hipError_t launch_reduce_partials(const float* pv, const int32_t* pi, int ct, const void* x, const int32_t* x_off,
                                   int B, int N, int D, int dt, int32_t* nb, float* best, hipStream_t stream);

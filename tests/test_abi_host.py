@@ -246,3 +246,20 @@ def test_run_schedule_rejects(lib):
     with_pos = ok[:3] + [0x50000, 0x40000, far]
     assert call(with_pos, 1, window=2, grid_w=0) == 1
     assert call(with_pos, 1, window=2, grid_w=8, block_rows=64) == 1
+
+
+def test_plan_queries_reject(lib):
+    """The queries of what a call runs reject bad arguments without writing their outputs."""
+    used, rows = ctypes.c_int32(-7), ctypes.c_int32(-7)
+    u, r = ctypes.byref(used), ctypes.byref(rows)
+    assert lib.mpm_affinity_plan(0, 1024, 768, 1, AUTO, 0, u, r) == 1
+    assert lib.mpm_affinity_plan(64, 16385, 768, 1, AUTO, 0, u, r) == 2
+    assert lib.mpm_affinity_plan(64, 1024, 767, 1, AUTO, 0, u, r) == 1
+    assert lib.mpm_affinity_plan(64, 1024, 768, 1, 9, 1, u, r) == 1
+    assert lib.mpm_affinity_plan(64, 1024, 768, 1, AUTO, 1, None, r) == 1
+    assert lib.mpm_affinity_plan(64, 1024, 768, 1, AUTO, 1, u, None) == 1
+    assert lib.mpm_local_tile_rows(2, 64, 40, 1, 0, 1, 0, r) == 1
+    assert lib.mpm_local_tile_rows(2, 64, 40, 1, 8, -1, 0, r) == 1
+    assert lib.mpm_local_tile_rows(2, 64, 40, 1, 8, 1, 64, r) == 1
+    assert lib.mpm_local_tile_rows(2, 64, 40, 1, 8, 1, 0, None) == 1
+    assert used.value == rows.value == -7

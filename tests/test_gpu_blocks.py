@@ -373,3 +373,38 @@ def test_pick_of_large_batches(B, N, D, packed, used):
     o = off.cpu().numpy()
     for b in (0, B - 1):
         check_nearest(to64(x[o[b]:o[b + 1]].cpu()), nb[b, :ns[b]].cpu().numpy())
+
+
+def test_plans_are_what_runs():
+    """affinity_plan agrees with the older queries where they apply, and with the partials a
+    call leaves: exactly the slots of its block rows are written, full or symmetric; the same
+    for the windowed blocks of any row width."""
+    from paper_2604_05718_amd import _lib
+
+    rng = np.random.default_rng(3)
+    shapes = [(1, 700, 64, "bf16"), (9, 900, 192, "bf16"), (64, 1024, 72, "bf16"), (16, 1024, 40, "bf16"),
+              (30, 1000, 52, "f32"), (64, 1024, 64, "bf16"), (3, 300, 24, "bf16")]
+    for B, N, D, dtype in shapes:
+        for packed in (False, True):
+            dt = TORCH_DT[dtype]
+            used, rows = mpm.affinity_plan(B, N, D, dt, packed=packed)
+            print(f"plan B={B} N={N} D={D} {dtype} packed={packed}: {used} {rows}", flush=True)
+            assert rows == mpm.affinity_block_rows(B, N, D, dt, packed=packed)
+            assert (used == "full_64") == (rows == 64) and (rows != 128 or used == "symmetric")
+            if D * (2 if dtype == "bf16" else 4) % 64 == 0:
+                if not packed:
+                    assert used == mpm.affinity_schedule_used(B, N, D, dt)
+                for s in ("full", "symmetric", "full_64"):
+                    assert mpm.affinity_plan(B, N, D, dt, s, packed)[0] == s
+            x = store(clustered(rng, B * N, D, k=50), dtype).to(DEV)
+            off = torch.arange(0, (B + 1) * N, N, dtype=torch.int32, device=DEV) if packed else None
+            ws = torch.full((mpm.workspace_bytes(B, N),), 0x5A, dtype=torch.uint8, device=DEV)
+            mpm.affinity(x if packed else x.view(B, N, D), off, N, ws=ws)
+            wl = torch.full_like(ws, 0x5A)
+            mpm.merge_local(x if packed else x.view(B, N, D), 32, 3, x_off=off, N=N if packed else None, ws=wl)
+            torch.cuda.synchronize()
+            o, T = _lib.workspace_offsets(B, N), (N + 63) // 64
+            for w, width in ((ws, rows), (wl, mpm.local_tile_rows(B, N, D, dt, 32, 3))):
+                pi = w[o["pi"]:o["pi"] + 4 * B * T * N].view(torch.int32).view(B, T, N)
+                tiles = (N + width - 1) // width
+                assert not bool((pi[:, :tiles] == 0x5A5A5A5A).any()) and bool((pi[:, tiles:] == 0x5A5A5A5A).all())
