@@ -245,13 +245,14 @@ __device__ __forceinline__ void exchange_half(float* v, int32_t* ix, int upper)
 // reverse direction, so the two halves write disjoint query partials, and each score
 // comes from the same MFMA sequence as in a whole block.
 //
-// LOCAL: the locality constraint of Sec. 5 on the full schedule. A work item is a query
-// block with every candidate tile its window band reaches ([tlo, thi], found from the
-// positions at the block and tile boundaries); the item
-// runs its tiles one after the other through the same ring (one K loop per tile), keeps
-// each query's running best across them in registers, masks every score by the window
-// test, and writes one partial per query (tile slot 0, tile width N). Positions (win.pos,
-// null: the token's index) are fetched per tile while its K loop runs, as given norms are.
+// LOCAL: the locality constraint of Sec. 5, on the symmetric schedule. A work item is a query
+// block with the candidate tiles its window band reaches from its own on ([tlo, thi] is the
+// whole band, found from the positions at the block and tile boundaries); the item runs them
+// one after the other through the same ring (one K loop per tile), keeps each query's running
+// best across them in registers, sets scores outside the window to -inf, and writes one partial
+// per query (the block's own tile slot) beside the reverse direction's of each tile; the slots
+// no item writes for the block's rows hold -inf. Positions (win.pos, null: the token's index)
+// are fetched per tile while its K loop runs, as given norms are.
 //
 // GIVEN (bfloat16 rows only): xinv holds the inverse row norms 1 / max(||x_j||, 1e-12),
 // one float per row packed like x, which the kernel then takes instead of summing them
@@ -293,8 +294,8 @@ __global__ __launch_bounds__(WC * WQ * kWave, 2) void affinity_partial_kernel(  
     // LOCAL: grid row [0] and column [1] of the item's candidates (0 .. CT-1) and queries (CT ..).
     __shared__ __attribute__((aligned(16))) int32_t win_rc[2][LOCAL ? CT + QT : 1];
     __shared__ int32_t win_pos[LOCAL ? CT + QT : 1];  // ... their positions as given
-    static_assert(!LOCAL || (!HALVES && QT == CT && CT + QT <= WC * WQ * kWave),
-                  "window items: square blocks, one position per thread");
+    static_assert(!LOCAL || (SYM && !HALVES && QT == CT && CT + QT <= WC * WQ * kWave),
+                  "window items: symmetric, square blocks, one position per thread");
     static_assert(!SYM || QT == CT, "the symmetric schedule pairs equal blocks");
     static_assert(!GIVEN || S::kBytes == 2, "given norms: bfloat16 rows");
     constexpr bool given = GIVEN;
@@ -389,7 +390,7 @@ __global__ __launch_bounds__(WC * WQ * kWave, 2) void affinity_partial_kernel(  
                     while (thi > tlo && grid_row(thi * CT) > r_last + win.radius) --thi;
                     // The symmetric schedule starts at the block's own tile: the tiles before
                     // it reach this block through their own items' reverse direction.
-                    it.cbase = (SYM ? t : tlo) * CT;
+                    it.cbase = t * CT;
                     it.tlo = tlo;
                     it.thi = thi;
                 }
@@ -796,7 +797,7 @@ __global__ __launch_bounds__(WC * WQ * kWave, 2) void affinity_partial_kernel(  
         const uint32_t wspan = 2u * (uint32_t)win.radius;
         // This lane's own row inside a 32-row tile, as an accumulator element (if it holds it).
         const int self_r = (((lrow >> 2) & 1) == khalf) ? 4 * (lrow >> 3) + (lrow & 3) : -1;
-        if constexpr (LOCAL && SYM) {
+        if constexpr (LOCAL) {
             // Both directions read the accumulators: pairs outside the window become -inf
             // there (the inverse norms that scale them are positive).
 #pragma unroll
@@ -843,20 +844,6 @@ __global__ __launch_bounds__(WC * WQ * kWave, 2) void affinity_partial_kernel(  
                     if (diag && wc * MT + mp + m == self_tile0 + wq * NT + nt) {  // the tile holding each lane's own query
 #pragma unroll
                         for (int r = 0; r < 16; ++r) sc[16 * m + r] = r == self_r ? -__builtin_inff() : sc[16 * m + r];
-                    }
-                }
-                if constexpr (LOCAL && !SYM) {
-#pragma unroll
-                    for (int g = 0; g < GR; ++g) {
-                        const int jl = wc * MT * 32 + mp * 32 + 8 * g + 4 * khalf;
-                        const int4 cr = *reinterpret_cast<const int4*>(&win_rc[0][jl]);
-                        const int4 cc = *reinterpret_cast<const int4*>(&win_rc[1][jl]);
-                        const int crv[4] = {cr.x, cr.y, cr.z, cr.w}, ccv[4] = {cc.x, cc.y, cc.z, cc.w};
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) {
-                            const bool in = (uint32_t)(crv[e] - q_r[nt]) <= wspan && (uint32_t)(ccv[e] - q_c[nt]) <= wspan;
-                            sc[4 * g + e] = in ? sc[4 * g + e] : -__builtin_inff();
-                        }
                     }
                 }
                 // The best of each group of four, then of the groups, by value alone; then the first
