@@ -7,6 +7,7 @@ import torch
 import oracle
 import paper_2604_05718_amd as mpm
 from parity import check_nearest, check_stage, to64
+from work_shares import deferred
 
 pytestmark = pytest.mark.gpu
 
@@ -60,16 +61,17 @@ def test_rows_of_any_width(dtype, D):
     check_merge(imgs, dtype, m)
 
 
-# Batches whose automatic pick is each block shape, with images that end at, before and
-# past a block, several images per XCD share or several shares per image, empty images.
+# Images that end at, before and past a block, several images per XCD share or several shares
+# per image, empty images: (values a row, sizes, block rows picked for bf16 and f32 on 256 CUs).
 WORK_CASES = {
-    "one_image_128": (64, [1500]),
-    "three_images_128": (64, [1024, 129, 897]),
-    "uneven_shares": (64, [300, 0, 513, 256, 1, 128, 640, 257, 384, 0, 511, 127]),
-    "many_small": (64, [65, 64, 1, 0, 63, 2] * 20),
-    "counted_limit": (32, [130, 1] * 256),          # 512 images, the most counted one by one
-    "past_counted_limit": (32, [130, 1] * 256 + [40]),
-    "long_and_short": (64, [2300] + [30] * 9 + [1700]),
+    "one_image": (64, [1500], (64, 64)),
+    "three_images": (64, [1024, 129, 897], (128, 64)),
+    "uneven_shares": (64, [300, 0, 513, 256, 1, 128, 640, 257, 384, 0, 511, 127], (128, 64)),
+    "many_small": (64, [65, 64, 1, 0, 63, 2] * 20, (64, 64)),
+    "counted_limit": (32, [130, 1] * 256, (128, 128)),          # 512 images, the most counted one by one
+    "past_counted_limit": (32, [130, 1] * 256 + [40], (128, 128)),
+    "long_and_short": (64, [2300] + [30] * 9 + [1700], (128, 128)),
+    "large_blocks": (32, [2300, 2000, 256, 0, 1, 1900, 2299, 2048] * 8, (256, 256)),
 }
 
 
@@ -79,10 +81,12 @@ def test_work_distribution(dtype, name):
     """Ragged packed batches on the automatic pick, dense or packed, equal those on the
     forced full schedule: same neighbours, maps and merged rows; sampled images against
     the oracle."""
-    D, ns = WORK_CASES[name]
+    D, ns, picks = WORK_CASES[name]
     rng = np.random.default_rng(len(ns) + D)
-    print(f"work distribution {name} {dtype}: rows {mpm.affinity_block_rows(len(ns), max(ns), D, TORCH_DT[dtype], packed=True)}",
-          flush=True)
+    rows = mpm.affinity_block_rows(len(ns), max(ns), D, TORCH_DT[dtype], packed=True)
+    print(f"work distribution {name} {dtype}: rows {rows}", flush=True)
+    if torch.cuda.get_device_properties(DEV).multi_processor_count == 256:
+        assert rows == picks[dtype == "f32"]
     imgs = [store(clustered(rng, n, D, k=max(1, n // 6)), dtype) for n in ns]
     x, off, N = packed(imgs)
     m = mpm.merge(x, off, N=N)
@@ -408,3 +412,65 @@ def test_plans_are_what_runs():
                 pi = w[o["pi"]:o["pi"] + 4 * B * T * N].view(torch.int32).view(B, T, N)
                 tiles = (N + width - 1) // width
                 assert not bool((pi[:, :tiles] == 0x5A5A5A5A).any()) and bool((pi[:, tiles:] == 0x5A5A5A5A).all())
+
+
+# Rows that are no whole number of 64 bytes cannot have a schedule forced: batches whose pick is
+# each kind of 256-row block, dense and packed, with deferred diagonal blocks and without, images
+# counted one by one and not.
+@pytest.mark.parametrize("dtype,B,N,D,packed,plan,halves",
+                         [("bf16", 64, 1024, 200, False, ("symmetric", 256), True),
+                          ("bf16", 16, 1024, 200, False, ("full", 256), False),
+                          ("f32", 46, 1924, 212, False, ("symmetric", 256), True),
+                          ("bf16", 16, 1024, 136, True, ("full", 256), False),
+                          ("bf16", 500, 200, 56, True, ("full", 256), False),
+                          ("bf16", 64, 2300, 200, True, ("symmetric", 256), True),
+                          ("f32", 100, 1500, 12, True, ("symmetric", 256), True)])
+def test_large_blocks_of_odd_rows(dtype, B, N, D, packed, plan, halves):
+    for seed in range(50):  # the first ragged lengths that leave blocks to the half-block launch
+        rng = np.random.default_rng(B * D + seed)
+        ns = [int(v) for v in rng.integers(int(0.55 * N), N + 1, B)] if packed else [N] * B
+        if packed:
+            ns[0], ns[B // 2], ns[-1] = 0, N, 1
+        if not halves or any(deferred(ns)):
+            break
+    print(f"large blocks of odd rows {dtype} B={B} N={N} D={D} packed={packed}", flush=True)
+    if torch.cuda.get_device_properties(DEV).multi_processor_count == 256:
+        assert mpm.affinity_plan(B, N, D, TORCH_DT[dtype], packed=packed) == plan
+    if plan[0] == "symmetric":
+        assert any(deferred(ns)) == halves
+    g = torch.Generator(device=DEV).manual_seed(B + D)
+    cent = torch.randn((200, D), generator=g, device=DEV)
+    x = cent[torch.randint(0, 200, (sum(ns),), generator=g, device=DEV)]
+    x = (x + 0.3 * torch.randn((sum(ns), D), generator=g, device=DEV)).to(TORCH_DT[dtype])
+    o = np.concatenate([[0], np.cumsum(ns)]).astype(np.int32)
+    off = torch.from_numpy(o).to(DEV)
+    m = mpm.merge(x, off, N=N) if packed else mpm.merge(x.view(B, N, D))
+    # Image by image: the small blocks, whatever the batch runs.
+    nb = m.nb
+    sample = sorted({1, 2, B // 4, B // 2, B - 2} | set(rng.integers(0, B, 6).tolist()))
+    for b in sample:
+        if ns[b] == 0:
+            continue
+        img = x[o[b]:o[b + 1]].contiguous()
+        one = mpm.argmax(img[None])
+        torch.cuda.synchronize()
+        assert torch.equal(nb[b, :ns[b]], one[0]), b
+    for b in (1, B // 2):
+        check_nearest(to64(x[o[b]:o[b + 1]].cpu()), nb[b, :ns[b]].cpu().numpy())
+
+
+@pytest.mark.parametrize("B,N,D", [(64, 1024, 96), (300, 400, 32), (20, 700, 224)])
+def test_given_norms_of_half_chunks(B, N, D):
+    """Two insertions on rows that end inside a chunk, the second on given norms and counted
+    ragged images: neighbours, maps and merged rows of sampled images against the oracle."""
+    rng = np.random.default_rng(N + D)
+    print(f"given norms of half chunks B={B} N={N} D={D}", flush=True)
+    x = torch.stack([store(clustered(rng, N, D, k=40), "bf16") for _ in range(B)])
+    m1 = mpm.merge(x.to(DEV), want_inv=True)
+    m2 = mpm.merge(m1.y, m1.y_off, N=N, x_inv=m1.y_inv)
+    torch.cuda.synchronize()
+    o1, o2 = m1.y_off.cpu().numpy(), m2.y_off.cpu().numpy()
+    for b in sorted({0, 7, B // 2, B - 1}):
+        y1 = to64(m1.y[o1[b]:o1[b + 1]].cpu())
+        s1 = check_stage(to64(x[b]), "bf16", m1.nb[b].cpu().numpy(), m1.map[b].cpu().numpy(), y1)
+        check_stage(y1, "bf16", m2.nb[b, :s1.count].cpu().numpy(), m2.map[b].cpu().numpy(), to64(m2.y[o2[b]:o2[b + 1]].cpu()))

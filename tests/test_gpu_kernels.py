@@ -11,6 +11,7 @@ import oracle
 import paper_2604_05718_amd as mpm
 from golden_io import all_merge_cases, load
 from parity import check_nearest, check_schedule_image, check_stage, rel_err, to64
+from work_shares import deferred
 
 pytestmark = pytest.mark.gpu
 
@@ -506,7 +507,7 @@ def _sym_case(name, dtype):
     rng = np.random.default_rng(zlib.crc32(name.encode()))
     if name == "dense_777":
         return [store(clustered(rng, 777, 128, k=30), dtype) for _ in range(3)], 777, 128
-    if name == "rows_192_bytes":  # bf16 rows of 192 bytes: the 64-byte-chunk, four-stage pipeline
+    if name == "rows_192_bytes":  # bf16 rows of 192 bytes: the second chunk is half a chunk
         return [store(clustered(rng, 777, 96, k=30), dtype) for _ in range(3)], 777, 96
     if name == "duplicated_rows":  # every token twice: exact ties in both directions
         imgs = []
@@ -520,15 +521,16 @@ def _sym_case(name, dtype):
         ns = [1, 256, 257, 512, 513, 1000, 3, 700]
         return [store(clustered(rng, n, 64, k=25), dtype) for n in ns], 1000, 64
     if name == "deferred_diagonals":
-        # 90 images on 8 XCD groups of 32 slots: groups of 12 images (120 blocks) take whole
-        # rounds only with a last round of 24; groups of 11 (110 blocks) defer 14 diagonal
-        # blocks (all of 3 images', 2 of a fourth) to the half-block second launch.
+        # 90 images, 900 blocks on 8 XCD groups of 32 slots: the groups of 112 blocks defer 16
+        # diagonal blocks (all of 4 images') to the half-block second launch, those of 113 none.
+        assert sorted(set(deferred([1024] * 90))) == [0, 16]
         return [store(clustered(rng, 1024, 64, k=25), dtype) for _ in range(90)], 1024, 64
     if name == "deferred_packed":
-        # 88 ragged images (deferred half blocks past an image's end are skipped), every
-        # fourth one made of duplicated rows (exact ties inside the half blocks).
+        # 88 ragged images, every fourth one made of duplicated rows (exact ties inside the
+        # half blocks).
         sizes = [1024, 1000, 769, 768, 513, 256, 1, 900]
         imgs = []
+        assert all(deferred([sizes[b % len(sizes)] for b in range(88)]))
         for b in range(88):
             n = sizes[b % len(sizes)]
             if b % 4 == 3 and n > 1:
@@ -690,8 +692,9 @@ def test_small_blocks_equal_full_schedule(dtype, name):
 
 
 def test_small_blocks_chosen_for_small_batches():
-    """Auto mode takes the 64 x 64 blocks when a batch has at most 32 blocks of
-    256 x 256 (rows a multiple of 64 bytes), and the large blocks otherwise."""
+    """Auto mode takes the 64 x 64 blocks for one image of 1024 tokens and for two of
+    1536-byte rows, larger blocks for more; rows that are no whole number of 64 bytes
+    have no schedule to choose."""
     assert mpm.affinity_schedule_used(1, 1024, 192, torch.float32) == "full_64"
     assert mpm.affinity_schedule_used(2, 1024, 768, torch.bfloat16) == "full_64"
     assert mpm.affinity_schedule_used(3, 1024, 768, torch.bfloat16) != "full_64"
@@ -914,9 +917,9 @@ EMPTY_CASES = {  # (D, dtype, schedule, image sizes)
     "persistent_bf16_full": (64, "bf16", "full", _EMPTY_SIZES),
     "persistent_bf16_symmetric": (64, "bf16", "symmetric", _EMPTY_SIZES),
     "persistent_f32": (32, "f32", "auto", _EMPTY_SIZES),
-    "staged_bf16": (24, "bf16", "auto", _EMPTY_SIZES),                   # 48-byte rows
+    "staged_bf16": (24, "bf16", "auto", _EMPTY_SIZES),                   # 48-byte rows: half a chunk
     "small_blocks": (64, "bf16", "full_64", [0, 700, 0]),
-    "symmetric_deferred": (64, "bf16", "symmetric", [0, 1024, 700, 0, 1, 1024] * 15),  # the half-block launch
+    "symmetric_deferred": (64, "bf16", "symmetric", [0, 1024, 700, 0, 1, 1024] * 14),  # the half-block launch
 }
 
 
@@ -929,6 +932,8 @@ def test_empty_images(case):
     D, dtype, schedule, ns = EMPTY_CASES[case]
     rng = np.random.default_rng(zlib.crc32(("empty-" + case).encode()))
     N = max(ns)
+    if case == "symmetric_deferred":  # every group leaves diagonal blocks to it
+        assert all(deferred(ns))
     imgs = [store(clustered(rng, n, D, k=max(1, n // 8)), dtype) for n in ns]
     x = torch.cat(imgs).to(DEV)
     off = torch.tensor(np.concatenate([[0], np.cumsum(ns)]), dtype=torch.int32, device=DEV)
@@ -987,9 +992,9 @@ def _step_case(name):
         return [store(clustered(rng, 700, 64, k=20), "f32") for _ in range(20)], 700, 64, "f32", "full", False
     if name == "full_64_one_image":
         return [store(clustered(rng, 1024, 64, k=12), "f32")], 1024, 64, "f32", "full_64", False
-    if name == "rows_48_bytes":  # bf16 rows of 48 bytes: the staged kernel (one partial per token)
+    if name == "rows_48_bytes":  # bf16 rows of 48 bytes: half a chunk, its last column zeroed
         return [store(clustered(rng, 300, 24, k=10), "bf16") for _ in range(3)], 300, 24, "bf16", "auto", False
-    if name == "rows_192_bytes":  # the 64-byte-chunk ring
+    if name == "rows_192_bytes":  # the second chunk is half a chunk
         return [store(clustered(rng, 777, 96, k=30), "bf16") for _ in range(12)], 777, 96, "bf16", "symmetric", False
     if name == "many_images":  # 20000 images of 4 tokens: the images-done counter runs to 20000
         return [store(rng.standard_normal((4, 32)), "bf16") for _ in range(20000)], 4, 32, "bf16", "auto", False

@@ -89,7 +89,7 @@ def test_window_hand_case_on_gpu(dtype):
 CASES = [  # (grid rows, grid cols, D, window, images)
     (5, 7, 64, 1, 3), (16, 16, 128, 2, 4), (17, 31, 96, 3, 2), (32, 32, 192, 0, 2), (20, 24, 64, 30, 2),
     (40, 40, 256, 4, 3),
-    # rows that are not a whole number of 64 bytes (bf16 80, f32 160): the register-staged kernel
+    # rows that are not a whole number of 64 bytes (bf16 80, f32 160): block_rows is not taken
     (12, 9, 40, 2, 2),
     # eight images or more: the persistent kernel's per-XCD image groups
     (24, 24, 64, 3, 9)]
@@ -101,8 +101,8 @@ CASES = [  # (grid rows, grid cols, D, window, images)
 def test_local_schedule_random_grids(dtype, gh, gw, D, window, B, block_rows):
     """Two windowed insertions on clustered tokens (the second on the ragged packed
     survivors and their carried positions), composition and gather, every image
-    checked, with either block size of the persistent kernel (rows that are not a
-    whole number of 64 bytes take the register-staged kernel either way); window 0
+    checked, with either block size (rows that are not a whole number of 64 bytes
+    run the library's pick either way); window 0
     leaves every token alone, a window covering the grid is the dense method."""
     rng = np.random.default_rng(gh * 1000 + gw * 10 + window)
     N = gh * gw
@@ -250,7 +250,7 @@ def test_local_block_choice():
         pytest.skip("the picks below are for a 256-CU device")
     assert picks == {("vit_l_1024", 4): 256, ("vit_l_1024", 2): 128, ("vit_b_512", 3): 128, ("stress_768", 4): 128}
     assert mpm.local_block_rows(16, 4096, 1024, torch.bfloat16, 64, 4, block_rows=128) == 128
-    assert mpm.local_block_rows(16, 4096, 40, torch.bfloat16, 64, 4) == 4096   # 80-byte rows: the staged kernel
+    assert mpm.local_block_rows(16, 4096, 40, torch.bfloat16, 64, 4) == 4096   # 80-byte rows: the argument is not taken
 
 
 @pytest.mark.parametrize("block_rows", [128, 256])
@@ -274,3 +274,54 @@ def test_largest_windows_are_dense(block_rows):
         for r in (m, p):
             assert torch.equal(r.y_off, dense.y_off) and torch.equal(r.map, dense.map)
             assert torch.equal(r.y[:total].view(torch.int16), dense.y[:total].view(torch.int16))
+
+
+# Rows that end inside a chunk: 256- and 128-row blocks (the library's picks), both types; and
+# packed batches of more blocks than slots, images counted one by one, empty ones among them.
+@pytest.mark.parametrize("dtype,B,gh,gw,D,window,rows", [("bf16", 16, 64, 64, 40, 4, 256), ("f32", 16, 64, 64, 36, 2, 128),
+                                                         ("bf16", 4, 64, 64, 72, 8, 128)])
+def test_local_rows_of_any_width(dtype, B, gh, gw, D, window, rows):
+    N = gh * gw
+    rng = np.random.default_rng(D + N)
+    cent = rng.standard_normal((B, 12, D))
+    x = torch.stack([store(cent[b][rng.integers(0, 12, N)] + 0.3 * rng.standard_normal((N, D)), dtype) for b in range(B)])
+    if torch.cuda.get_device_properties(DEV).multi_processor_count == 256:
+        assert mpm.local_tile_rows(B, N, D, TORCH_DT[dtype], gw, window) == rows
+    print(f"local rows of any width {dtype} D={D} B={B} window={window}", flush=True)
+    res = mpm.run_schedule(x.to(DEV), insertions=2, grid_w=gw, window=window)
+    torch.cuda.synchronize()
+    for b in sorted({0, B // 2, B - 1}):
+        check_local_schedule_image(x[b], dtype, res, b, gw, window)
+
+
+@pytest.mark.parametrize("dtype,D", [("bf16", 40), ("f32", 20), ("bf16", 64)])
+def test_local_counted_packed(dtype, D):
+    """More blocks than slots (520 or more of 128 rows): images ending inside a grid row and a
+    block, empty and one-token ones, at either end of a group's share."""
+    rng = np.random.default_rng(D)
+    gw, window = 20, 2
+    ns = [int(v) for v in rng.integers(0, 400, 330)]
+    ns[0], ns[1], ns[-1], ns[164], ns[165] = 0, 400, 1, 0, 129
+    N = max(ns)
+    assert sum(-(-n // 128) for n in ns) > 512
+    print(f"local counted packed {dtype} D={D}: {len(ns)} images", flush=True)
+    x64 = [oracle.round_to(rng.standard_normal((n, D)), dtype) for n in ns]
+    off = np.concatenate([[0], np.cumsum(ns)]).astype(np.int32)
+    res = mpm.merge_local(store(np.concatenate(x64), dtype).to(DEV), gw, window, x_off=torch.from_numpy(off).to(DEV), N=N,
+                          block_rows=128 if D == 64 else 0)
+    torch.cuda.synchronize()
+    nbs, maps, y_off = res.nb.cpu().numpy(), res.map.cpu().numpy(), res.y_off.cpu().numpy()
+    for b, n in enumerate(ns):
+        if n == 0:
+            assert y_off[b + 1] == y_off[b] and np.all(maps[b] == -1)
+            continue
+        p = np.arange(n, dtype=np.int32)
+        nn = oracle.nearest(x64[b], pos=p, grid_w=gw, window=window)
+        empty = nn.nb < 0
+        assert np.array_equal(nbs[b, :n][empty], nn.nb[empty]), b
+        with np.errstate(invalid="ignore"):
+            gap = nn.top1 - nn.top2
+        for i in np.flatnonzero((nbs[b, :n] != nn.nb) & ~empty):
+            assert gap[i] < 1e-5 and oracle.cosine(x64[b], int(i), int(nbs[b, i])) >= nn.top1[i] - 1e-5, (b, i)
+        ref = oracle.merge(x64[b], dtype, nb=nbs[b, :n], pos=p, grid_w=gw, window=window)
+        assert np.array_equal(maps[b, :n], ref.map) and y_off[b + 1] - y_off[b] == ref.count, b

@@ -112,8 +112,8 @@ int main()
 """
 
 
-def _run(tmp_path, text):
-    """The driver's output (it counts the batches it checked)."""
+def _run(tmp_path, text, result=int):
+    """The driver's output (the number of batches it checked)."""
     if shutil.which("g++") is None:
         pytest.skip("no host compiler")
     src = tmp_path / "work.cpp"
@@ -124,7 +124,7 @@ def _run(tmp_path, text):
                     str(src), "-o", str(exe)], check=True)
     r = subprocess.run([str(exe)], capture_output=True, text=True)
     assert r.returncode == 0, r.stdout + r.stderr
-    return int(r.stdout)
+    return result(r.stdout)
 
 
 def test_every_block_exactly_once(tmp_path):
@@ -172,6 +172,49 @@ int main()
     return 0;
 }
 """
+
+
+SHARES_MAIN = r"""
+int main()
+{
+    const int rows = 256, slots = 32;
+    std::mt19937 rng(11);
+    for (int k = 0; k < 60; ++k) {
+        const int B = 1 + (int)(rng() % 120);
+        std::vector<int> n(B);
+        for (int& v : n) v = (int)(rng() % 4 == 0 ? 0 : rng() % 1400);
+        std::vector<int32_t> items(B + 1, 0), diags(B + 1, 0);
+        const WorkShape shape(kOrderSymmetric, B, 6);
+        for (int i = 0; i < B; ++i) {
+            const int nb = (n[work_place(i, shape.run)] + rows - 1) / rows;
+            items[i + 1] = items[i] + work_items(kOrderSymmetric, nb);
+            diags[i + 1] = diags[i] + nb;
+        }
+        const WorkCounts<true> c{shape, items.data(), diags.data()};
+        for (int v : n) std::printf("%d ", v);
+        std::printf("|");
+        for (int lone = 0; lone < 2; ++lone)
+            for (int g = 0; g < 8; ++g) std::printf(" %d", work_share(c, B, g, 3, slots, true, lone != 0).ndef);
+        std::printf("/");
+        ++shapes;
+    }
+    return 0;
+}
+"""
+
+
+def test_shares_in_python_match_the_header(tmp_path):
+    from work_shares import deferred
+
+    head = DRIVER[:DRIVER.index("int main()")].replace("static void", "[[maybe_unused]] static void")
+    batches = [b for b in _run(tmp_path, head + SHARES_MAIN, str).split("/") if b]
+    assert len(batches) == 60
+    some = 0
+    for b in batches:
+        ns, got = ([int(v) for v in part.split()] for part in b.split("|"))
+        assert deferred(ns) + deferred(ns, lone=True) == got
+        some += any(got[:8])
+    assert some >= 10
 
 
 def test_lone_diagonals_are_deferred_once(tmp_path):
