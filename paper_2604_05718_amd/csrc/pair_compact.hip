@@ -19,7 +19,9 @@
 // (the workspace's sync region); the one counted last turns the counts into offsets in place
 // once its own writes are issued. Its chain of a store, an atomic, a load and a store to the
 // device's coherence point took 2 us of every launch: 64 images of 1024 tokens 7.6 -> 5.8 us, one
-// image 7.6 -> 6.3 us.
+// image 7.6 -> 6.3 us. Affinity of 64-byte rows and compaction, counted / added directly: 192
+// images of 64 rows 10.6 / 10.1 us and of 400 22.2 / 21.5, 256 of them 11.5 / 11.6 and 26.8 /
+// 27.0, 320 14.0 / 15.1 and 33.0 / 34.4.
 // Without the counters (neighbours given by the caller), a second one-workgroup launch scans
 // them. No workgroup ever waits for another.
 #include <algorithm>

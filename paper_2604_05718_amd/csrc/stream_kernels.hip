@@ -215,8 +215,11 @@ __global__ __launch_bounds__(kRowThreads) void pair_average_inv_kernel(
 // Lanes per row in the last pair average of a schedule: as inv_lanes, but at least a 128-byte
 // line's (or the whole row's, if shorter), and more, up to a wave, while the batch's `rows`
 // leave compute units without a workgroup and lanes of the row have vectors to take (nothing
-// but the split of the row over the lanes depends on it). One image of 1024 768-byte rows on 8
-// lanes a row: 32 workgroups, its schedule 18.1 us; on 64: 256 workgroups, 17.1 us.
+// but the split of the row over the lanes depends on it). Schedules replayed from a graph,
+// without / with more lanes: one image of 196 rows of 768 bytes, two insertions, 33.0 / 29.9 us,
+// of 1024 rows of 1536 bytes 45.2 / 42.3, of 2304 of 2048 bytes 70.5 / 67.9; four of 576 rows of
+// 1536 bytes 47.5 / 45.9; where the rows fill the chip (eight of 1024 768-byte rows, one of
+// 4096 2048-byte rows) the same.
 int scatter_lanes(int vpr, long rows)
 {
     int g = 1;
