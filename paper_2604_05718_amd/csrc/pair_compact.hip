@@ -286,18 +286,24 @@ __global__ __launch_bounds__(256) void reduce_partials_kernel(const float* __res
 // - / 7.3 / 8.8, 16 of 768-byte rows - / 5.2 / 4.0.
 constexpr int kBestLanes = 16, kFewLanes = 4;
 constexpr int kThreadPieces = 4, kFewPieces = 32;
+// A batch whose rows run in two turns of the chip on sixteen lanes, with more tiles than a lane takes in two
+// turns, reads its tiles on sixteen lanes at every width: it waits for its loads only. Two packed
+// images of up to 5249 16-byte rows (41 tiles), the query, one lane a row / sixteen: 25.2 / 21.0 us.
+constexpr long kWideRows = 1L << 16;
+constexpr int kWideTiles = 8;
 // Workgroups at most; a larger batch's rows are taken in turn, so that rows past their image's
 // end cost a test and no workgroup each (1380 images of at most 3487 rows, a twentieth of them
 // filled, on 16 lanes: 136 us with a workgroup for each 16 rows, 88 with these, 96 with 4096).
 constexpr long kBestGroups = 1L << 14;
 
 // The same reduction with the cosine of the chosen pair: the score divided by the query's own
-// norm. LANES lanes take a row: lane l its partial tiles l, l + LANES, ... and its 16-byte
-// pieces l, l + LANES, ..., four of either in flight; a butterfly over the lanes merges the
-// partials and adds the squares. Bound by memory: one thread a row read long rows one line per
+// norm. LANES lanes take a row: lane l its partial tiles l, l + LANES, ..., four in flight, merged
+// by a butterfly. The squares are summed by SUM lanes, lane l its 16-byte pieces l, l + SUM, ...,
+// four in flight, added by a butterfly (lanes past SUM repeat them): the order, and with it the
+// cosine, depends on the row's width only. Bound by memory: one thread a row read long rows one line per
 // lane, a piece at a time: 12.0 us on 16 images of 1024 768-byte rows (12.6 MB), 4.0 us on 16
 // lanes.
-template <class S, int LANES>
+template <class S, int LANES, int SUM>
 __global__ __launch_bounds__(256) void reduce_best_kernel(const float* __restrict__ pv,
                                                           const int32_t* __restrict__ pi,
                                                           const uint8_t* __restrict__ x,
@@ -338,11 +344,11 @@ __global__ __launch_bounds__(256) void reduce_best_kernel(const float* __restric
         const int pieces = (int)((long)D * S::kBytes / 16);
         const uint8_t* xr = x + ((long)row0 + i) * ((long)D * S::kBytes);
         float t2 = 0.0f;
-        for (int c0 = lane; c0 < pieces; c0 += 4 * LANES) {
+        for (int c0 = lane % SUM; c0 < pieces; c0 += 4 * SUM) {
             u32x4 w[4];
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
-                const int c = c0 + u * LANES;
+                const int c = c0 + u * SUM;
                 w[u] = c < pieces ? load16(xr + 16 * c) : u32x4{0u, 0u, 0u, 0u};
             }
 #pragma unroll
@@ -355,7 +361,7 @@ __global__ __launch_bounds__(256) void reduce_best_kernel(const float* __restric
             const bool c = ov > v || (ov == v && (uint32_t)oi < (uint32_t)j);
             v = c ? ov : v;
             j = c ? oi : j;
-            t2 += __shfl_xor(t2, o);
+            if (o < SUM) t2 += __shfl_xor(t2, o);
         }
         if (lane == 0) {
             nb[g] = j;
@@ -389,21 +395,29 @@ hipError_t launch_compact_t(const float* pv, const int32_t* pi, int T, int ct, i
     return hipGetLastError();
 }
 
-template <class S>
-void launch_best(int lanes, const float* pv, const int32_t* pi, const void* x, const int32_t* x_off, int B, int N, int D,
-                 int T, int ct, int32_t* nb, float* best, hipStream_t stream)
+template <class S, int LANES, int SUM>
+void launch_best_as(const float* pv, const int32_t* pi, const void* x, const int32_t* x_off, int B, int N, int D, int T,
+                    int ct, int32_t* nb, float* best, hipStream_t stream)
 {
-    const uint8_t* xp = static_cast<const uint8_t*>(x);
-    const long rows = 256 / lanes;
-    const dim3 grid((unsigned)std::min<long>(((long)B * N + rows - 1) / rows, kBestGroups)), block(256);
-    if (lanes == 1)
-        hipLaunchKernelGGL((reduce_best_kernel<S, 1>), grid, block, 0, stream, pv, pi, xp, x_off, B, N, D, T, ct, nb, best);
-    else if (lanes == kFewLanes)
-        hipLaunchKernelGGL((reduce_best_kernel<S, kFewLanes>), grid, block, 0, stream, pv, pi, xp, x_off, B, N, D, T, ct,
-                           nb, best);
-    else
-        hipLaunchKernelGGL((reduce_best_kernel<S, kBestLanes>), grid, block, 0, stream, pv, pi, xp, x_off, B, N, D, T, ct,
-                           nb, best);
+    constexpr long ROWS = 256 / LANES;
+    const dim3 grid((unsigned)std::min<long>(((long)B * N + ROWS - 1) / ROWS, kBestGroups));
+    hipLaunchKernelGGL((reduce_best_kernel<S, LANES, SUM>), grid, dim3(256), 0, stream, pv, pi,
+                       static_cast<const uint8_t*>(x), x_off, B, N, D, T, ct, nb, best);
+}
+
+template <class S>
+void launch_best(const float* pv, const int32_t* pi, const void* x, const int32_t* x_off, int B, int N, int D, int T,
+                 int ct, int32_t* nb, float* best, hipStream_t stream)
+{
+    const int pieces = D * S::kBytes / 16;
+    const bool wide = (long)B * N <= kWideRows && (N + ct - 1) / ct > kWideTiles;
+    if (pieces > kFewPieces) launch_best_as<S, kBestLanes, kBestLanes>(pv, pi, x, x_off, B, N, D, T, ct, nb, best, stream);
+    else if (pieces > kThreadPieces && wide)
+        launch_best_as<S, kBestLanes, kFewLanes>(pv, pi, x, x_off, B, N, D, T, ct, nb, best, stream);
+    else if (pieces > kThreadPieces)
+        launch_best_as<S, kFewLanes, kFewLanes>(pv, pi, x, x_off, B, N, D, T, ct, nb, best, stream);
+    else if (wide) launch_best_as<S, kBestLanes, 1>(pv, pi, x, x_off, B, N, D, T, ct, nb, best, stream);
+    else launch_best_as<S, 1, 1>(pv, pi, x, x_off, B, N, D, T, ct, nb, best, stream);
 }
 
 }  // namespace
@@ -437,10 +451,8 @@ hipError_t launch_reduce_partials(const float* pv, const int32_t* pi, int ct, co
                            x_off, B, N, T, ct, nb);
         return hipGetLastError();
     }
-    const int pieces = D * (dt == kBf16 ? 2 : 4) / 16;
-    const int lanes = pieces <= kThreadPieces ? 1 : pieces <= kFewPieces ? kFewLanes : kBestLanes;
-    if (dt == kBf16) launch_best<Bf16>(lanes, pv, pi, x, x_off, B, N, D, T, ct, nb, best, stream);
-    else launch_best<F32>(lanes, pv, pi, x, x_off, B, N, D, T, ct, nb, best, stream);
+    if (dt == kBf16) launch_best<Bf16>(pv, pi, x, x_off, B, N, D, T, ct, nb, best, stream);
+    else launch_best<F32>(pv, pi, x, x_off, B, N, D, T, ct, nb, best, stream);
     return hipGetLastError();
 }
 
