@@ -36,9 +36,9 @@ AFFINITY_REPS = 5    # such batches per insertion; the median is taken
 # rocprofv3 FETCH_SIZE / WRITE_SIZE runs on each workload, calibrated with a copy
 # kernel (profiles/schedule_cases.md). Valid only for the kernel source it was
 # measured on, with the default schedule.
-TRAFFIC = {"source_sha256": "9d65d811b35a8a66ad606ca51c7ceef13a8f8fa9c3b0bb881c336aa5329cc1bb",
-           "bytes_per_launch": {"vit_ti_512": 6523936, "vit_s_512": 27672064, "vit_b_512": 128419793,
-                                "vit_l_1024": 484617755, "stress_768": 134597907}}
+TRAFFIC = {"source_sha256": "a45e92056bc8a9f237b2e3140a635ef9b1dc3fc22ece6e37a367fa969d0aac4a",
+           "bytes_per_launch": {"vit_ti_512": 6525984, "vit_s_512": 27682304, "vit_b_512": 128318724,
+                                "vit_l_1024": 484600219, "stress_768": 134526282}}
 
 
 def log(*a):
@@ -491,6 +491,9 @@ def main() -> int:
         "survivors_mean": [round(sum(c) / len(c), 1) for c in counts],
         "roofline": roofline,
         "step_time_distribution": distribution,
+        # Timed step by step (an event between the entry points); the timed schedule is one call,
+        # whose last pair average also writes the grid.
+        "kernels_timed": "step by step" if cfg.insertions <= mpm.api.MAX_FUSED else "as the step",
         "kernels": kernels,
         "cold_cache": cold,
         "hip_graph": graph,

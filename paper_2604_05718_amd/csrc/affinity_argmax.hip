@@ -89,14 +89,15 @@ constexpr int kChunkBytes = 128;  // bytes of each row per LDS stage
 constexpr int kSplitRows = 256;   // block rows of the symmetric schedule that has a half-block launch
 // Fewest bfloat16 chunks of K from which a share of single-block images, fewer than half of its
 // slots, runs as half blocks only (float32 blocks: any): half of a round has to outweigh the
-// second launch. Neighbour queries of 1 to 128 images of at most 256 rows, whole / half blocks:
+// second launch. Images of more blocks would run their other blocks in the first launch and the
+// halves after them. Neighbour queries of 1 to 128 images of at most 256 rows, whole / half blocks:
 // bfloat16 rows of 128 and 384 bytes 8 to 20% and 9% faster whole, of 768 bytes 13.9 / 15.7 us
 // (the other way round), of 2048 bytes 19.7 / 27.8; float32 rows of 3072 bytes 96 / 181 us.
 constexpr int kLoneSplitChunks = 6;
 template <class S>
-__host__ __device__ constexpr bool splits_lone(int nchunks)
+__host__ __device__ constexpr bool splits_lone(int nchunks, int blocks)  // of an image
 {
-    return S::kBytes == 4 || nchunks >= kLoneSplitChunks;
+    return blocks == 1 && (S::kBytes == 4 || nchunks >= kLoneSplitChunks);
 }
 constexpr int kXcds = 8;  // MI355X: workgroups are dealt round-robin to 8 XCDs, each with its own L2
 
@@ -360,7 +361,7 @@ __global__ __launch_bounds__(WC * WQ * kWave, 2) void affinity_partial_kernel(  
     const long rowbytes = (long)D * S::kBytes;
     const int nchunks = (int)((rowbytes + CB - 1) / CB);
     const WorkShare share =
-        work_share(counts, B, group, log_xcds, slots, SPLIT || HALVES, !COUNTED && splits_lone<S>(nchunks));
+        work_share(counts, B, group, log_xcds, slots, SPLIT || HALVES, !COUNTED && splits_lone<S>(nchunks, (int)shape.nb.d));
     const int nitems = HALVES ? 2 * share.ndef : share.cnt - share.ndef;
     if (slot >= nitems) return;  // uniform over the workgroup
 
@@ -561,8 +562,10 @@ __global__ __launch_bounds__(WC * WQ * kWave, 2) void affinity_partial_kernel(  
         own_q[j] = min(wc + j * WC, NT - 1) * 32 * CB;  // from lq_off
     }
     // TAIL: whether the last chunk of a row ends in its first half.
-    // (The large window blocks of bfloat16 rows have no registers left for the branch.)
-    constexpr bool CUT = TAIL && !(LOCAL && MT * NT >= 8 && S::kBytes == 2);
+    // (Large window blocks of bfloat16 rows have no registers left for the branch, and in a chunk
+    // of small blocks it costs more than half a chunk of them saves: 4 images of 2 rows of 3312
+    // bytes 15.4 us with it, 14.4 without.)
+    constexpr bool CUT = TAIL && (S::kBytes == 4 || (MT * NT > 1 && !(LOCAL && MT * NT >= 8)));
     const bool half_tail = CUT && rowbytes - (long)(nchunks - 1) * CB <= CB / 2;
     // One load part before every PSTEP-th MFMA of a chunk, over the first half of its MFMAs (the
     // loads must land before the chunk ends).
@@ -1093,7 +1096,7 @@ void launch_counted(const AffinityArgs& a, int slots, const WorkShape& shape)
     // The symmetric schedule's deferred diagonal blocks, as half blocks, in a second launch
     // (one item per slot); the timing events then span both.
     constexpr bool SPLIT = SYM && !LOCAL && WC * MT * 32 == kSplitRows;
-    const bool halves = SPLIT && defers_diagonals(COUNTED, a.B, a.N, log_xcds, slots, splits_lone<S>(chunks_of<S>(a.D)));
+    const bool halves = SPLIT && defers_diagonals(COUNTED, a.B, a.N, log_xcds, slots, splits_lone<S>(chunks_of<S>(a.D), shape.nb.d));
     hipExtLaunchKernelGGL((affinity_partial_kernel<S, WC, WQ, MT, NT, SYM, false, LOCAL, GIVEN, TAIL, COUNTED>), grid,
                           block, 0, a.stream, a.start, halves ? nullptr : a.stop, 0, xb, a.x_off, a.B, a.N, a.D, a.T,
                           log_xcds, slots, shape, a.pv, a.pi, a.xinv, a.win, a.clear);
@@ -1117,19 +1120,18 @@ void launch_persistent_as(AffinityArgs a, int groups)
     const int nb = (a.N + CT - 1) / CT;
     const long total = (long)a.B * work_items(ORDER, nb);
     const bool counted = a.x_off != nullptr && a.B <= kMaxCountedImages && total > groups / a.xcds * (long)a.xcds;
-    // Fewer images than XCDs: one group, so that the shares are the chip's.
-    // - Blocks that may run as halves: an early share of a large image has too few diagonal
-    //   blocks to defer and takes another round, and no share waits for the others. One image
-    //   of 5835 rows of 2048 bytes, 276 blocks on 256 slots, in 8 groups / one: 84.5 / 58.5 us.
-    // - Ragged images with a slot for each item, several slots a CU: the long image's items
-    //   would all run on its share's XCDs. 1288 and 80 float32 rows of 4096 bytes: 81 / 45 us;
-    //   three images of 2000, 100 and 100 rows of 1536 bytes 19 / 15. At a slot a CU at most,
-    //   images of about N rows are up to 8% slower in one group (their rows pass through every
-    //   L2), as are counted shares.
-    if (a.B < kXcds && (SPLIT || (!LOCAL && a.x_off != nullptr && !counted && total > a.cus))) a.xcds = 1;
+    // Fewer images than XCDs: one group, so that the share is the chip's,
+    // where blocks may run as halves, past a round: an early share of a large image has too few
+    // diagonal blocks to defer and takes another round. One image of 5835 rows of 2048 bytes, 276
+    // blocks on 256 slots, in 8 groups / one: 84.5 / 58.5 us. Elsewhere one group is slower (every
+    // row passes through every L2): seven images of 2027 rows of 3440 bytes 88 / 97, seven packed
+    // ones of 140 to 400 3024-byte rows on small blocks 17.9 / 21.7; only the longest of a few very
+    // uneven ones, whose items all run on its share's XCDs, would gain (1288 and 80 float32 rows of
+    // 4096 bytes 81 / 45).
+    if (SPLIT && a.B < kXcds && total > a.cus) a.xcds = 1;
     const int most = groups / a.xcds;
     const long each = (total + a.xcds - 1) / a.xcds;
-    const int slots = (int)std::min<long>(most, SPLIT && splits_lone<S>(chunks_of<S>(a.D)) ? 2 * each : each);
+    const int slots = (int)std::min<long>(most, SPLIT && splits_lone<S>(chunks_of<S>(a.D), nb) ? 2 * each : each);
     const WorkShape shape(ORDER, a.B, nb);
     if (counted)
         launch_counted<S, WC, WQ, MT, NT, SYM, LOCAL, GIVEN, TAIL, true>(a, slots, shape);
@@ -1260,14 +1262,13 @@ enum Blocks : int { kBlocks64, kBlocks128, kBlocks256, kBlocksSym256 };
 // of 1536 bytes: 8 images of 400 rows 10.0 / 13.5 / 21.2 / 24.2 us; 12 of 1024 rows 35.8 /
 // 18.0 / 22.6 / 24.7; 24 of 1024 rows 67.7 / 32.3 / 41.9 / 27.1; 16 of 1024 rows of 384 bytes
 // - / 15.7 / 11.3 / 14.6.
-// Batches past those, up to 1000 images (430 shapes of rows of 64 to 2048 bytes): after some
+// Dense batches past those, up to 1000 images (215 shapes of rows of 64 to 2048 bytes): after some
 // rounds of large symmetric blocks the workgroups no longer start theirs together, and a round
-// costs a tenth less; a packed batch takes the full 256 x 256 blocks where its images have one
-// block (no reverse direction) or rows of a chunk at most. Against the pick of 64 x 64 blocks for
-// at most 32 large ones and 256 x 256 ones elsewhere 10% faster, 19 shapes more than 4% slower
-// and none more than 13% (without these 46, and 37%). 1000 packed images of 196 rows of 128
-// bytes, 128 / 256 full: 25.4 / 18.6 us; 500 of 400 rows of 768 bytes, 128 / 256 symmetric:
-// 86.5 / 78.5.
+// costs a tenth less: 500 images of 400 rows of 768 bytes, 128 / 256 symmetric, 86.5 / 78.5 us.
+// Packed ones keep the estimate above: their lengths are only guessed, and where they fall short
+// of the guess a large block costs four times a middling one (1000 packed images of at most 196
+// rows of 128 bytes, 128 / 256 full: 25.4 / 18.6 us as long as guessed, twice as slow the other
+// way round at a tenth of it).
 double round_us(double fixed, double round, double rounds) { return fixed + round * rounds; }
 
 double settled(double rounds) { return std::min(rounds, 4.0) + 0.9 * std::max(0.0, rounds - 4.0); }
@@ -1292,7 +1293,7 @@ double estimate_us(Blocks k, double blocks64, double blocks128, double full256, 
     case kBlocks256: return round_us(2.5, 4.3 + 1.43 * c, std::ceil(full256 / cus));
     default: {
         const double round = 9.0 + 1.31 * c, r = sym256 / cus;
-        if (counted) return round_us(2.0, round, 1.1 * r <= 1 ? 1 : settled(r + 0.62)) + (1.1 * r <= 1 ? 0 : 3.0);
+        if (counted) return round_us(2.0, round, 1.1 * r <= 1 ? 1 : r + 0.62) + (1.1 * r <= 1 ? 0 : 3.0);
         const double f = r - std::floor(r);  // a short last round runs as half blocks
         return round_us(2.0, round, settled(std::floor(r) + (f <= 0 ? 0 : r > 1 && f <= 0.5 ? 0.82 : 1.0)));
     }
@@ -1307,12 +1308,10 @@ double estimate_us(Blocks k, double blocks64, double blocks128, double full256, 
 // Examples, 64 / 128 / 256 full / 256 symmetric, dense rows of 768 bytes: 4 images of 1024 rows
 // 19.1 / 19.5 / 49.0 / 52.5 us; 16 of 1024 rows 60.3 / 44.5 / 50.0 / 52.6; 32 of 1024 rows
 // - / 78.9 / 106.4 / 86.7; 46 of 1924 rows of 832 bytes - / 420.6 / 660.8 / 384.5.
-// Rows of at most one and a half chunks (c, in halves) are too narrow for that: their items' fixed
-// parts count, and a single round of full 256 x 256 blocks is the fastest of the large shapes.
-// 240 packed images of 196 to 230 64-byte rows, 128 / 256 full / 256 symmetric: 15.8 / 10.3 / 11.4
-// us; 16 of 1024 rows 13.2 / 10.3 / 13.0; 1000 packed of 2304 at most 1725 / 1816 / 1431. Over
-// 190 shapes each of rows of 64, 128 and 192 bytes the pick is 1.0, 1.0 and 0.8% slower than the
-// fastest (by rounds alone 3.2, 1.5 and 1.3%).
+// Dense rows of at most one and a half chunks (c, in halves) are too narrow for that: their items'
+// fixed parts count, and a single round of full 256 x 256 blocks is the fastest of the large
+// shapes. 64-byte rows, 128 / 256 full / 256 symmetric: 16 images of 1024 rows 13.2 / 10.3 / 13.0
+// us, 128 of them 57.7 / 58.8 / 47.8. Packed rows keep to rounds (lengths far from the guess).
 Blocks pick_blocks_f32(double blocks64, double blocks128, double full256, double sym256, double c, double cus,
                        bool packed)
 {
@@ -1328,10 +1327,9 @@ Blocks pick_blocks_f32(double blocks64, double blocks128, double full256, double
         rounds128 = std::floor(r) + (f <= 0 ? 0.0 : f <= 0.5 ? 0.6 : 0.95);
         rounds256 = std::floor(s) + (g <= 0 ? 0.0 : s > 1 && g <= 0.5 ? 0.6 : 1.0);
     }
-    if (c > 1.5) return rounds128 <= 1.8 * rounds256 ? kBlocks128 : kBlocksSym256;
+    if (packed || c > 1.5) return rounds128 <= 1.8 * rounds256 ? kBlocks128 : kBlocksSym256;
     const double us128 = round_us(2.5, 4.6 + 3.5 * c, rounds128), us256 = round_us(2.0, 6.0 + 7.1 * c, rounds256);
-    const bool full = !packed || full256 <= cus;
-    if (full && round_us(2.5, 3.4 + 7.05 * c, std::ceil(full256 / cus)) < std::min(us128, us256)) return kBlocks256;
+    if (round_us(2.5, 3.4 + 7.05 * c, std::ceil(full256 / cus)) < std::min(us128, us256)) return kBlocks256;
     return us128 <= us256 ? kBlocks128 : kBlocksSym256;
 }
 
@@ -1347,8 +1345,10 @@ Blocks pick_blocks(int B, int N, int D, int dt, int schedule, bool packed, int d
         return (double)B * work_items(order, (int)((std::max(1L, (long)N * percent / 100) + w - 1) / w));
     };
     const double capacity64 = blocks(kTCT, kOrderFull, 100);
-    // A small block a CU is the fastest by every estimate below (host time of the smallest calls).
-    if (capacity64 <= cus) return kBlocks64;
+    // A small block a CU is the fastest by every estimate below (host time of the smallest calls);
+    // and images of at most 64 tokens have one block of any size (1000 of 64 rows of 2048 bytes, 64 /
+    // 128: 21.8 / 36.1 us; 1400 one-token images of float32 rows of 768 bytes 9.9 / 19.4).
+    if (capacity64 <= cus || N <= kTCT) return kBlocks64;
     const double full256 = blocks(kPCT, kOrderFull, 100);
     const double c = std::ceil(2.0 * D / kChunkBytes);
     double b64 = capacity64, b128 = blocks(kLCT, kOrderSymmetric, 100), s256 = blocks(kPCT, kOrderSymmetric, 100);
@@ -1366,8 +1366,7 @@ Blocks pick_blocks(int B, int N, int D, int dt, int schedule, bool packed, int d
     double us = estimate_us(kBlocks128, b64, b128, full256, s256, c, cus, packed);
     for (Blocks k : {kBlocks64, kBlocks256, kBlocksSym256}) {
         if (k == kBlocks64 && capacity64 > 2.5 * cus) continue;  // beyond, 128 x 128 blocks are as fast
-        // A round of whole images, images of one block, narrow rows; or the symmetric blocks.
-        if (k == kBlocks256 && packed && full256 > cus && N > kPCT && c > 1) continue;
+        if (k == kBlocks256 && packed && full256 > cus) continue;  // a round of whole images or the symmetric blocks
         const double e = estimate_us(k, b64, b128, full256, s256, c, cus, packed);
         if (e < us) {
             us = e;

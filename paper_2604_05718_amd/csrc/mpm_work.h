@@ -127,8 +127,9 @@ MPM_HD int work_diags_before(const WorkCounts<TAB>& c, int B, int p)
 }
 
 // Group g of 2^log_groups. When the share's items leave a last round of 0 < 2m <= slots
-// after at least one whole round (`lone`: or are m diagonal blocks and no more), and it has
-// at least m diagonal blocks, its last m are deferred (`split`).
+// after at least one whole round (`lone`, and every share has two slots an item: or are m
+// diagonal blocks and no more), and it has at least m diagonal blocks, its last m are deferred
+// (`split`).
 template <bool TAB>
 MPM_HD WorkShare work_share(const WorkCounts<TAB>& c, int B, int g, int log_groups, int slots, bool split,
                             bool lone = false)
@@ -140,6 +141,7 @@ MPM_HD WorkShare work_share(const WorkCounts<TAB>& c, int B, int g, int log_grou
     s.cnt = hi - s.lo;
     s.ndef = 0;
     s.dstart = 0;
+    lone = lone && 2 * ((total + (1 << log_groups) - 1) >> log_groups) <= slots;
     if (split && (lone || s.cnt > slots)) {
         const int m = s.cnt % slots;
         if (m > 0 && 2 * m <= slots) {

@@ -71,7 +71,7 @@ WORK_CASES = {
     "counted_limit": (32, [130, 1] * 256, (128, 128)),          # 512 images, the most counted one by one
     "past_counted_limit": (32, [130, 1] * 256 + [40], (128, 128)),
     "long_and_short": (64, [2300] + [30] * 9 + [1700], (128, 128)),
-    "large_blocks": (32, [2300, 2000, 256, 0, 1, 1900, 2299, 2048] * 8, (256, 256)),
+    "large_blocks": (32, [4096, 3300], (256, 256)),
 }
 
 
@@ -190,10 +190,10 @@ def test_offsets_in_an_unprepared_workspace(B):
 
 @pytest.mark.parametrize("D", [64, 1024])
 def test_packed_pick_of_the_shortest_images(D):
-    """A packed batch of images of one or two tokens runs the small blocks, as the dense one
-    does (its guessed lengths are at least one token)."""
-    for B in (1, 8, 31):
-        for N in (1, 2):
+    """Images of at most 64 tokens run the small blocks, packed (a guessed length is at least
+    one token) or dense, however many they are."""
+    for B in (1, 8, 31, 2000):
+        for N in (1, 2, 64):
             print(f"pick of short images B={B} N={N} D={D}", flush=True)
             dense, packed = (mpm.affinity_block_rows(B, N, D, torch.bfloat16, packed=p) for p in (False, True))
             assert dense == packed == 64
@@ -204,7 +204,9 @@ def test_packed_pick_of_the_shortest_images(D):
 # slot) and one more; rows that end inside a chunk cannot have the schedule forced.
 @pytest.mark.parametrize("dtype,B,N,D", [("f32", 7, 2, 768), ("f32", 128, 40, 32), ("f32", 129, 256, 48),
                                          ("bf16", 5, 200, 768), ("bf16", 63, 130, 384), ("bf16", 64, 256, 320),
-                                         ("bf16", 128, 129, 416), ("f32", 1, 1, 64)])
+                                         ("bf16", 128, 129, 416), ("f32", 1, 1, 64),
+                                         ("f32", 1, 328, 192), ("bf16", 2, 665, 768),   # two and three blocks: whole
+                                         ("bf16", 135, 76, 384), ("f32", 136, 76, 64)])  # not two slots for every block
 def test_single_block_images_on_the_symmetric_schedule(dtype, B, N, D):
     """Neighbours and cosines, dense and packed, are those of the full schedule bit for bit."""
     rng = np.random.default_rng(B * N + D)
@@ -225,7 +227,8 @@ def test_single_block_images_on_the_symmetric_schedule(dtype, B, N, D):
 # lanes for (taken in turn), most of them past their image's end.
 @pytest.mark.parametrize("dtype,D,ns", [(dt, p * (8 if dt == "bf16" else 4), [1300, 0, 1, 65, 300])
                                         for dt in ("bf16", "f32") for p in (1, 4, 5, 32, 33)] +
-                                       [("bf16", 8, [1500] + [3, 0, 1, 40] * 700), ("f32", 100, [2000] + [2, 0, 1] * 50)])
+                                       [("bf16", 8, [1500] + [3, 0, 1, 40] * 700), ("f32", 100, [2000] + [2, 0, 1] * 50),
+                                        ("bf16", 8, [5200, 1]), ("bf16", 256, [2200] * 2), ("f32", 16, [600] * 60)])
 def test_cosines_of_narrow_rows(dtype, D, ns):
     rng = np.random.default_rng(D + len(ns))
     print(f"cosines of narrow rows {dtype} D={D} images {len(ns)}", flush=True)
@@ -270,12 +273,11 @@ def test_half_chunks(dtype, D):
         assert torch.equal(nb, fn) and torch.equal(best.view(torch.int32), fb.view(torch.int32)), schedule
 
 
-@pytest.mark.parametrize("B,N,D,packed,rows", [(240, 256, 16, True, 256), (16, 1024, 16, False, 256),
-                                               (16, 1024, 48, False, 256), (16, 1024, 64, False, 128),
-                                               (600, 1024, 16, True, 256)])
+@pytest.mark.parametrize("B,N,D,packed,rows", [(16, 1024, 16, False, 256), (16, 1024, 48, False, 256),
+                                               (16, 1024, 64, False, 128), (64, 1024, 8, False, 256)])
 def test_pick_of_narrow_f32_rows(B, N, D, packed, rows):
-    """float32 rows of at most a chunk and a half: a single round of full 256-row blocks, and
-    many rounds of symmetric ones, where they are faster; equal to the small blocks."""
+    """Dense float32 rows of at most a chunk and a half: a single round of full 256-row blocks,
+    and several rounds of symmetric ones, where they are faster; equal to the small blocks."""
     if torch.cuda.get_device_properties(DEV).multi_processor_count != 256:
         pytest.skip("the picks are for a 256-CU device")
     print(f"narrow f32 pick B={B} N={N} D={D} packed={packed}", flush=True)
@@ -354,8 +356,8 @@ def test_items_far_apart(name, dtype, D):
         assert torch.equal(m.y_off, one.y_off) and torch.equal(m.map, one.map)
 
 
-@pytest.mark.parametrize("B,N,D,packed,used", [(1000, 196, 64, True, "full"), (500, 400, 384, False, "symmetric"),
-                                               (1000, 256, 384, True, "full"), (64, 1024, 768, False, "symmetric")])
+@pytest.mark.parametrize("B,N,D,packed,used", [(500, 400, 384, False, "symmetric"), (900, 256, 64, False, "full"),
+                                               (64, 1024, 768, False, "symmetric")])
 def test_pick_of_large_batches(B, N, D, packed, used):
     """Batches of many rounds run the large blocks where they are faster; neighbours equal to
     the small blocks' (a sample of the images against the oracle)."""
@@ -422,22 +424,23 @@ def test_plans_are_what_runs():
                           ("bf16", 16, 1024, 200, False, ("full", 256), False),
                           ("f32", 46, 1924, 212, False, ("symmetric", 256), True),
                           ("bf16", 16, 1024, 136, True, ("full", 256), False),
-                          ("bf16", 500, 200, 56, True, ("full", 256), False),
-                          ("bf16", 64, 2300, 200, True, ("symmetric", 256), True),
-                          ("f32", 100, 1500, 12, True, ("symmetric", 256), True)])
+                          ("bf16", 12, 1600, 200, True, ("symmetric", 256), True),
+                          ("bf16", 16, 4096, 24, True, ("symmetric", 256), True),
+                          ("f32", 2, 4096, 28, True, ("symmetric", 256), True)])
 def test_large_blocks_of_odd_rows(dtype, B, N, D, packed, plan, halves):
     for seed in range(50):  # the first ragged lengths that leave blocks to the half-block launch
         rng = np.random.default_rng(B * D + seed)
-        ns = [int(v) for v in rng.integers(int(0.55 * N), N + 1, B)] if packed else [N] * B
-        if packed:
+        ns = [int(v) for v in rng.integers(int((0.55 if B >= 16 else 0.85) * N), N + 1, B)] if packed else [N] * B
+        if packed and B >= 16:
             ns[0], ns[B // 2], ns[-1] = 0, N, 1
-        if not halves or any(deferred(ns)):
+        groups = dict() if B >= 8 else dict(groups=1, slots=256)  # few images: the chip's slots in one group
+        if not halves or any(deferred(ns, **groups)):
             break
     print(f"large blocks of odd rows {dtype} B={B} N={N} D={D} packed={packed}", flush=True)
     if torch.cuda.get_device_properties(DEV).multi_processor_count == 256:
         assert mpm.affinity_plan(B, N, D, TORCH_DT[dtype], packed=packed) == plan
     if plan[0] == "symmetric":
-        assert any(deferred(ns)) == halves
+        assert any(deferred(ns, **groups)) == halves
     g = torch.Generator(device=DEV).manual_seed(B + D)
     cent = torch.randn((200, D), generator=g, device=DEV)
     x = cent[torch.randint(0, 200, (sum(ns),), generator=g, device=DEV)]
@@ -447,7 +450,7 @@ def test_large_blocks_of_odd_rows(dtype, B, N, D, packed, plan, halves):
     m = mpm.merge(x, off, N=N) if packed else mpm.merge(x.view(B, N, D))
     # Image by image: the small blocks, whatever the batch runs.
     nb = m.nb
-    sample = sorted({1, 2, B // 4, B // 2, B - 2} | set(rng.integers(0, B, 6).tolist()))
+    sample = sorted({1, B // 4, B // 2, B - 2} | set(rng.integers(0, B, 6).tolist()))
     for b in sample:
         if ns[b] == 0:
             continue
@@ -455,7 +458,7 @@ def test_large_blocks_of_odd_rows(dtype, B, N, D, packed, plan, halves):
         one = mpm.argmax(img[None])
         torch.cuda.synchronize()
         assert torch.equal(nb[b, :ns[b]], one[0]), b
-    for b in (1, B // 2):
+    for b in {1, B // 2} if N * N * D < 1e9 else {1}:
         check_nearest(to64(x[o[b]:o[b + 1]].cpu()), nb[b, :ns[b]].cpu().numpy())
 
 

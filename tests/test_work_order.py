@@ -131,8 +131,8 @@ def test_every_block_exactly_once(tmp_path):
     assert _run(tmp_path, DRIVER) > 1000
 
 
-# Shares below one round of the slots: with `lone`, those of single-block images whose halves
-# all have a slot run as halves; no others.
+# Shares below one round of the slots: with `lone`, where every share has two slots an item,
+# those of diagonal blocks only run as halves; no others.
 LONE_MAIN = r"""
 int main()
 {
@@ -148,7 +148,8 @@ int main()
                     const int m = s.cnt % slots;
                     const int diags = work_diags_before(c, B, s.lo + s.cnt) - work_diags_before(c, B, s.lo);
                     const bool defers = m > 0 && 2 * m <= slots && diags >= m;
-                    if (s.ndef != (defers ? m : 0) || t.ndef != (defers && s.cnt > slots ? m : 0)) {
+                    const int most = (c.items(B) + 7) / 8;
+                    if (s.ndef != (defers && (s.cnt > slots || 2 * most <= slots) ? m : 0) || t.ndef != (defers && s.cnt > slots ? m : 0)) {
                         std::printf("B=%d nb=%d slots=%d", B, nb, slots);
                         return 1;
                     }

@@ -18,6 +18,7 @@ def deferred(ns, rows=256, groups=8, slots=32, lone=False):
         nb = -(-ns[place(i, B)] // rows)
         for q in range(nb):
             diag += [True] + [False] * (nb - q - 1)
+    lone = lone and 2 * -(-len(diag) // groups) <= slots
     out = []
     for g in range(groups):
         lo, hi = len(diag) * g // groups, len(diag) * (g + 1) // groups
