@@ -36,9 +36,9 @@ AFFINITY_REPS = 5    # such batches per insertion; the median is taken
 # rocprofv3 FETCH_SIZE / WRITE_SIZE runs on each workload, calibrated with a copy
 # kernel (profiles/schedule_cases.md). Valid only for the kernel source it was
 # measured on, with the default schedule.
-TRAFFIC = {"source_sha256": "a45e92056bc8a9f237b2e3140a635ef9b1dc3fc22ece6e37a367fa969d0aac4a",
-           "bytes_per_launch": {"vit_ti_512": 6525984, "vit_s_512": 27682304, "vit_b_512": 128318724,
-                                "vit_l_1024": 484600219, "stress_768": 134526282}}
+TRAFFIC = {"source_sha256": "32d68f79e94f75ef0402e6f3c43e6b3d30f21775095524660a3e996f6090c730",
+           "bytes_per_launch": {"vit_ti_512": 6532128, "vit_s_512": 27681280, "vit_b_512": 128536473,
+                                "vit_l_1024": 484660947, "stress_768": 134442557}}
 
 
 def log(*a):
