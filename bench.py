@@ -36,7 +36,7 @@ AFFINITY_REPS = 5    # such batches per insertion; the median is taken
 # rocprofv3 FETCH_SIZE / WRITE_SIZE runs on each workload, calibrated with a copy
 # kernel (profiles/schedule_cases.md). Valid only for the kernel source it was
 # measured on, with the default schedule.
-TRAFFIC = {"source_sha256": "32d68f79e94f75ef0402e6f3c43e6b3d30f21775095524660a3e996f6090c730",
+TRAFFIC = {"source_sha256": "e8539ceef30d7525a5728e5314070ee62a3b293e3694bbf92f6ee03cfc06665e",
            "bytes_per_launch": {"vit_ti_512": 6532128, "vit_s_512": 27681280, "vit_b_512": 128536473,
                                 "vit_l_1024": 484660947, "stress_768": 134442557}}
 

@@ -87,12 +87,12 @@ struct Mfma<F32> {
 
 constexpr int kChunkBytes = 128;  // bytes of each row per LDS stage
 constexpr int kSplitRows = 256;   // block rows of the symmetric schedule that has a half-block launch
-// Fewest bfloat16 chunks of K from which a share of single-block images, fewer than half of its
-// slots, runs as half blocks only (float32 blocks: any): half of a round has to outweigh the
-// second launch. Images of more blocks would run their other blocks in the first launch and the
-// halves after them. Neighbour queries of 1 to 128 images of at most 256 rows, whole / half blocks:
-// bfloat16 rows of 128 and 384 bytes 8 to 20% and 9% faster whole, of 768 bytes 13.9 / 15.7 us
-// (the other way round), of 2048 bytes 19.7 / 27.8; float32 rows of 3072 bytes 96 / 181 us.
+// Fewest bfloat16 chunks of K from which a batch of single-block images with two slots for each
+// runs as half blocks only (float32 blocks: any): half of a round has to outweigh the second
+// launch. Images of more blocks would run their other blocks in the first launch and the halves
+// after them. Neighbour queries of 1 to 128 images of at most 256 rows, whole / half blocks:
+// bfloat16 rows of 768 bytes 15.7 / 13.9 us, of 2048 bytes 27.8 / 19.7, float32 rows of 3072
+// bytes 181 / 96; bfloat16 rows of 128 and 384 bytes are 8 to 20% and 9% faster whole.
 constexpr int kLoneSplitChunks = 6;
 template <class S>
 __host__ __device__ constexpr bool splits_lone(int nchunks, int blocks)  // of an image
@@ -498,7 +498,7 @@ __global__ __launch_bounds__(WC * WQ * kWave, 2) void affinity_partial_kernel(  
     // loads, or, for window items, behind the last loads (their next tile is found in a few
     // instructions; before the loads it delayed every one of a lone workgroup's, 2538 images of
     // 24 rows of 2048 bytes 103 us against 97. Found behind the loads, the next item of 128 x 128
-    // dense blocks cost 6%: 32 images of 900 rows of 1536 bytes 42.4 us against 39.9).
+    // dense blocks cost 5%: 32 images of 900 rows of 1536 bytes 42.2 us against 40.3).
     auto advance = [&]() {
         if (ichunk < nchunks) return;
         ichunk = 0;
@@ -1096,7 +1096,8 @@ void launch_counted(const AffinityArgs& a, int slots, const WorkShape& shape)
     // The symmetric schedule's deferred diagonal blocks, as half blocks, in a second launch
     // (one item per slot); the timing events then span both.
     constexpr bool SPLIT = SYM && !LOCAL && WC * MT * 32 == kSplitRows;
-    const bool halves = SPLIT && defers_diagonals(COUNTED, a.B, a.N, log_xcds, slots, splits_lone<S>(chunks_of<S>(a.D), shape.nb.d));
+    const bool lone = splits_lone<S>(chunks_of<S>(a.D), (int)shape.nb.d);
+    const bool halves = SPLIT && defers_diagonals(COUNTED, a.B, a.N, log_xcds, slots, lone);
     hipExtLaunchKernelGGL((affinity_partial_kernel<S, WC, WQ, MT, NT, SYM, false, LOCAL, GIVEN, TAIL, COUNTED>), grid,
                           block, 0, a.stream, a.start, halves ? nullptr : a.stop, 0, xb, a.x_off, a.B, a.N, a.D, a.T,
                           log_xcds, slots, shape, a.pv, a.pi, a.xinv, a.win, a.clear);
@@ -1120,14 +1121,13 @@ void launch_persistent_as(AffinityArgs a, int groups)
     const int nb = (a.N + CT - 1) / CT;
     const long total = (long)a.B * work_items(ORDER, nb);
     const bool counted = a.x_off != nullptr && a.B <= kMaxCountedImages && total > groups / a.xcds * (long)a.xcds;
-    // Fewer images than XCDs: one group, so that the share is the chip's,
-    // where blocks may run as halves, past a round: an early share of a large image has too few
-    // diagonal blocks to defer and takes another round. One image of 5835 rows of 2048 bytes, 276
-    // blocks on 256 slots, in 8 groups / one: 84.5 / 58.5 us. Elsewhere one group is slower (every
-    // row passes through every L2): seven images of 2027 rows of 3440 bytes 88 / 97, seven packed
-    // ones of 140 to 400 3024-byte rows on small blocks 17.9 / 21.7; only the longest of a few very
-    // uneven ones, whose items all run on its share's XCDs, would gain (1288 and 80 float32 rows of
-    // 4096 bytes 81 / 45).
+    // Fewer images than XCDs: one group, so that the share is the chip's, where blocks may run as
+    // halves, past a round. An early share of a large image has too few diagonal blocks to defer
+    // and takes another round: one image of 5835 rows of 2048 bytes, 276 blocks on 256 slots, in 8
+    // groups / one 84.5 / 58.5 us. Elsewhere one group is slower (every row passes through every
+    // L2): seven images of 2027 rows of 3440 bytes 88 / 97, seven packed ones of 140 to 400
+    // 3024-byte rows on small blocks 17.9 / 21.7; only a few very uneven images, the longest one's
+    // items all on its share's XCDs, would gain (1288 and 80 float32 rows of 4096 bytes 81 / 45).
     if (SPLIT && a.B < kXcds && total > a.cus) a.xcds = 1;
     const int most = groups / a.xcds;
     const long each = (total + a.xcds - 1) / a.xcds;
@@ -1301,13 +1301,14 @@ double estimate_us(Blocks k, double blocks64, double blocks128, double full256, 
 }
 
 // float32 rows: a block's matrix work outweighs the rest of it, so only the rounds count, in
-// units of a round of 128 x 128 symmetric blocks (two per CU); one of 256 x 256 blocks takes 1.8. Up to four 64 x 64 blocks a CU run as fast as the rest of the chip allows
-// (they are whole rounds of a quarter of the work). Timed on 170 dense and 170 packed shapes, 1 to
-// 64 images of 100 to 4096 rows of 192 to 4096 bytes: 0.6% slower than the fastest of the four
-// shapes, against 59% for 64 x 64 blocks of at most 32 large blocks and 256 x 256 ones elsewhere.
-// Examples, 64 / 128 / 256 full / 256 symmetric, dense rows of 768 bytes: 4 images of 1024 rows
-// 19.1 / 19.5 / 49.0 / 52.5 us; 16 of 1024 rows 60.3 / 44.5 / 50.0 / 52.6; 32 of 1024 rows
-// - / 78.9 / 106.4 / 86.7; 46 of 1924 rows of 832 bytes - / 420.6 / 660.8 / 384.5.
+// units of a round of 128 x 128 symmetric blocks (two per CU); one of 256 x 256 blocks takes
+// 1.8. Up to four 64 x 64 blocks a CU run as fast as the rest of the chip allows (they are whole
+// rounds of a quarter of the work). Timed on 170 dense and 170 packed shapes, 1 to 64 images of
+// 100 to 4096 rows of 192 to 4096 bytes: 0.6% slower than the fastest of the four shapes, against
+// 59% for 64 x 64 blocks of at most 32 large blocks and 256 x 256 ones elsewhere. Examples, 64 /
+// 128 / 256 full / 256 symmetric, dense rows of 768 bytes: 4 images of 1024 rows 19.1 / 19.5 /
+// 49.0 / 52.5 us; 16 of 1024 rows 60.3 / 44.5 / 50.0 / 52.6; 32 of 1024 rows - / 78.9 / 106.4 /
+// 86.7; 46 of 1924 rows of 832 bytes - / 420.6 / 660.8 / 384.5.
 // Dense rows of at most one and a half chunks (c, in halves) are too narrow for that: their items'
 // fixed parts count, and a single round of full 256 x 256 blocks is the fastest of the large
 // shapes. 64-byte rows, 128 / 256 full / 256 symmetric: 16 images of 1024 rows 13.2 / 10.3 / 13.0
